@@ -139,7 +139,7 @@ struct DevBuf {
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // ----------------------------------------------------------------------------- dense FP64 kernels
-constexpr int NB = 64;  // block size of the blocked Cholesky and triangular solves
+constexpr int NB = 128;  // block size of the blocked Cholesky and triangular solves
 
 // C = alpha op(A) op(B) + beta C (column-major).  lower: only entries with m >= n are written.
 void dgemm(hipStream_t s, bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha,
@@ -228,7 +228,7 @@ struct Envelope {
 // n x n symmetric matrix A (lower triangle).  Rows >= n_fac are dense
 // ("boundary") rows; the trailing block A[n_fac:, n_fac:] is NOT updated here
 // (use schur_update).  dinv receives the inverse of every NB x NB diagonal
-// block (cdiv(n_fac, NB) * NB * NB doubles).  A non-positive pivot sets *status.
+// block by rows (cdiv(n_fac, NB) * NB * NB doubles).  A non-positive pivot sets *status.
 void potrf(hipStream_t s, double* A, int64_t lda, int64_t n, int64_t n_fac, const Envelope& env,
            double* dinv, int* status);
 // A[n_fac:, n_fac:] -= L_b L_b^T  with L_b = A[n_fac:, :n_fac] (lower triangle).
@@ -244,7 +244,7 @@ void trsm(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double* 
 void mirror_envelope(hipStream_t s, double* A, int64_t lda, int64_t n, const Envelope& env);
 
 // fill / copy helpers
-// Y = (L L^T)^{-1} (full, symmetric) from a dense lower Cholesky factor and its inverted diagonal blocks
+// Y = (L L^T)^{-1}, lower triangle only, from a dense lower Cholesky factor and its inverted diagonal blocks
 void potri_lower(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double* dinv, double* Y,
                  int64_t ldy);
 void fill(hipStream_t s, double* p, int64_t count, double v);
@@ -252,7 +252,10 @@ void fill_matrix(hipStream_t s, double* p, int64_t rows, int64_t cols, int64_t l
 void copy_matrix(hipStream_t s, const double* src, int64_t lds, double* dst, int64_t ldd, int64_t rows,
                  int64_t cols);
 void mirror_lower(hipStream_t s, double* A, int64_t lda, int64_t n);  // upper <- lower^T
-void add_diag(hipStream_t s, double* A, int64_t lda, int64_t n, double v);
+// B = A + alpha Z Z^T + sigma I from the lower triangle of A (n x n), Z n x k with ld n (k <= 8): the
+// lower triangle of B, and with `full` its mirrored upper one; B may be A
+void add_outer(hipStream_t s, int64_t n, const double* A, int64_t lda, int k, const double* Z, double alpha,
+               double sigma, double* B, int64_t ldb, bool full);
 
 // Symmetric eigen-decomposition of small m x m matrices (m <= 64), one
 // workgroup each: A (m x m, ld m, column-major) -> V (columns), w ascending.

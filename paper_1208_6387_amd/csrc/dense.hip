@@ -25,12 +25,12 @@ namespace rpf {
 // One output tile (tx, ty) of K split z, called with the same tile by every thread of the
 // workgroup (consecutive tiles of the grouped kernel reuse the LDS: the barrier that opens each k
 // stage orders a tile's stores after the previous tile's reads).
-template <int BM, int BN, int WGM, int WGN, bool TA, bool TB>
+template <int BM, int BN, int WGM, int WGN, bool TA, bool TB, int BK = 16>
 __device__ __forceinline__ void dgemm_tile(int64_t M, int64_t N, int64_t K, double alpha, const double* A,
                                            int64_t lda, const double* B, int64_t ldb, double beta, double* C,
                                            int64_t ldc, int lower, int64_t kchunk, double* part, int tx, int ty,
                                            int z) {
-  constexpr int BK = 16, PAD = 2;
+  constexpr int PAD = 2;
   constexpr int WTM = BM / WGM, WTN = BN / WGN, TM = WTM / 16, TN = WTN / 16;
   constexpr int EA = BM * BK / 256, EB = BN * BK / 256;
   static_assert(WGM * WGN == 4 && TM >= 1 && TN >= 1 && EA >= 1 && EB >= 1, "bad tile");
@@ -126,14 +126,14 @@ __device__ __forceinline__ void dgemm_tile(int64_t M, int64_t N, int64_t K, doub
       }
 }
 
-template <int BM, int BN, int WGM, int WGN, bool TA, bool TB>
+template <int BM, int BN, int WGM, int WGN, bool TA, bool TB, int BK = 16>
 __global__ __launch_bounds__(256) void k_dgemm(int64_t M, int64_t N, int64_t K, double alpha,
                                                const double* A, int64_t lda, const double* B,
                                                int64_t ldb, double beta, double* C, int64_t ldc,
                                                int lower, int64_t kchunk, double* part) {
   int tx, ty;
   xcd_tile(gridDim.x, gridDim.y, tx, ty);
-  dgemm_tile<BM, BN, WGM, WGN, TA, TB>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, lower, kchunk, part, tx, ty,
+  dgemm_tile<BM, BN, WGM, WGN, TA, TB, BK>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, lower, kchunk, part, tx, ty,
                                        blockIdx.z);
 }
 
@@ -1609,170 +1609,227 @@ void rows_gemm(hipStream_t s, int64_t N, int a, int b, double alpha, const doubl
 }
 
 // ============================================================================ Cholesky
-// One NB x NB diagonal block (NB = 64), blocked by 16: four steps, each (1) factors its 16 x 16
-// diagonal block and inverts it on one wavefront (lane r holds row r in registers; the column
-// values of the other rows come by cross-lane shuffles, no LDS round trips), (2) solves the panel
-// below it, L21 = A21 L11^{-T}, and (3) updates the trailing lower triangle, A22 -= L21 L21^T, both
-// on all 256 threads from LDS.  The inverse factor is then assembled block row by block row:
-// W_ik = -W_ii sum_{j=k}^{i-1} L_ij W_jk.  A single right-looking wavefront needs either ~20k
-// unrolled instructions (more than the instruction cache holds) or 64 dependent steps over LDS;
-// this form has 4 short serial steps.  Rows and columns beyond jb are padded with the identity.
-// Value of v in lane src of the wavefront, src uniform (here a compile-time constant once the
-// loops are unrolled): two v_readlane into scalar registers, no LDS round trip as a shuffle takes.
-__device__ inline double lane_value(double v, int src) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
-  return __hiloint2double(hi, lo);
+// Value of v in lane J of this lane's row of sixteen: one cross-lane move, no scalar registers and no LDS.
+template <int J>
+__device__ __forceinline__ double row_lane(double v) {
+  return __builtin_amdgcn_update_dpp(v, v, 0x150 + J, 0xf, 0xf, true);
 }
 
-__global__ __launch_bounds__(256) void k_potrf_diag(double* Ag, int64_t lda, int jb, double* dinv, int* status,
+// 1 / d and 1 / sqrt(d) by one third-order step on the hardware estimates (within an ulp of the division),
+// d well inside the range of the format: they stand on the serial chain of the factorisation.
+__device__ __forceinline__ double pivot_recip(double d) {
+  const double r = __builtin_amdgcn_rcp(d), e = __builtin_fma(-d, r, 1.0);
+  return __builtin_fma(__builtin_fma(e, e, e), r, r);
+}
+__device__ __forceinline__ double pivot_rsqrt(double d) {
+  const double y = __builtin_amdgcn_rsq(d), h = d * y;
+  const double e = __builtin_fma(-h, y, 1.0) - __builtin_fma(d, y, -h) * y;  // 1 - d y y, d y unrounded
+  return __builtin_fma(e * y, __builtin_fma(0.375, e, 0.5), y);
+}
+
+// Steps J .. 15 of the elimination of a symmetric 16 x 16 tile and of the identity beside it: lane c of
+// every row of sixteen holds column c of each (a, x), and both take the same row operations
+// row_i -= (a_iJ / d_J) row_J; r = 1 / d_J.  At the end a_j (j <= c) is d_j l_cj and x is the inverse of
+// the unit factor.  Row J + 1 goes first, so that the next reciprocal runs under the rest of the step.
+template <int J = 0>
+__device__ __forceinline__ void eliminate(double (&a)[16], double (&x)[16], double r) {
+  if constexpr (J < 15) {
+    const double ta = -a[J] * r, tx = -x[J] * r;
+    double next = 0.0;
+#pragma unroll
+    for (int i = J + 1; i < 16; ++i) {
+      const double f = row_lane<J>(a[i]);
+      a[i] = __builtin_fma(f, ta, a[i]);
+      x[i] = __builtin_fma(f, tx, x[i]);
+      if (i == J + 1) next = pivot_recip(row_lane<J + 1>(a[J + 1]));
+    }
+    // keeps x beside a: left alone, the compiler runs a through all steps first and spills the factors
+#pragma unroll
+    for (int i = J + 1; i < 16; ++i) asm volatile("" : "+v"(a[i]), "+v"(x[i]));
+    eliminate<J + 1>(a, x, next);
+  }
+}
+template <int J = 0>
+__device__ __forceinline__ void scale_rows(double (&a)[16], double (&x)[16], double rs) {
+  if constexpr (J < 16) {
+    const double f = row_lane<J>(rs);
+    a[J] *= f;
+    x[J] *= f;
+    scale_rows<J + 1>(a, x, rs);
+  }
+}
+
+// One NB x NB (128 x 128) diagonal block: its Cholesky factor L and W = L^{-1}, one workgroup of sixteen
+// waves, in 16-wide steps over one LDS array.  M[c][r] holds A(r, c) and then L(r, c) for r >= c (columns
+// contiguous, as in memory), and M[r][c] holds W(r, c) for r > c in the half that L leaves free; the
+// row stride of 144 doubles puts the two k-rows that a half-wave reads on opposite bank halves.  Step k:
+//   (1) wave 0 factors the 16 x 16 tile k and inverts it (eliminate);
+//   (2) L_ik = A_ik W_kk^T for the tiles below, and W_k,j = W_kk Acc_k,j for the tiles left of it;
+//   (3) A_ij -= L_ik L_jk^T and Acc_ij -= L_ik W_kj, tile by tile on FP64 MFMA.  Wave 0 takes the next
+//       diagonal tile and goes straight on with its step (1) while the other waves do the rest.
+// It is bound by the serial step (1), about 1.5 us of 2 us a step.  Rows and columns from jb on are
+// those of the identity.  dinv: W by rows, dinv[r NB + c], zeros above the diagonal.
+__global__ __launch_bounds__(1024) void k_potrf_diag(double* Ag, int64_t lda, int jb, double* dinv, int* status,
                                                     int blk) {
-  static_assert(NB == 64, "k_potrf_diag assumes 64 x 64 blocks");
-  constexpr int QB = 16;
-  __shared__ double A[NB][NB + 1];
-  __shared__ double W[NB][NB + 1];
-  __shared__ double T[3][QB][QB + 1];
+  static_assert(NB == 128, "k_potrf_diag assumes 128 x 128 blocks");
+  constexpr int QB = 16, LD = NB + 16, NT = NB / QB;
+  __shared__ double M[NB * LD];
+  __shared__ double Wd[QB * QB];  // W_kk of the current step, Wd[q][c] = W_kk(c, q)
+  __shared__ double wdiag[NB];
   __shared__ int bad;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int fl = lane & 15, fk = lane >> 4;
   if (tid == 0) bad = 0;
   {
-    // all sixteen loads of a thread at clamped (always valid) addresses, issued together and
-    // waited for once; values outside the lower jb x jb triangle are replaced afterwards (a load
-    // behind a branch would cost one global-memory round trip each)
-    double v[NB * NB / 256];
+    // all 16 loads of a thread at clamped (always valid) addresses, issued together and masked
+    // afterwards: a load behind a branch would cost one round trip to memory each
+    double v[NB * NB / 1024];
+    const int r = tid & (NB - 1), c0 = tid >> 7;
 #pragma unroll
-    for (int u = 0; u < NB * NB / 256; ++u) {
-      const int e = tid + 256 * u;
-      const int r = min(e & (NB - 1), jb - 1), c = min(e >> 6, jb - 1);
-      v[u] = Ag[(int64_t)c * lda + r];
+    for (int u = 0; u < NB * NB / 1024; ++u) {
+      const int c = min(c0 + 8 * u, jb - 1);  // rows above the diagonal read the diagonal's line again
+      v[u] = Ag[(int64_t)c * lda + min(max(r, c), jb - 1)];
     }
 #pragma unroll
-    for (int u = 0; u < NB * NB / 256; ++u) {
-      const int e = tid + 256 * u;
-      const int r = e & (NB - 1), c = e >> 6;
-      A[r][c] = (r < jb && c < jb && c <= r) ? v[u] : ((r == c) ? 1.0 : 0.0);
-      W[r][c] = 0.0;
+    for (int u = 0; u < NB * NB / 1024; ++u) {
+      const int c = c0 + 8 * u;
+      if (r >= c) M[c * LD + r] = (r < jb && c < jb) ? v[u] : ((r == c) ? 1.0 : 0.0);
     }
+  }
+  const int nk = (jb + QB - 1) / QB;
+  // rows of the identity past the tiles of jb, which no step reaches
+  for (int e = QB * nk * NB + tid; e < NB * NB; e += 1024) {
+    const int r = e >> 7, c = e & (NB - 1);
+    dinv[e] = r == c ? 1.0 : 0.0;
   }
   __syncthreads();
-  for (int kb = 0; kb < NB / QB; ++kb) {
-    const int k0 = kb * QB;
-    if (wave == 0) {
-      // (1) 16 x 16 Cholesky and its inverse; lanes >= 16 carry zeros and are never read back
-      const int r = lane & (QB - 1);
-      double a[QB];
+  // step (1) of tile k, by wave 0
+  auto factor_tile = [&](int k) {
+    const int o = QB * k;
+    double a[QB], x[QB];
 #pragma unroll
-      for (int c = 0; c < QB; ++c) a[c] = (lane < QB && c <= r) ? A[k0 + r][k0 + c] : 0.0;
-      double rd[QB];
-      bool badw = false;
+    for (int i = 0; i < QB; ++i) {
+      a[i] = M[(i >= fl) ? (o + fl) * LD + o + i : (o + i) * LD + o + fl];
+      x[i] = i == fl ? 1.0 : 0.0;
+    }
+    auto own = [&] {  // entry c of lane c
+      double d = 0.0;
+#pragma unroll
+      for (int j = 0; j < QB; ++j) d = j == fl ? a[j] : d;
+      return d;
+    };
+    // a diagonal far from one is brought there by powers of two (exactly): A = P A' P, L = P L'
+    double d = M[(o + fl) * LD + o + fl];
+    const bool far = __any(!(d > 1e-200 && d < 1e200));
+    int e = 0;
+    if (far) {
+      (void)frexp(d, &e);
+      e >>= 1;
+#pragma unroll
+      for (int i = 0; i < QB; ++i) a[i] = ldexp(a[i], -e - __shfl(e, (lane & 48) + i, 64));
+    }
+    eliminate(a, x, pivot_recip(row_lane<0>(a[0])));
+    d = own();
+    if (__any(!(d > 0.0)) && lane == 0) bad = 1;
+    const double rs = pivot_rsqrt(d);
+    scale_rows(a, x, rs);
+    double dl = d * rs, dw = rs;
+    if (far) {
+      dl = ldexp(dl, e);
+      dw = ldexp(dw, -e);
 #pragma unroll
       for (int j = 0; j < QB; ++j) {
-        double d = lane_value(a[j], j);
-        if (!(d > 0.0)) {
-          badw = true;
-          d = 1.0;
+        a[j] = ldexp(a[j], e);
+        x[j] = ldexp(x[j], -e);
+      }
+    }
+    if (fk == 0) {
+#pragma unroll
+      for (int j = 0; j < QB; ++j) {
+        // L(c, j) for c >= j, W(j, c) for j > c
+        M[(o + j) * LD + o + fl] = (j < fl) ? a[j] : (j == fl ? dl : x[j]);
+        Wd[fl * QB + j] = j > fl ? x[j] : (j == fl ? dw : 0.0);
+      }
+      wdiag[o + fl] = dw;
+    }
+  };
+  // tile product D[row][col] = sum_q P[q][row] Q[q][col], both operands 16-row slabs of LDS
+  auto tile_mma = [&](const double* P, int ldp, const double* Q, int ldq, v4d acc) {
+#pragma unroll
+    for (int q = 0; q < QB; q += 4)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(P[(q + fk) * ldp + fl], Q[(q + fk) * ldq + fl], acc, 0, 0, 0);
+    return acc;
+  };
+  // C[row][col] -= (that product)
+  auto tile_sub = [&](double* C, const double* P, const double* Q) {
+    const v4d acc = tile_mma(P, LD, Q, LD, v4d{0.0, 0.0, 0.0, 0.0});
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      double* c = C + (fk + 4 * r) * LD + fl;
+      *c -= acc[r];
+    }
+  };
+  // the finished columns of L and rows of W of step k, by nt threads
+  auto store_tile = [&](int k, int t, int nt) {
+    const int o = QB * k;
+    for (int e = t; e < QB * NB; e += nt) {
+      const int i = o + (e >> 7), j = e & (NB - 1);
+      const double v = M[i * LD + j];
+      if (j >= i && j < jb && i < jb) Ag[(int64_t)i * lda + j] = v;                // L(j, i)
+      dinv[i * NB + j] = j < i ? v : (j == i ? wdiag[i] : 0.0);                    // W(i, j)
+    }
+  };
+  for (int k = 0; k < nk; ++k) {
+    const int o = QB * k, p = o - QB;
+    // (3) of step k - 1, and (1)
+    if (wave == 0) {
+      if (k > 0) tile_sub(M + o * LD + o, M + p * LD + o, M + p * LD + o);
+      factor_tile(k);
+    } else if (k > 0) {
+      store_tile(k - 1, tid - 64, 1024 - 64);
+      const int nr = nk - k;                  // tile rows below step k - 1
+      const int ntri = nr * (nr + 1) / 2;     // trailing tiles; the first is wave 0's
+      const int total = ntri + nr * k;
+      for (int u = wave; u < total; u += 15) {
+        if (u < ntri) {
+          int i = 0, b = u;
+          while (b > i) b -= ++i;             // u -> (i, b), b <= i
+          const int oi = o + QB * i, oj = o + QB * b;
+          // as D[j][i], so that the tile's i runs along M's rows
+          tile_sub(M + oj * LD + oi, M + p * LD + oj, M + p * LD + oi);
+        } else {
+          const int v = u - ntri;
+          const int oi = o + QB * (v / k), kk = v % k;
+          double* C = M + oi * LD + QB * kk;
+          if (kk < k - 1) {
+            tile_sub(C, M + p * LD + oi, M + p * LD + QB * kk);
+          } else {
+            // the first product into this tile, with W_pp itself: its strict lower part and diagonal
+            v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int q = 0; q < QB; q += 4) {
+              const int qq = q + fk;
+              const double m = M[(p + qq) * LD + p + fl], g = wdiag[p + fl];
+              acc = __builtin_amdgcn_mfma_f64_16x16x4f64(M[(p + qq) * LD + oi + fl],
+                                                         qq > fl ? m : (qq == fl ? g : 0.0), acc, 0, 0, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) C[(fk + 4 * r) * LD + fl] = -acc[r];
+          }
         }
-        const double piv = sqrt(d);
-        rd[j] = 1.0 / piv;
-        if (r == j) a[j] = piv;
-        if (r > j) a[j] *= rd[j];
-#pragma unroll
-        for (int c = j + 1; c < QB; ++c) {
-          const double lcj = lane_value(a[j], c);  // row c's entry in column j
-          if (r >= c) a[c] -= a[j] * lcj;
-        }
       }
-      if (lane < QB) {
-#pragma unroll
-        for (int c = 0; c < QB; ++c)
-          if (c <= r) A[k0 + r][k0 + c] = a[c];
-      }
-      // inverse, lane t = column t: x[k] *= 1/l_kk; x[i] -= l_ik x[k] for i > k
-      double x[QB];
-#pragma unroll
-      for (int i = 0; i < QB; ++i) x[i] = (i == r) ? 1.0 : 0.0;
-#pragma unroll
-      for (int k = 0; k < QB; ++k) {
-        x[k] *= rd[k];
-#pragma unroll
-        for (int i = k + 1; i < QB; ++i) x[i] -= lane_value(a[k], i) * x[k];  // l_ik from row i's lane
-      }
-      if (lane < QB) {
-#pragma unroll
-        for (int i = 0; i < QB; ++i) W[k0 + i][k0 + r] = (i >= r) ? x[i] : 0.0;
-      }
-      if (badw && lane == 0) bad = 1;
     }
     __syncthreads();
-    const int r0 = k0 + QB, rem = NB - r0;
-    if (rem > 0) {
-      // (2) panel: L[r][k0 + c] = sum_{q <= c} A[r][k0 + q] W[k0 + c][k0 + q]
-      double pv[3];
+    // (2) tiles below (as W_kk A_ik^T: M holds A transposed) and to the left, the same product of M
+    for (int u = wave; u < nk - 1; u += 16) {
+      double* C = M + o * LD + QB * (u >= k ? u + 1 : u);
+      const v4d acc = tile_mma(Wd, QB, C, LD, v4d{0.0, 0.0, 0.0, 0.0});
 #pragma unroll
-      for (int u = 0; u < 3; ++u) {
-        const int e = tid + 256 * u;
-        pv[u] = 0.0;
-        if (e < rem * QB) {
-          const int rr = r0 + e / QB, c = e % QB;
-          double acc = 0.0;
-          // fixed trip count (W is zero above its diagonal), so the LDS reads are issued together
-#pragma unroll
-          for (int q = 0; q < QB; ++q) acc += A[rr][k0 + q] * W[k0 + c][k0 + q];
-          pv[u] = acc;
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int u = 0; u < 3; ++u) {
-        const int e = tid + 256 * u;
-        if (e < rem * QB) A[r0 + e / QB][k0 + e % QB] = pv[u];
-      }
-      __syncthreads();
-      // (3) trailing lower triangle: A[i][c] -= sum_q L[i][k0 + q] L[c][k0 + q], r0 <= c <= i
-      const int ntri = rem * (rem + 1) / 2;
-      for (int e = tid; e < ntri; e += 256) {
-        // e -> (i, c) with i - r0 = ii, c - r0 = cc <= ii, row-wise
-        int ii = (int)((sqrt(8.0 * e + 1.0) - 1.0) * 0.5);
-        while ((ii + 1) * (ii + 2) / 2 <= e) ++ii;
-        while (ii * (ii + 1) / 2 > e) --ii;
-        const int cc = e - ii * (ii + 1) / 2;
-        const int i = r0 + ii, c = r0 + cc;
-        double acc = 0.0;
-#pragma unroll
-        for (int q = 0; q < QB; ++q) acc += A[i][k0 + q] * A[c][k0 + q];
-        A[i][c] -= acc;
-      }
-      __syncthreads();
-    }
-  }
-  // off-diagonal blocks of the inverse, block row by block row
-  for (int ib = 1; ib < NB / QB; ++ib) {
-    // T_k = sum_{j=k}^{ib-1} L_{ib,j} W_{j,k} for k < ib
-    for (int e = tid; e < ib * QB * QB; e += 256) {
-      const int k = e / (QB * QB), rr = (e / QB) % QB, cc = e % QB;
-      double acc = 0.0;
-      // the trip count is a multiple of 16: unrolled by 4, the LDS reads of four terms are in flight
-#pragma unroll 4
-      for (int q = k * QB; q < ib * QB; ++q) acc += A[ib * QB + rr][q] * W[q][k * QB + cc];
-      T[k][rr][cc] = acc;
-    }
-    __syncthreads();
-    // W_{ib,k} = -W_{ib,ib} T_k
-    for (int e = tid; e < ib * QB * QB; e += 256) {
-      const int k = e / (QB * QB), rr = (e / QB) % QB, cc = e % QB;
-      double acc = 0.0;
-#pragma unroll
-      for (int q = 0; q < QB; ++q) acc += W[ib * QB + rr][ib * QB + q] * T[k][q][cc];
-      W[ib * QB + rr][k * QB + cc] = -acc;
+      for (int r = 0; r < 4; ++r) C[(fk + 4 * r) * LD + fl] = acc[r];
     }
     __syncthreads();
   }
-  // the factor (lower part of the jb x jb block) and dinv (column-major, upper part zero)
-  for (int e = tid; e < NB * NB; e += 256) {
-    const int r = e & (NB - 1), c = e >> 6;
-    if (r < jb && c < jb && c <= r) Ag[(int64_t)c * lda + r] = A[r][c];
-    dinv[(int64_t)c * NB + r] = (r >= c) ? W[r][c] : 0.0;
-  }
+  if (nk > 0) store_tile(nk - 1, tid, 1024);
   if (tid == 0 && bad) atomicCAS(status, 0, blk + 1);
 }
 
@@ -1789,21 +1846,129 @@ Envelope Envelope::dense(int64_t n) {
   return e;
 }
 
-// Two levels: NB-wide steps (diagonal block, panel) inside panels of PANEL = 4 NB columns.  A step
+// L21 = A21 W^T in place for the NB-wide column block `col` (jb columns) on two ranges of rows (below the
+// diagonal block, and the boundary rows), W = L11^{-1} by rows (dinv).  One workgroup per 32 rows reads
+// all of its columns before it writes any.  Wave w takes the column tiles w and 7 - w, nine 16 x 16
+// blocks of the triangle in all, whose W operands are loaded before the rows are waited for: one load
+// latency and 72 MFMAs a wave, 5 us where the four k-stages of the general product took 11.
+__global__ __launch_bounds__(256) void k_panel(double* col, int64_t lda, int64_t r0, int64_t len0, int64_t r1,
+                                               int64_t len1, int jb, const double* dinv) {
+  static_assert(NB == 128, "k_panel assumes 128-wide blocks");
+  constexpr int LD = 40;  // the two k-rows of a half-wave (two apart) on opposite bank halves
+  __shared__ double As[NB * LD];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int fl = lane & 15, fk = lane >> 4;
+  const int64_t t0 = (len0 + 31) / 32;
+  const bool second = (int64_t)blockIdx.x >= t0;
+  const int64_t off = 32 * (second ? (int64_t)blockIdx.x - t0 : (int64_t)blockIdx.x);
+  double* C = col + (second ? r1 : r0) + off;
+  const int nr = (int)min<int64_t>(32, (second ? len1 : len0) - off);
+  double2 wv[18];
+  const int n1 = 2 * (w + 1);  // 8-k groups of tile w, then 18 - n1 of tile 7 - w
+#pragma unroll
+  for (int g = 0; g < 18; ++g) {
+    const int j = g < n1 ? w : 7 - w, q0 = 8 * (g < n1 ? g : g - n1);
+    wv[g] = *(const double2*)(dinv + (16 * j + fl) * NB + q0 + 2 * fk);
+  }
+  {
+    double v[16];
+    const int r = min(tid & 31, nr - 1);
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = C[(int64_t)min((tid >> 5) + 8 * u, jb - 1) * lda + r];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int q = (tid >> 5) + 8 * u;
+      As[q * LD + (tid & 31)] = q < jb ? v[u] : 0.0;
+    }
+  }
+  __syncthreads();
+  v4d acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) acc[i][rt] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int g = 0; g < 18; ++g) {
+    const int q = 8 * (g < n1 ? g : g - n1) + 2 * fk;
+    double x[2], y[2];
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+      x[rt] = As[q * LD + 16 * rt + fl];
+      y[rt] = As[(q + 1) * LD + 16 * rt + fl];
+    }
+    const int i = g < n1 ? 0 : 1;
+    if (i == 0) {
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) {
+        acc[0][rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(wv[g].x, x[rt], acc[0][rt], 0, 0, 0);
+        acc[0][rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(wv[g].y, y[rt], acc[0][rt], 0, 0, 0);
+      }
+    } else {
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) {
+        acc[1][rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(wv[g].x, x[rt], acc[1][rt], 0, 0, 0);
+        acc[1][rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(wv[g].y, y[rt], acc[1][rt], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int c = 16 * (i == 0 ? w : 7 - w) + fk + 4 * r, row = 16 * rt + fl;
+        if (c < jb && row < nr) C[(int64_t)c * lda + row] = acc[i][rt][r];
+      }
+}
+
+// C -= X Y^T for two ranges of rows of the factor in one launch: rows X0 (len0) only where they reach the
+// lower triangle (their first row is the first row of Y), rows X1 (len1) in full; Y: N x K.  64 x 64
+// tiles with 64-k stages: a rank-NB update is two stages, so two load latencies.
+__global__ __launch_bounds__(256) void k_rank_update(int64_t len0, const double* X0, double* C0, int64_t len1,
+                                                     const double* X1, double* C1, int64_t N, int64_t K,
+                                                     const double* Y, int64_t lda) {
+  const int t0 = (int)((len0 + 63) / 64);
+  const bool second = (int)blockIdx.x >= t0;
+  dgemm_tile<64, 64, 2, 2, false, true, 64>(second ? len1 : len0, N, K, -1.0, second ? X1 : X0, lda, Y, lda, 1.0,
+                                            second ? C1 : C0, lda, second ? 0 : 1, K, nullptr,
+                                            second ? (int)blockIdx.x - t0 : (int)blockIdx.x, blockIdx.y, 0);
+}
+
+static void rank_update(hipStream_t s, double* A, int64_t lda, int64_t j0, int64_t K, int64_t r0, int64_t rend,
+                        int64_t r1, int64_t len1, int64_t cend) {
+  const int64_t N = cend - r0;
+  if (N <= 0 || K <= 0) return;
+  const int64_t tiles = cdiv(rend - r0, 64) + cdiv(len1, 64);
+  if (tiles == 0) return;
+  RPF_CHECK(cdiv(N, 64) <= 65535, RPF_EINVAL, "potrf: grid too large");
+  hipLaunchKernelGGL(k_rank_update, dim3((unsigned)tiles, (unsigned)cdiv(N, 64)), dim3(256), 0, s, rend - r0,
+                     A + j0 * lda + r0, A + r0 * lda + r0, len1, A + j0 * lda + r1, A + r0 * lda + r1, N, K,
+                     A + j0 * lda + r0, lda);
+  RPF_LAUNCH_CHECK();
+}
+
+// Two levels: NB-wide steps (diagonal block, panel) inside panels of PANEL = 2 NB columns.  A step
 // updates only the columns of its own panel (rank NB); everything to the right of a panel gets
 // one rank-PANEL update once the panel is done, so the trailing matrix and the boundary rows are
-// read and written once per panel instead of once per step, by GEMMs with K = PANEL (compute-bound
-// instead of memory-bound).  The result is the same factor (the updates of one column commute).
+// read and written once per panel instead of once per step.  A step is bound by the latency of its three
+// dependent launches, so the rows below and the boundary rows share each of them.  The result is the
+// same factor (the updates of one column commute).
 bool gemm_nt_flex(hipStream_t s, int64_t M, int64_t N, int64_t K, double alpha, const double* X, int64_t ldx,
                   const double* Y, int64_t ldy, double beta, double* C, int64_t ldc, bool lower, DevBuf<double>& wa,
                   DevBuf<double>& wb);
 
 void potrf(hipStream_t s, double* A, int64_t lda, int64_t n, int64_t n_fac, const Envelope& env, double* dinv,
            int* status) {
-  constexpr int64_t PANEL = 4 * NB;
+  constexpr int64_t PANEL = 2 * NB;
+  // rows from which a trailing update goes to the large-problem kernel (which needs copies of its
+  // operands): below, its 128 x 128 tiles leave CUs idle
+  constexpr int64_t LARGE = 4096;
   const int64_t nblk = cdiv(n_fac, NB);
   RPF_CHECK((int64_t)env.rend.size() >= nblk, RPF_EINVAL, "potrf: envelope too short");
   DevBuf<double> wa, wb;  // operand copies of the large rank-PANEL updates
+  const int64_t nbnd = n - n_fac;
   for (int64_t P0 = 0; P0 < n_fac; P0 += PANEL) {
     const int64_t P1 = std::min<int64_t>(P0 + PANEL, n_fac);
     int64_t pend = P1;  // rows (and columns) reached by the panel's envelope
@@ -1811,24 +1976,19 @@ void potrf(hipStream_t s, double* A, int64_t lda, int64_t n, int64_t n_fac, cons
       const int64_t t = j0 / NB;
       const int jb = (int)std::min<int64_t>(NB, n_fac - j0);
       double* dt = dinv + t * NB * NB;
-      hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(256), 0, s, A + j0 * lda + j0, lda, jb, dt, status, (int)t);
+      hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(1024), 0, s, A + j0 * lda + j0, lda, jb, dt, status, (int)t);
       RPF_LAUNCH_CHECK();
       const int64_t r0 = j0 + jb;
       const int64_t rend = std::max<int64_t>(r0, std::min<int64_t>(env.rend[t], n_fac));
       pend = std::max(pend, rend);
-      double* col = A + j0 * lda;
-      // panel: L21 = A21 L11^{-T}, in place (one N tile covers the jb columns)
-      if (rend > r0) dgemm(s, false, true, rend - r0, jb, jb, 1.0, col + r0, lda, dt, NB, 0.0, col + r0, lda);
-      if (n > n_fac) dgemm(s, false, true, n - n_fac, jb, jb, 1.0, col + n_fac, lda, dt, NB, 0.0, col + n_fac, lda);
-      // update of the remaining columns of this panel (rows within the envelope, boundary rows)
-      const int64_t cend = std::min(rend, P1);
-      if (cend > r0) {
-        dgemm(s, false, true, rend - r0, cend - r0, jb, -1.0, col + r0, lda, col + r0, lda, 1.0,
-              A + r0 * lda + r0, lda, true);
-        if (n > n_fac)
-          dgemm(s, false, true, n - n_fac, cend - r0, jb, -1.0, col + n_fac, lda, col + r0, lda, 1.0,
-                A + r0 * lda + n_fac, lda);
+      const int64_t tiles = cdiv(rend - r0, 32) + cdiv(nbnd, 32);
+      if (tiles > 0) {
+        hipLaunchKernelGGL(k_panel, dim3((unsigned)tiles), dim3(256), 0, s, A + j0 * lda, lda, r0, rend - r0, n_fac,
+                           nbnd, jb, dt);
+        RPF_LAUNCH_CHECK();
       }
+      // the remaining columns of this panel (rows within the envelope, boundary rows)
+      rank_update(s, A, lda, j0, jb, r0, rend, n_fac, nbnd, std::min(rend, P1));
     }
     // rank-PANEL update of everything right of the panel (the boundary-boundary block is deferred);
     // rows of a step's columns past its own envelope end are zero, so one product over the
@@ -1836,15 +1996,14 @@ void potrf(hipStream_t s, double* A, int64_t lda, int64_t n, int64_t n_fac, cons
     if (pend > P1) {
       const int64_t K = P1 - P0;
       double* pc = A + P0 * lda;
-      if (!gemm_nt_flex(s, pend - P1, pend - P1, K, -1.0, pc + P1, lda, pc + P1, lda, 1.0, A + P1 * lda + P1, lda, true,
-                        wa, wb))
-        dgemm(s, false, true, pend - P1, pend - P1, K, -1.0, pc + P1, lda, pc + P1, lda, 1.0, A + P1 * lda + P1, lda,
-              true);
-      if (n > n_fac &&
-          !gemm_nt_flex(s, n - n_fac, pend - P1, K, -1.0, pc + n_fac, lda, pc + P1, lda, 1.0, A + P1 * lda + n_fac, lda,
-                        false, wa, wb))
-        dgemm(s, false, true, n - n_fac, pend - P1, K, -1.0, pc + n_fac, lda, pc + P1, lda, 1.0, A + P1 * lda + n_fac,
-              lda);
+      const bool big0 = pend - P1 >= LARGE, big1 = nbnd >= LARGE;
+      const bool done0 = big0 && gemm_nt_flex(s, pend - P1, pend - P1, K, -1.0, pc + P1, lda, pc + P1, lda, 1.0,
+                                              A + P1 * lda + P1, lda, true, wa, wb);
+      const bool done1 = big1 && gemm_nt_flex(s, nbnd, pend - P1, K, -1.0, pc + n_fac, lda, pc + P1, lda, 1.0,
+                                              A + P1 * lda + n_fac, lda, false, wa, wb);
+      if (!done0) rank_update(s, A, lda, P0, K, P1, pend, n_fac, done1 ? 0 : nbnd, pend);
+      else if (!done1 && nbnd > 0)
+        dgemm(s, false, true, nbnd, pend - P1, K, -1.0, pc + n_fac, lda, pc + P1, lda, 1.0, A + P1 * lda + n_fac, lda);
     }
   }
   RPF_HIP(hipStreamSynchronize(s));  // the operand copies are freed on return
@@ -1925,20 +2084,20 @@ template <bool FWD, int H, bool UP = false>
 __global__ __launch_bounds__(256) void k_trsm_panel(const double* L, int64_t ldl, int64_t n, const double* dinv,
                                                     const int64_t* lo, const int64_t* hi, double* B, int64_t ldb,
                                                     int64_t nrhs) {
-  constexpr int PW = 16 * H;
-  __shared__ double S[NB][PW + 1];
-  __shared__ double red[4][NB][PW + 1];
+  constexpr int PW = 16 * H, SB = 64;  // rows of a step: half of a diagonal block
+  __shared__ double S[SB][PW + 1];
+  __shared__ double red[4][SB][PW + 1];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
   const int64_t col0 = (int64_t)blockIdx.x * PW + li;  // this lane's column in part 0 (part h: + 16 h)
   bool cok[H];
 #pragma unroll
   for (int h = 0; h < H; ++h) cok[h] = col0 + 16 * h < nrhs;
-  const int64_t nblk = (n + NB - 1) / NB;
+  const int64_t nblk = (n + SB - 1) / SB;
   for (int64_t step = 0; step < nblk; ++step) {
     const int64_t t = FWD ? step : nblk - 1 - step;
-    const int64_t j0 = t * NB;
-    const int jb = (int)min<int64_t>(NB, n - j0);
+    const int64_t j0 = t * SB;
+    const int jb = (int)min<int64_t>(SB, n - j0);
     v4d acc[4][H];
 #pragma unroll
     for (int q = 0; q < 4; ++q)
@@ -1946,11 +2105,11 @@ __global__ __launch_bounds__(256) void k_trsm_panel(const double* L, int64_t ldl
       for (int h = 0; h < H; ++h) acc[q][h] = v4d{0.0, 0.0, 0.0, 0.0};
     int64_t kb, ke;
     if (FWD) {
-      kb = max<int64_t>(0, lo[t]);
+      kb = max<int64_t>(0, lo[t / 2]);
       ke = j0;
     } else {
       kb = j0 + jb;
-      ke = min<int64_t>(hi[t], n);
+      ke = min<int64_t>(hi[t / 2], n);
     }
     // group g covers k in [kb + 16 g, kb + 16 g + 16); wave w takes g = w, w + 4, ...
     auto load = [&](int64_t k0, double* a, double* b) {
@@ -1995,23 +2154,23 @@ __global__ __launch_bounds__(256) void k_trsm_panel(const double* L, int64_t ldl
 #pragma unroll
         for (int r = 0; r < 4; ++r) red[w][16 * q + lk + 4 * r][16 * h + li] = acc[q][h][r];
     __syncthreads();
-    for (int e = tid; e < NB * PW; e += 256) {
+    for (int e = tid; e < SB * PW; e += 256) {
       const int ri = e / PW, cj = e % PW;
       const int64_t gc = (int64_t)blockIdx.x * PW + cj;
       const double bv = (ri < jb && gc < nrhs) ? B[j0 + ri + gc * ldb] : 0.0;
       S[ri][cj] = bv - (red[0][ri][cj] + red[1][ri][cj] + red[2][ri][cj] + red[3][ri][cj]);
     }
     __syncthreads();
-    // X_t = inv(L_tt) S (forward) or inv(L_tt)^T S (backward): dinv column-major NB x NB; wave w
+    // X_t = inv(L_tt) S (forward) or inv(L_tt)^T S (backward): the inverse stands by rows; wave w
     // forms rows 16 w .. 16 w + 15 of every column part
     v4d x[H];
 #pragma unroll
     for (int h = 0; h < H; ++h) x[h] = v4d{0.0, 0.0, 0.0, 0.0};
-    const double* D = dinv + t * NB * NB;
+    const double* D = dinv + (t / 2) * NB * NB + (t & 1) * (SB * NB + SB);
 #pragma unroll 4
-    for (int kk = 0; kk < NB; kk += 4) {
+    for (int kk = 0; kk < SB; kk += 4) {
       const int k = kk + lk, i = 16 * w + li;
-      const double av = FWD ? D[i + k * NB] : D[k + i * NB];
+      const double av = FWD ? D[k + i * NB] : D[i + k * NB];
 #pragma unroll
       for (int h = 0; h < H; ++h) x[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, S[k][16 * h + li], x[h], 0, 0, 0);
     }
@@ -2061,137 +2220,163 @@ void trsm(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double* 
     RPF_HIP(hipStreamSynchronize(s));  // the bounds buffer is freed on return
     return;
   }
-  if (dense && nrhs >= 4096) {
-    // Full factor, many right-hand sides (the identity of the condensation): left-looking by row
-    // blocks.  Block t first takes the contributions of all solved blocks, B_t -= L_t,prev X_prev
-    // (one product with a long inner dimension, split over K when its output tiles alone cannot
-    // fill the chip), then X_t = inv(L_tt) B_t; B is read once per block instead of rewritten for
-    // every trailing update.
-    // the split-K workspace is sized once for the largest block: growing it inside the loop would
-    // free and reallocate it (a device-wide synchronisation) at every larger block
-    DevBuf<double> ws;
-    {
-      size_t most = 0;
-      for (int64_t t = 0; t < nblk; ++t) {
-        const int64_t j0 = t * NB;
-        const int jb = (int)std::min<int64_t>(NB, n - j0);
-        const int64_t kdim = trans ? n - j0 - jb : j0;
-        const int sp = kdim > 0 ? gemm_splitk_count(jb, nrhs, kdim) : 1;
-        if (sp > 1) most = std::max(most, (size_t)sp * jb * nrhs);
-      }
-      ws.ensure(most);
-    }
-    auto update = [&](bool ta, int jb, int64_t kdim, const double* A, const double* Bsrc, double* C) {
-      if (kdim <= 0) return;
-      const int sp = gemm_splitk_count(jb, nrhs, kdim);
-      if (sp > 1) {
-        ws.ensure((size_t)sp * jb * nrhs);
-        dgemm_splitk(s, ta, false, jb, nrhs, kdim, -1.0, A, ldl, Bsrc, ldb, 1.0, C, ldb, ws.p, sp);
-      } else {
-        dgemm(s, ta, false, jb, nrhs, kdim, -1.0, A, ldl, Bsrc, ldb, 1.0, C, ldb);
-      }
-    };
-    if (!trans) {
-      for (int64_t t = 0; t < nblk; ++t) {
-        const int64_t j0 = t * NB;
-        const int jb = (int)std::min<int64_t>(NB, n - j0);
-        update(false, jb, j0, L + j0, B, B + j0);
-        // in place: the single row tile of this product reads all of B_t before writing it
-        dgemm(s, false, false, jb, nrhs, jb, 1.0, dinv + t * NB * NB, NB, B + j0, ldb, 0.0, B + j0, ldb);
-      }
-    } else {
-      for (int64_t t = nblk - 1; t >= 0; --t) {
-        const int64_t j0 = t * NB;
-        const int jb = (int)std::min<int64_t>(NB, n - j0);
-        const int64_t r0 = j0 + jb;
-        update(true, jb, n - r0, L + j0 * ldl + r0, B + r0, B + j0);
-        dgemm(s, true, false, jb, nrhs, jb, 1.0, dinv + t * NB * NB, NB, B + j0, ldb, 0.0, B + j0, ldb);
-      }
-    }
-    return;
+  // Right-looking: X_t = inv(L_tt) B_t (or its transpose) through a block buffer, then the update of the
+  // rows of its envelope below (above).
+  DevBuf<double> xt((size_t)NB * nrhs);
+  for (int64_t u = 0; u < nblk; ++u) {
+    const int64_t t = trans ? nblk - 1 - u : u;
+    const int64_t j0 = t * NB;
+    const int jb = (int)std::min<int64_t>(NB, n - j0);
+    // dinv holds the inverse by rows, i.e. its transpose by columns
+    dgemm(s, !trans, false, jb, nrhs, jb, 1.0, dinv + t * NB * NB, NB, B + j0, ldb, 0.0, xt.p, NB);
+    copy_matrix(s, xt.p, NB, B + j0, ldb, jb, nrhs);
+    const int64_t r0 = trans ? std::max<int64_t>(0, env.cstart[t]) : j0 + jb;
+    const int64_t r1 = trans ? j0 : std::min<int64_t>(env.rend[t], n);
+    if (r1 > r0)
+      dgemm(s, trans, false, r1 - r0, nrhs, jb, -1.0, trans ? L + r0 * ldl + j0 : L + j0 * ldl + r0, ldl, xt.p, NB, 1.0,
+            B + r0, ldb);
   }
-  // Banded factors: right-looking, each solved block updates the rows of its envelope below.
-  if (!trans) {
-    for (int64_t t = 0; t < nblk; ++t) {
-      const int64_t j0 = t * NB;
-      const int jb = (int)std::min<int64_t>(NB, n - j0);
-      const double* dt = dinv + t * NB * NB;
-      dgemm(s, false, false, jb, nrhs, jb, 1.0, dt, NB, B + j0, ldb, 0.0, B + j0, ldb);
-      const int64_t r0 = j0 + jb;
-      const int64_t rend = std::min<int64_t>(env.rend[t], n);
-      if (rend > r0)
-        dgemm(s, false, false, rend - r0, nrhs, jb, -1.0, L + j0 * ldl + r0, ldl, B + j0, ldb, 1.0, B + r0, ldb);
+  RPF_HIP(hipStreamSynchronize(s));  // the block buffer is freed on return
+}
+
+// ============================================================================ block inverses
+// X = the inverses of the diagonal blocks of bw rows (a multiple of NB) of a lower factor L, each bw x bw
+// column-major in a slab of its own, from the inverted NB x NB blocks: the pairs of inverted blocks of
+// h rows are joined level by level (h = NB, 2 NB, ..), X21 = -X22 (L21 X11), so the work is a few
+// launches of large products instead of a serial walk over the rows.  What the products skip
+// is known to be zero: L21 X11 starts at the column's own row, X22 T ends at the row's own column.
+__device__ inline int64_t block_rows(int64_t n, int64_t j, int64_t h) { return min(h, max<int64_t>(n - j, 0)); }
+
+// X11 of every NB block: the transpose of dinv (by rows), zeros above the diagonal; 64 x 64 through LDS
+__global__ __launch_bounds__(256) void k_place_dinv(int64_t n, int64_t bw, const double* dinv, double* X) {
+  __shared__ double t[64][65];
+  const int64_t d = blockIdx.y, j = d * NB;
+  const int r0 = (blockIdx.x & 1) * 64, c0 = (blockIdx.x >> 1) * 64;
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  for (int r = ty; r < 64; r += 4) t[r][tx] = dinv[d * NB * NB + (r0 + r) * NB + c0 + tx];
+  __syncthreads();
+  const int64_t lj = j % bw;
+  double* x = X + (j / bw) * bw * bw + lj * bw + lj;
+  for (int c = ty; c < 64; c += 4)
+    if (j + r0 + tx < n && j + c0 + c < n) x[(c0 + c) * bw + r0 + tx] = t[tx][c];
+}
+
+// One level.  Grid: (row tiles, column tiles, pairs); T: h x h per pair.
+template <int TILE, int BK, bool SECOND>
+__global__ __launch_bounds__(256) void k_join_blocks(int64_t n, int64_t bw, int64_t h, const double* L, int64_t ldl,
+                                                     double* X, double* T) {
+  const int64_t j = 2 * h * (int64_t)blockIdx.z;  // bw is a multiple of 2 h, or holds the whole factor
+  const int64_t M = block_rows(n, j + h, h);
+  const int64_t i0 = (int64_t)blockIdx.x * TILE, j0 = (int64_t)blockIdx.y * TILE;
+  if (i0 >= M) return;
+  const int64_t lj = j % bw;
+  double* X11 = X + (j / bw) * bw * bw + lj * bw + lj;
+  double* Tp = T + (int64_t)blockIdx.z * h * h;
+  if (!SECOND)
+    dgemm_tile<TILE, TILE, 2, 2, false, false, BK>(M, h, h - j0, 1.0, L + (j + j0) * ldl + j + h, ldl, X11 + j0, bw, 0.0,
+                                                   Tp, h, 0, h, nullptr, blockIdx.x, blockIdx.y, 0);
+  else
+    dgemm_tile<TILE, TILE, 2, 2, false, false, BK>(M, h, min<int64_t>(i0 + TILE, M), -1.0, X11 + h * bw + h, bw, Tp, h,
+                                                   0.0, X11 + h, bw, 0, h, nullptr, blockIdx.x, blockIdx.y, 0);
+}
+
+static int64_t join_scratch(int64_t n, int64_t bw) {
+  int64_t most = 1;
+  for (int64_t h = NB; h < bw; h *= 2) most = std::max(most, cdiv(n, 2 * h) * h * h);
+  return most;
+}
+
+static void invert_blocks(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double* dinv, double* X,
+                          int64_t bw, double* T) {
+  hipLaunchKernelGGL(k_place_dinv, dim3(4, (unsigned)cdiv(n, NB)), dim3(256), 0, s, n, bw, dinv, X);
+  for (int64_t h = NB; h < bw; h *= 2) {
+    const int64_t pairs = cdiv(n, 2 * h);
+    if (n <= h) break;
+    // 64 x 64 tiles until they alone fill the chip several times over
+    if (pairs * (h / 64) * (h / 64) < 4096) {
+      const dim3 g((unsigned)(h / 64), (unsigned)(h / 64), (unsigned)pairs);
+      hipLaunchKernelGGL((k_join_blocks<64, 64, false>), g, dim3(256), 0, s, n, bw, h, L, ldl, X, T);
+      hipLaunchKernelGGL((k_join_blocks<64, 64, true>), g, dim3(256), 0, s, n, bw, h, L, ldl, X, T);
+    } else {
+      const dim3 g((unsigned)(h / 128), (unsigned)(h / 128), (unsigned)pairs);
+      hipLaunchKernelGGL((k_join_blocks<128, 16, false>), g, dim3(256), 0, s, n, bw, h, L, ldl, X, T);
+      hipLaunchKernelGGL((k_join_blocks<128, 16, true>), g, dim3(256), 0, s, n, bw, h, L, ldl, X, T);
     }
-  } else {
-    for (int64_t t = nblk - 1; t >= 0; --t) {
-      const int64_t j0 = t * NB;
-      const int jb = (int)std::min<int64_t>(NB, n - j0);
-      const double* dt = dinv + t * NB * NB;
-      dgemm(s, true, false, jb, nrhs, jb, 1.0, dt, NB, B + j0, ldb, 0.0, B + j0, ldb);
-      const int64_t cs = std::max<int64_t>(0, env.cstart[t]);
-      if (j0 > cs)
-        dgemm(s, true, false, j0 - cs, nrhs, jb, -1.0, L + cs * ldl + j0, ldl, B + j0, ldb, 1.0, B + cs, ldb);
-    }
+    RPF_LAUNCH_CHECK();
   }
 }
 
+// Lower tiles of Y = X^T X, X lower triangular (ld bw): tile row i0 takes the rows of X from i0 on.
+template <int TILE, int BK>
+__global__ __launch_bounds__(256) void k_xtx(int64_t n, const double* X, int64_t bw, double* Y, int64_t ldy) {
+  const int64_t i0 = (int64_t)blockIdx.x * TILE;
+  dgemm_tile<TILE, TILE, 2, 2, true, false, BK>(n, n, n - i0, 1.0, X + i0, bw, X + i0, bw, 0.0, Y, ldy, 1, n, nullptr,
+                                                blockIdx.x, blockIdx.y, 0);
+}
+
 // Y = (L L^T)^{-1} from a dense lower Cholesky factor L (n x n, ld ldl) and its inverted diagonal
-// blocks: the forward solve L X = I, then L^T Y = X, skipping what is known to be zero or not
-// needed.  X = L^{-1} is lower triangular, so block row t of the forward solve only involves the
-// columns left of its diagonal block and the diagonal block itself; Y is symmetric, so the backward
-// solve forms its lower triangle only (block row t: the columns up to its diagonal block, which need
-// only lower-triangle entries of the rows below), and the upper triangle is mirrored at the end.
-// Same arithmetic as the full solves with identity right-hand sides, about a quarter of the flops.
+// blocks: X = L^{-1} by joining blocks, then Y = X^T X, its lower triangle only (the upper one is left
+// to the caller, see mirror_lower and add_outer).  Two thirds n^3 flops in about 2 log2(n / NB) + 2
+// launches.
 void potri_lower(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double* dinv, double* Y,
                  int64_t ldy) {
   if (n <= 0) return;
-  const int64_t nblk = cdiv(n, NB);
-  fill_matrix(s, Y, n, n, ldy, 0.0);
-  add_diag(s, Y, ldy, n, 1.0);
-  // the split-K workspace is sized once for the largest block (see trsm)
-  DevBuf<double> ws;
-  {
-    size_t most = 0;
-    for (int64_t t = 0; t < nblk; ++t) {
-      const int64_t j0 = t * NB;
-      const int jb = (int)std::min<int64_t>(NB, n - j0);
-      const int64_t fw[2][2] = {{j0, j0}, {j0 + jb, n - j0 - jb}};  // (ncol, kdim) forward, backward
-      for (const auto& d : fw) {
-        if (d[0] <= 0 || d[1] <= 0) continue;
-        const int sp = gemm_splitk_count(jb, d[0], d[1]);
-        if (sp > 1) most = std::max(most, (size_t)sp * jb * d[0]);
-      }
-    }
-    ws.ensure(most);
+  const int64_t bw = cdiv(n, NB) * NB;
+  DevBuf<double> X((size_t)bw * bw), T(join_scratch(n, bw));
+  invert_blocks(s, L, ldl, n, dinv, X.p, bw, T.p);
+  if (n < 4096)
+    hipLaunchKernelGGL((k_xtx<64, 64>), dim3((unsigned)cdiv(n, 64), (unsigned)cdiv(n, 64)), dim3(256), 0, s, n, X.p, bw,
+                       Y, ldy);
+  else
+    hipLaunchKernelGGL((k_xtx<128, 16>), dim3((unsigned)cdiv(n, 128), (unsigned)cdiv(n, 128)), dim3(256), 0, s, n, X.p,
+                       bw, Y, ldy);
+  RPF_LAUNCH_CHECK();
+  RPF_HIP(hipStreamSynchronize(s));  // the workspaces are freed on return
+}
+
+// B (n x n, ldb) = A (lower triangle of n x n, lda) + alpha Z Z^T + sigma I, Z n x k (ld n, k <= KDET - 1):
+// its lower triangle, and with `full` the mirrored upper one too, in one pass over 64 x 64 tiles.
+__global__ __launch_bounds__(256) void k_add_outer(int64_t n, const double* A, int64_t lda, int k, const double* Z,
+                                                   double alpha, double sigma, double* B, int64_t ldb, int full) {
+  __shared__ double t[64][65];
+  __shared__ double zr[8][64], zc[8][64];
+  const int64_t r0 = (int64_t)blockIdx.x * 64, c0 = (int64_t)blockIdx.y * 64;
+  if (c0 > r0) return;
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  for (int q = ty; q < k; q += 4) {
+    zr[q][tx] = r0 + tx < n ? Z[q * n + r0 + tx] : 0.0;
+    zc[q][tx] = c0 + tx < n ? alpha * Z[q * n + c0 + tx] : 0.0;
   }
-  auto update = [&](bool ta, int jb, int64_t ncol, int64_t kdim, const double* A, const double* Bsrc, double* C) {
-    if (kdim <= 0 || ncol <= 0) return;
-    const int sp = gemm_splitk_count(jb, ncol, kdim);
-    if (sp > 1) {
-      ws.ensure((size_t)sp * jb * ncol);
-      dgemm_splitk(s, ta, false, jb, ncol, kdim, -1.0, A, ldl, Bsrc, ldy, 1.0, C, ldy, ws.p, sp);
-    } else {
-      dgemm(s, ta, false, jb, ncol, kdim, -1.0, A, ldl, Bsrc, ldy, 1.0, C, ldy);
-    }
-  };
-  // forward: X_t = inv(L_tt) (I_t - L_t,prev X_prev), nonzero in columns [0, j0 + jb)
-  for (int64_t t = 0; t < nblk; ++t) {
-    const int64_t j0 = t * NB;
-    const int jb = (int)std::min<int64_t>(NB, n - j0);
-    update(false, jb, j0, j0, L + j0, Y, Y + j0);
-    // in place: the single row tile of this product reads all of its rows before writing them
-    dgemm(s, false, false, jb, j0 + jb, jb, 1.0, dinv + t * NB * NB, NB, Y + j0, ldy, 0.0, Y + j0, ldy);
+  __syncthreads();
+  const int64_t r = r0 + tx;
+  double v[16];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) v[u] = A[min(c0 + ty + 4 * u, n - 1) * lda + min(r, n - 1)];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int lc = ty + 4 * u;
+    const int64_t c = c0 + lc;
+    double x = v[u];
+    for (int q = 0; q < k; ++q) x += zr[q][tx] * zc[q][lc];
+    if (r == c) x += sigma;
+    t[lc][tx] = x;
+    if (r < n && c < n && r >= c) B[c * ldb + r] = x;
   }
-  // backward, lower triangle: Y_t = inv(L_tt)^T (X_t - L_below,t^T Y_below) in columns [0, j0 + jb)
-  for (int64_t t = nblk - 1; t >= 0; --t) {
-    const int64_t j0 = t * NB;
-    const int jb = (int)std::min<int64_t>(NB, n - j0);
-    const int64_t r0 = j0 + jb;
-    update(true, jb, j0 + jb, n - r0, L + j0 * ldl + r0, Y + r0, Y + j0);
-    dgemm(s, true, false, jb, j0 + jb, jb, 1.0, dinv + t * NB * NB, NB, Y + j0, ldy, 0.0, Y + j0, ldy);
+  if (!full) return;
+  __syncthreads();
+  for (int lr = ty; lr < 64; lr += 4) {  // row r0 + lr of the lower tile is a column of the upper one
+    const int64_t cc = r0 + lr, rr = c0 + tx;
+    if (cc < n && rr < cc) B[cc * ldb + rr] = t[tx][lr];
   }
-  mirror_lower(s, Y, ldy, n);
-  RPF_HIP(hipStreamSynchronize(s));  // the split-K workspace is freed on return
+}
+
+void add_outer(hipStream_t s, int64_t n, const double* A, int64_t lda, int k, const double* Z, double alpha,
+               double sigma, double* B, int64_t ldb, bool full) {
+  if (n <= 0) return;
+  RPF_CHECK(k <= 8, RPF_EINVAL, "add_outer: more than 8 columns");
+  hipLaunchKernelGGL(k_add_outer, dim3((unsigned)cdiv(n, 64), (unsigned)cdiv(n, 64)), dim3(256), 0, s, n, A, lda, k, Z,
+                     alpha, sigma, B, ldb, full ? 1 : 0);
+  RPF_LAUNCH_CHECK();
 }
 
 // ============================================================================ elementwise helpers
@@ -2219,11 +2404,6 @@ __global__ void k_mirror_lower(double* A, int64_t lda, int64_t n) {
     const int64_t r = i % n, c = i / n;
     if (r < c) A[c * lda + r] = A[r * lda + c];
   }
-}
-
-__global__ void k_add_diag(double* A, int64_t lda, int64_t n, double v) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) A[i * lda + i] += v;
 }
 
 void fill(hipStream_t s, double* p, int64_t count, double v) {
@@ -2271,11 +2451,14 @@ __global__ __launch_bounds__(256) void k_mirror_env(double* A, int64_t lda, int6
 
 void mirror_envelope(hipStream_t s, double* A, int64_t lda, int64_t n, const Envelope& env) {
   if (n <= 0) return;
-  const int64_t nblk = cdiv(n, NB);
-  RPF_CHECK((int64_t)env.rend.size() >= nblk, RPF_EINVAL, "mirror_envelope: envelope too short");
-  std::vector<int64_t> re(env.rend.begin(), env.rend.begin() + nblk);
+  const int64_t nblk = cdiv(n, 64);  // the kernel's 64-column tiles, each with the rows of its NB block
+  RPF_CHECK((int64_t)env.rend.size() >= cdiv(n, NB), RPF_EINVAL, "mirror_envelope: envelope too short");
+  std::vector<int64_t> re(nblk);
   int64_t tiles = 1;
-  for (int64_t t = 0; t < nblk; ++t) tiles = std::max<int64_t>(tiles, cdiv(std::min(re[t], n) - t * NB, NB));
+  for (int64_t t = 0; t < nblk; ++t) {
+    re[t] = env.rend[t * 64 / NB];
+    tiles = std::max<int64_t>(tiles, cdiv(std::min(re[t], n) - t * 64, 64));
+  }
   DevBuf<int64_t> d;
   d.upload(re.data(), re.size(), s);
   hipLaunchKernelGGL(k_mirror_env, dim3((unsigned)tiles, (unsigned)nblk), dim3(256), 0, s, A, lda, n, d.p);
@@ -2286,12 +2469,6 @@ void mirror_envelope(hipStream_t s, double* A, int64_t lda, int64_t n, const Env
 void mirror_lower(hipStream_t s, double* A, int64_t lda, int64_t n) {
   if (n <= 0) return;
   hipLaunchKernelGGL(k_mirror_lower, dim3((unsigned)cdiv(n * n, 256)), dim3(256), 0, s, A, lda, n);
-  RPF_LAUNCH_CHECK();
-}
-
-void add_diag(hipStream_t s, double* A, int64_t lda, int64_t n, double v) {
-  if (n <= 0) return;
-  hipLaunchKernelGGL(k_add_diag, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, A, lda, n, v);
   RPF_LAUNCH_CHECK();
 }
 

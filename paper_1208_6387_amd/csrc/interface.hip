@@ -1055,10 +1055,8 @@ void ensure_coarse(rpf_problem pb, const rpf_pattern* pats, hipStream_t s) {
   RPF_HIP(hipMemsetAsync(st.p, 0, sizeof(int), s));
   potrf(s, GtG.p, nG, nG, nG, env, dinv.p, st.p);
   pb->Ginv.alloc((size_t)nG * nG);
-  fill(s, pb->Ginv.p, (int64_t)nG * nG, 0.0);
-  add_diag(s, pb->Ginv.p, nG, nG, 1.0);
-  trsm(s, GtG.p, nG, nG, dinv.p, env, pb->Ginv.p, nG, nG, false);
-  trsm(s, GtG.p, nG, nG, dinv.p, env, pb->Ginv.p, nG, nG, true);
+  potri_lower(s, GtG.p, nG, nG, dinv.p, pb->Ginv.p, nG);
+  mirror_lower(s, pb->Ginv.p, nG, nG);
   int hst = 0;
   RPF_HIP(hipMemcpyAsync(&hst, st.p, sizeof(int), hipMemcpyDeviceToHost, s));
   RPF_HIP(hipStreamSynchronize(s));
@@ -1499,6 +1497,7 @@ void ensure_coarse_M(rpf_problem pb, const rpf_pattern* pats, int kind, hipStrea
   RPF_LAUNCH_CHECK();
   pb->Hinv.alloc((size_t)nG * nG);
   potri_lower(s, H.p, nG, nG, dinv.p, pb->Hinv.p, nG);
+  mirror_lower(s, pb->Hinv.p, nG, nG);
   int hst = 0;
   std::vector<double> hd((size_t)2 * nG);
   RPF_HIP(hipMemcpyAsync(&hst, st.p, sizeof(int), hipMemcpyDeviceToHost, s));

@@ -67,17 +67,6 @@ __global__ void k_max(const double* x, int64_t n, double* out) {
   if (threadIdx.x == 0) out[0] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
 }
 
-__global__ void k_symmetrize(double* A, int64_t n, int64_t ld) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n * n) return;
-  const int64_t r = i % n, c = i / n;
-  if (r > c) {
-    const double v = 0.5 * (A[c * ld + r] + A[r * ld + c]);
-    A[c * ld + r] = v;
-    A[r * ld + c] = v;
-  }
-}
-
 __device__ inline uint16_t bf16_rne(float f) {
   uint32_t u = __float_as_uint(f);
   u += 0x7FFFu + ((u >> 16) & 1u);
@@ -267,8 +256,7 @@ extern "C" rpf_status pattern_factor(int32_t n, const int32_t* rowptr, const int
     const double sigma = 1e-9 * normS;
     DevBuf<double> C((size_t)n_b * n_b), dinvC((size_t)cdiv(n_b, NB) * NB * NB), V((size_t)n_b * kb),
         W((size_t)n_b * kb), H(kb * kb), U(kb * kb), theta(kb);
-    copy_matrix(s, P->S.p, n_b, C.p, n_b, n_b, n_b);
-    add_diag(s, C.p, n_b, n_b, sigma);
+    add_outer(s, n_b, P->S.p, n_b, 0, nullptr, 0.0, sigma, C.p, n_b, false);
     const Envelope envC = Envelope::dense(n_b);
     potrf(s, C.p, n_b, n_b, n_b, envC, dinvC.p, P->status.p);
     check_status(s, P->status.p, "pattern_factor (Schur complement S + sigma I)");
@@ -317,17 +305,13 @@ extern "C" rpf_status pattern_condense(rpf_pattern p, int32_t prec, void* stream
     const int nb = p->n_b;
     if (!(p->condensed & 1u)) {
       DevBuf<double> M((size_t)nb * nb), dinv((size_t)cdiv(nb, NB) * NB * NB);
-      copy_matrix(s, p->S.p, nb, M.p, nb, nb, nb);
-      if (p->k > 0) dgemm(s, false, true, nb, nb, p->k, 1.0, p->Z.p, nb, p->Z.p, nb, 1.0, M.p, nb);
+      add_outer(s, nb, p->S.p, nb, p->k, p->Z.p, 1.0, 0.0, M.p, nb, false);
       const Envelope env = Envelope::dense(nb);
       RPF_HIP(hipMemsetAsync(p->status.p, 0, sizeof(int), s));
       potrf(s, M.p, nb, nb, nb, env, dinv.p, p->status.p);
       p->Splus.alloc((size_t)nb * nb);
       potri_lower(s, M.p, nb, nb, dinv.p, p->Splus.p, nb);
-      if (p->k > 0) dgemm(s, false, true, nb, nb, p->k, -1.0, p->Z.p, nb, p->Z.p, nb, 1.0, p->Splus.p, nb);
-      hipLaunchKernelGGL(k_symmetrize, dim3((unsigned)cdiv((int64_t)nb * nb, 256)), dim3(256), 0, s, p->Splus.p,
-                         (int64_t)nb, (int64_t)nb);
-      RPF_LAUNCH_CHECK();
+      add_outer(s, nb, p->Splus.p, nb, p->k, p->Z.p, -1.0, 0.0, p->Splus.p, nb, true);
       check_status(s, p->status.p, "pattern_condense (S + Z Z^T)");
       p->condensed |= 1u;
     }
