@@ -234,11 +234,19 @@ void potrf(hipStream_t s, double* A, int64_t lda, int64_t n, int64_t n_fac, cons
 // A[n_fac:, n_fac:] -= L_b L_b^T  with L_b = A[n_fac:, :n_fac] (lower triangle).
 void schur_update(hipStream_t s, double* A, int64_t lda, int64_t n, int64_t n_fac);
 
-// B <- L^{-1} B (trans = false) or L^{-T} B (trans = true), L = leading n x n of a factor.
+// Explicit inverses of the TRI_BW-row diagonal blocks of a lower factor, a TRI_BW x TRI_BW column-major slab
+// each: lo = L_TT^{-1} (zeros above the diagonal), up = its transpose.
+constexpr int64_t TRI_BW = 512;
+struct TriInv {
+  DevBuf<double> lo, up;
+};
+void build_tri_inv(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double* dinv, TriInv& inv);
+// B <- (L L^T)^{-1} B, L = leading n x n of a factor with its inverted NB blocks (dinv, see potrf) and
+// TRI_BW blocks (inv).
 // upper: the strict upper triangle of L's envelope holds L^T (mirror_envelope has run on it), so the
 // transposed solve reads the rows of L^T as contiguous columns.
-void trsm(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double* dinv,
-          const Envelope& env, double* B, int64_t ldb, int64_t nrhs, bool trans, bool upper = false);
+void potrs(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double* dinv, const TriInv& inv,
+           const Envelope& env, double* B, int64_t ldb, int64_t nrhs, bool upper = false);
 // A[c, r] = A[r, c] for every entry r > c of the envelope of the leading n x n factor (column block
 // t: rows up to env.rend[t]); the lower triangle is left as it is.
 void mirror_envelope(hipStream_t s, double* A, int64_t lda, int64_t n, const Envelope& env);

@@ -2187,58 +2187,6 @@ __global__ __launch_bounds__(256) void k_trsm_panel(const double* L, int64_t ldl
   }
 }
 
-void trsm(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double* dinv, const Envelope& env,
-          double* B, int64_t ldb, int64_t nrhs, bool trans, bool upper) {
-  if (n <= 0 || nrhs <= 0) return;
-  const int64_t nblk = cdiv(n, NB);
-  bool dense = true;
-  for (int64_t t = 0; t < nblk && dense; ++t) dense = env.cstart[t] <= 0 && env.rend[t] >= n;
-  if (!dense && nrhs >= 2048) {
-    // banded factor, many right-hand sides: one persistent pass per 16- or 32-column panel
-    std::vector<int64_t> bounds(2 * nblk);
-    for (int64_t t = 0; t < nblk; ++t) {
-      bounds[t] = env.cstart[t];
-      bounds[nblk + t] = env.rend[t];
-    }
-    DevBuf<int64_t> db;
-    db.upload(bounds.data(), bounds.size(), s);
-    // 16 columns per workgroup, two workgroups per CU, where the band of L (or of the mirrored L^T)
-    // is read sixteen rows at a time: 12.7 ms each way at 8192 columns of the 20^3 pattern (32
-    // columns, one workgroup per CU: 14 ms forward, 14.3 ms backward).  Without the mirror the
-    // backward reads columns of L, and 32 columns per workgroup halve that less efficient band
-    // traffic (15.5 ms; 21 ms at 16).
-    if (!trans)
-      hipLaunchKernelGGL((k_trsm_panel<true, 1>), dim3((unsigned)cdiv(nrhs, 16)), dim3(256), 0, s, L, ldl, n, dinv,
-                         db.p, db.p + nblk, B, ldb, nrhs);
-    else if (upper)
-      hipLaunchKernelGGL((k_trsm_panel<false, 1, true>), dim3((unsigned)cdiv(nrhs, 16)), dim3(256), 0, s, L, ldl, n,
-                         dinv, db.p, db.p + nblk, B, ldb, nrhs);
-    else
-      hipLaunchKernelGGL((k_trsm_panel<false, 2>), dim3((unsigned)cdiv(nrhs, 32)), dim3(256), 0, s, L, ldl, n, dinv,
-                         db.p, db.p + nblk, B, ldb, nrhs);
-    RPF_LAUNCH_CHECK();
-    RPF_HIP(hipStreamSynchronize(s));  // the bounds buffer is freed on return
-    return;
-  }
-  // Right-looking: X_t = inv(L_tt) B_t (or its transpose) through a block buffer, then the update of the
-  // rows of its envelope below (above).
-  DevBuf<double> xt((size_t)NB * nrhs);
-  for (int64_t u = 0; u < nblk; ++u) {
-    const int64_t t = trans ? nblk - 1 - u : u;
-    const int64_t j0 = t * NB;
-    const int jb = (int)std::min<int64_t>(NB, n - j0);
-    // dinv holds the inverse by rows, i.e. its transpose by columns
-    dgemm(s, !trans, false, jb, nrhs, jb, 1.0, dinv + t * NB * NB, NB, B + j0, ldb, 0.0, xt.p, NB);
-    copy_matrix(s, xt.p, NB, B + j0, ldb, jb, nrhs);
-    const int64_t r0 = trans ? std::max<int64_t>(0, env.cstart[t]) : j0 + jb;
-    const int64_t r1 = trans ? j0 : std::min<int64_t>(env.rend[t], n);
-    if (r1 > r0)
-      dgemm(s, trans, false, r1 - r0, nrhs, jb, -1.0, trans ? L + r0 * ldl + j0 : L + j0 * ldl + r0, ldl, xt.p, NB, 1.0,
-            B + r0, ldb);
-  }
-  RPF_HIP(hipStreamSynchronize(s));  // the block buffer is freed on return
-}
-
 // ============================================================================ block inverses
 // X = the inverses of the diagonal blocks of bw rows (a multiple of NB) of a lower factor L, each bw x bw
 // column-major in a slab of its own, from the inverted NB x NB blocks: the pairs of inverted blocks of
@@ -2377,6 +2325,177 @@ void add_outer(hipStream_t s, int64_t n, const double* A, int64_t lda, int k, co
   hipLaunchKernelGGL(k_add_outer, dim3((unsigned)cdiv(n, 64), (unsigned)cdiv(n, 64)), dim3(256), 0, s, n, A, lda, k, Z,
                      alpha, sigma, B, ldb, full ? 1 : 0);
   RPF_LAUNCH_CHECK();
+}
+
+// ============================================================================ triangular solves
+// up_b = (lo_b)^T for the bw x bw blocks of the inverses, 64 x 64 tiles through LDS
+__global__ __launch_bounds__(256) void k_transpose_blocks(int64_t bw, const double* lo, double* up) {
+  __shared__ double t[64][65];
+  const double* x = lo + (int64_t)blockIdx.z * bw * bw;
+  double* y = up + (int64_t)blockIdx.z * bw * bw;
+  const int64_t r0 = (int64_t)blockIdx.x * 64, c0 = (int64_t)blockIdx.y * 64;
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  for (int c = ty; c < 64; c += 4) t[c][tx] = x[(c0 + c) * bw + r0 + tx];
+  __syncthreads();
+  for (int r = ty; r < 64; r += 4) y[(r0 + r) * bw + c0 + tx] = t[tx][r];
+}
+
+void build_tri_inv(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double* dinv, TriInv& inv) {
+  if (n <= 0) return;
+  const int64_t nb = cdiv(n, TRI_BW), len = nb * TRI_BW * TRI_BW;
+  inv.lo.ensure((size_t)len);
+  inv.up.ensure((size_t)len);
+  // the joined blocks below the diagonal fit in the slab of the transposes until those are made
+  static_assert(TRI_BW == 4 * NB, "scratch of the last level: half a slab a pair");
+  fill(s, inv.lo.p, len, 0.0);
+  invert_blocks(s, L, ldl, n, dinv, inv.lo.p, TRI_BW, inv.up.p);
+  hipLaunchKernelGGL(k_transpose_blocks, dim3(TRI_BW / 64, TRI_BW / 64, (unsigned)nb), dim3(256), 0, s, TRI_BW,
+                     inv.lo.p, inv.up.p);
+  RPF_LAUNCH_CHECK();
+}
+
+// C (M x c, column-major) = beta C + alpha op(A) X with few columns (16 per workgroup): a workgroup takes
+// 32 rows, its four waves a quarter of K each, 32 k at a time with the next 32 on their way, and the
+// four partial results are added in LDS.  TA: op(A) = A^T, A stored K x M.  A walk over a 512-row block
+// is four load latencies a wave (5 us at 6,700 rows and 8 columns), where the general product has 32
+// dependent k-stages of 16 (14 to 17 us at K = 128 alone).
+template <bool TA>
+__global__ __launch_bounds__(256) void k_skinny(int64_t M, int64_t c, int64_t K, double alpha, const double* A,
+                                                int64_t lda, const double* X, int64_t ldx, double beta, double* C,
+                                                int64_t ldc) {
+  constexpr int R = 2, U = 8;  // row tiles of a workgroup, MFMA steps of a batch
+  __shared__ double red[4][16 * R][17];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int fl = lane & 15, fk = lane >> 4;
+  const int64_t m0 = (int64_t)blockIdx.x * 16 * R, c0 = (int64_t)blockIdx.y * 16;
+  const int64_t kc = (K + 127) / 128 * 32;  // a wave's quarter, whole batches
+  const int64_t kb = min(w * kc, K), ke = min(kb + kc, K);
+  const double* Xc = X + min(c0 + fl, c - 1) * ldx;
+  const double* Ar[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    const int64_t m = min(m0 + 16 * i + fl, M - 1);
+    Ar[i] = TA ? A + m * lda : A + m;
+  }
+  v4d acc[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) acc[i] = v4d{0.0, 0.0, 0.0, 0.0};
+  double a[R][U], x[U], na[R][U], nx[U];
+  auto load = [&](int64_t k0, double (&pa)[R][U], double (&px)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t k = k0 + 4 * u + fk, kk = min(k, K - 1);
+#pragma unroll
+      for (int i = 0; i < R; ++i) pa[i][u] = TA ? Ar[i][kk] : Ar[i][kk * lda];
+      px[u] = Xc[kk];
+    }
+  };
+  if (kb < ke) load(kb, a, x);
+  for (int64_t k0 = kb; k0 < ke; k0 += 4 * U) {
+    const bool more = k0 + 4 * U < ke;
+    if (more) load(k0 + 4 * U, na, nx);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool in = k0 + 4 * u + fk < ke;
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+        acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? x[u] : 0.0, in ? a[i][u] : 0.0, acc[i], 0, 0, 0);
+    }
+    if (more) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        x[u] = nx[u];
+#pragma unroll
+        for (int i = 0; i < R; ++i) a[i][u] = na[i][u];
+      }
+    }
+  }
+  // item r of lane l: column l / 16 + 4 r, row l % 16
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) red[w][16 * i + fl][fk + 4 * r] = acc[i][r];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 2 * R; ++u) {
+    const int row = tid & (16 * R - 1), col = (tid / (16 * R)) + u * (256 / (16 * R));
+    if (col < 16 && m0 + row < M && c0 + col < c) {
+      const double v = alpha * (red[0][row][col] + red[1][row][col] + red[2][row][col] + red[3][row][col]);
+      double* o = C + (c0 + col) * ldc + m0 + row;
+      *o = beta == 0.0 ? v : v + beta * *o;
+    }
+  }
+}
+
+// up to this many columns k_skinny is the faster one (64 x 64 tiles re-read less of A above)
+constexpr int64_t SKINNY = 96;
+static void tri_product(hipStream_t s, bool ta, int64_t M, int64_t c, int64_t K, double alpha, const double* A,
+                        int64_t lda, const double* X, int64_t ldx, double beta, double* C, int64_t ldc) {
+  if (M <= 0 || c <= 0 || K <= 0) return;
+  if (c > SKINNY) {
+    dgemm(s, ta, false, M, c, K, alpha, A, lda, X, ldx, beta, C, ldc);
+    return;
+  }
+  const dim3 g((unsigned)cdiv(M, 32), (unsigned)cdiv(c, 16));
+  if (ta)
+    hipLaunchKernelGGL(k_skinny<true>, g, dim3(256), 0, s, M, c, K, alpha, A, lda, X, ldx, beta, C, ldc);
+  else
+    hipLaunchKernelGGL(k_skinny<false>, g, dim3(256), 0, s, M, c, K, alpha, A, lda, X, ldx, beta, C, ldc);
+  RPF_LAUNCH_CHECK();
+}
+
+// The serial chain of a solve is its diagonal blocks: they are taken TRI_BW = 512 rows at a time through
+// explicit inverses, two launches each (X_T = inv(L_TT) B_T, then the rows below in the envelope).
+// The forward solution goes to a second buffer and the backward one returns to B, so nothing is
+// copied.  Many columns of a banded factor instead take one persistent pass each way.
+void potrs(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double* dinv, const TriInv& inv,
+           const Envelope& env, double* B, int64_t ldb, int64_t nrhs, bool upper) {
+  if (n <= 0 || nrhs <= 0) return;
+  const int64_t nblk = cdiv(n, NB);
+  bool dense = true;
+  for (int64_t t = 0; t < nblk && dense; ++t) dense = env.cstart[t] <= 0 && env.rend[t] >= n;
+  if (!dense && nrhs >= 2048) {
+    std::vector<int64_t> bounds(2 * nblk);
+    for (int64_t t = 0; t < nblk; ++t) {
+      bounds[t] = env.cstart[t];
+      bounds[nblk + t] = env.rend[t];
+    }
+    DevBuf<int64_t> db;
+    db.upload(bounds.data(), bounds.size(), s);
+    // 16 columns per workgroup, two workgroups per CU, where the band of L (or of the mirrored L^T)
+    // is read sixteen rows at a time: 12.7 ms each way at 8192 columns of the 20^3 pattern (32
+    // columns, one workgroup per CU: 14 ms forward, 14.3 ms backward).  Without the mirror the
+    // backward reads columns of L, and 32 columns per workgroup halve that less efficient band
+    // traffic (15.5 ms; 21 ms at 16).
+    hipLaunchKernelGGL((k_trsm_panel<true, 1>), dim3((unsigned)cdiv(nrhs, 16)), dim3(256), 0, s, L, ldl, n, dinv, db.p,
+                       db.p + nblk, B, ldb, nrhs);
+    if (upper)
+      hipLaunchKernelGGL((k_trsm_panel<false, 1, true>), dim3((unsigned)cdiv(nrhs, 16)), dim3(256), 0, s, L, ldl, n,
+                         dinv, db.p, db.p + nblk, B, ldb, nrhs);
+    else
+      hipLaunchKernelGGL((k_trsm_panel<false, 2>), dim3((unsigned)cdiv(nrhs, 32)), dim3(256), 0, s, L, ldl, n, dinv,
+                         db.p, db.p + nblk, B, ldb, nrhs);
+    RPF_LAUNCH_CHECK();
+    RPF_HIP(hipStreamSynchronize(s));  // the bounds buffer is freed on return
+    return;
+  }
+  DevBuf<double> F((size_t)n * nrhs);
+  const int64_t nT = cdiv(n, TRI_BW), per = TRI_BW / NB;
+  for (int64_t t = 0; t < nT; ++t) {
+    const int64_t j0 = t * TRI_BW, jb = std::min(TRI_BW, n - j0), r0 = j0 + jb;
+    const int64_t rend = std::min(env.rend[std::min((t + 1) * per, nblk) - 1], n);
+    tri_product(s, false, jb, nrhs, jb, 1.0, inv.lo.p + t * TRI_BW * TRI_BW, TRI_BW, B + j0, ldb, 0.0, F.p + j0, n);
+    tri_product(s, false, rend - r0, nrhs, jb, -1.0, L + j0 * ldl + r0, ldl, F.p + j0, n, 1.0, B + r0, ldb);
+  }
+  for (int64_t t = nT - 1; t >= 0; --t) {
+    const int64_t j0 = t * TRI_BW, jb = std::min(TRI_BW, n - j0);
+    int64_t cs = j0;
+    for (int64_t q = t * per; q < std::min((t + 1) * per, nblk); ++q) cs = std::min(cs, std::max<int64_t>(0, env.cstart[q]));
+    tri_product(s, false, jb, nrhs, jb, 1.0, inv.up.p + t * TRI_BW * TRI_BW, TRI_BW, F.p + j0, n, 0.0, B + j0, ldb);
+    tri_product(s, !upper, j0 - cs, nrhs, jb, -1.0, upper ? L + j0 * ldl + cs : L + cs * ldl + j0, ldl, B + j0, ldb, 1.0,
+                F.p + cs, n);
+  }
+  RPF_HIP(hipStreamSynchronize(s));  // the second buffer is freed on return
 }
 
 // ============================================================================ elementwise helpers

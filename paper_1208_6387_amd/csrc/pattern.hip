@@ -233,6 +233,7 @@ extern "C" rpf_status pattern_factor(int32_t n, const int32_t* rowptr, const int
     if (n_i > 0) {
       P->dinv_ii.alloc((size_t)nblk * NB * NB);
       potrf(s, P->L.p, P->ld, n, n_i, P->env_ii, P->dinv_ii.p, P->status.p);
+      build_tri_inv(s, P->L.p, P->ld, n_i, P->dinv_ii.p, P->inv_ii);
       schur_update(s, P->L.p, P->ld, n, n_i);
       // L_ii^T in the (otherwise unused) upper triangle: the backward solves read it row-contiguous
       mirror_envelope(s, P->L.p, P->ld, n_i, P->env_ii);
@@ -259,14 +260,15 @@ extern "C" rpf_status pattern_factor(int32_t n, const int32_t* rowptr, const int
     add_outer(s, n_b, P->S.p, n_b, 0, nullptr, 0.0, sigma, C.p, n_b, false);
     const Envelope envC = Envelope::dense(n_b);
     potrf(s, C.p, n_b, n_b, n_b, envC, dinvC.p, P->status.p);
+    TriInv invC;
+    build_tri_inv(s, C.p, n_b, n_b, dinvC.p, invC);
     check_status(s, P->status.p, "pattern_factor (Schur complement S + sigma I)");
     hipLaunchKernelGGL(k_random_block, dim3((unsigned)cdiv((int64_t)n_b * kb, 256)), dim3(256), 0, s, V.p,
                        (int64_t)n_b, (int64_t)n_b, kb);
     RPF_LAUNCH_CHECK();
     orthonormalize(s, V.p, n_b, n_b, kb);
     for (int it = 0; it < 3; ++it) {
-      trsm(s, C.p, n_b, n_b, dinvC.p, envC, V.p, n_b, kb, false);
-      trsm(s, C.p, n_b, n_b, dinvC.p, envC, V.p, n_b, kb, true);
+      potrs(s, C.p, n_b, n_b, dinvC.p, invC, envC, V.p, n_b, kb);
       orthonormalize(s, V.p, n_b, n_b, kb);
     }
     dgemm(s, false, false, n_b, kb, n_b, 1.0, P->S.p, n_b, V.p, n_b, 0.0, W.p, n_b);
@@ -390,8 +392,9 @@ extern "C" rpf_status rpf_dposv(int64_t n, double* A, int64_t lda, int64_t nrhs,
     const Envelope env = Envelope::dense(n);
     potrf(s, A, lda, n, n, env, dinv.p, st.p);
     if (nrhs > 0) {
-      trsm(s, A, lda, n, dinv.p, env, B, ldb, nrhs, false);
-      trsm(s, A, lda, n, dinv.p, env, B, ldb, nrhs, true);
+      TriInv inv;
+      build_tri_inv(s, A, lda, n, dinv.p, inv);
+      potrs(s, A, lda, n, dinv.p, inv, env, B, ldb, nrhs);
     }
     check_status(s, st.p, "rpf_dposv");
   });

@@ -14,6 +14,7 @@ struct rpf_pattern_s {
   rpf::DevBuf<double> L;
   int64_t ld = 0;
   rpf::DevBuf<double> dinv_ii;  // inverses of the NB x NB diagonal blocks of L_ii
+  rpf::TriInv inv_ii;           // and of its TRI_BW-row ones
   rpf::Envelope env_ii;
   bool L_upper = false;         // the upper triangle of L_ii's envelope holds L_ii^T
 
