@@ -224,15 +224,23 @@ struct Envelope {
   static Envelope dense(int64_t n);
 };
 
-// In-place blocked right-looking Cholesky of the leading n_fac columns of the
-// n x n symmetric matrix A (lower triangle).  Rows >= n_fac are dense
-// ("boundary") rows; the trailing block A[n_fac:, n_fac:] is NOT updated here
-// (use schur_update).  dinv receives the inverse of every NB x NB diagonal
-// block by rows (cdiv(n_fac, NB) * NB * NB doubles).  A non-positive pivot sets *status.
-void potrf(hipStream_t s, double* A, int64_t lda, int64_t n, int64_t n_fac, const Envelope& env,
-           double* dinv, int* status);
-// A[n_fac:, n_fac:] -= L_b L_b^T  with L_b = A[n_fac:, :n_fac] (lower triangle).
-void schur_update(hipStream_t s, double* A, int64_t lda, int64_t n, int64_t n_fac);
+// Rows of a partial factorisation below its columns: n rows (column-major, ld), sorted by the first column
+// in which they are not zero; active[t]: how many of them reach column block t (NB columns) or
+// an earlier one.
+struct BoundaryRows {
+  double* p = nullptr;
+  int64_t ld = 0, n = 0;
+  std::vector<int64_t> active;
+};
+
+// In-place blocked right-looking Cholesky of the n x n symmetric matrix A (lower triangle); the boundary
+// rows become L_b = A_b L^{-T}.  A may stand in band storage: only entries of the envelope, and of the
+// rectangles of its column blocks, are touched.  dinv receives the inverse of every NB x NB diagonal
+// block by rows (cdiv(n, NB) * NB * NB doubles).  A non-positive pivot sets *status.
+void potrf(hipStream_t s, double* A, int64_t lda, int64_t n, const Envelope& env, double* dinv, int* status,
+           const BoundaryRows& bnd = BoundaryRows());
+// S -= L_b L_b^T (lower triangle), L_b with n columns.
+void schur_update(hipStream_t s, double* S, int64_t lds, int64_t n, const BoundaryRows& bnd);
 
 // Explicit inverses of the TRI_BW-row diagonal blocks of a lower factor, a TRI_BW x TRI_BW column-major slab
 // each: lo = L_TT^{-1} (zeros above the diagonal), up = its transpose.

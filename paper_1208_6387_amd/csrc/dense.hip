@@ -1846,12 +1846,12 @@ Envelope Envelope::dense(int64_t n) {
   return e;
 }
 
-// L21 = A21 W^T in place for the NB-wide column block `col` (jb columns) on two ranges of rows (below the
-// diagonal block, and the boundary rows), W = L11^{-1} by rows (dinv).  One workgroup per 32 rows reads
+// L21 = A21 W^T in place for an NB-wide column block (jb columns) on two ranges of rows (C0: below the
+// diagonal block; C1: the boundary rows), W = L11^{-1} by rows (dinv).  One workgroup per 32 rows reads
 // all of its columns before it writes any.  Wave w takes the column tiles w and 7 - w, nine 16 x 16
 // blocks of the triangle in all, whose W operands are loaded before the rows are waited for: one load
 // latency and 72 MFMAs a wave, 5 us where the four k-stages of the general product took 11.
-__global__ __launch_bounds__(256) void k_panel(double* col, int64_t lda, int64_t r0, int64_t len0, int64_t r1,
+__global__ __launch_bounds__(256) void k_panel(double* C0, int64_t ld0, int64_t len0, double* C1, int64_t ld1,
                                                int64_t len1, int jb, const double* dinv) {
   static_assert(NB == 128, "k_panel assumes 128-wide blocks");
   constexpr int LD = 40;  // the two k-rows of a half-wave (two apart) on opposite bank halves
@@ -1862,7 +1862,8 @@ __global__ __launch_bounds__(256) void k_panel(double* col, int64_t lda, int64_t
   const int64_t t0 = (len0 + 31) / 32;
   const bool second = (int64_t)blockIdx.x >= t0;
   const int64_t off = 32 * (second ? (int64_t)blockIdx.x - t0 : (int64_t)blockIdx.x);
-  double* C = col + (second ? r1 : r0) + off;
+  double* C = (second ? C1 : C0) + off;
+  const int64_t lda = second ? ld1 : ld0;
   const int nr = (int)min<int64_t>(32, (second ? len1 : len0) - off);
   double2 wv[18];
   const int n1 = 2 * (w + 1);  // 8-k groups of tile w, then 18 - n1 of tile 7 - w
@@ -1923,29 +1924,30 @@ __global__ __launch_bounds__(256) void k_panel(double* col, int64_t lda, int64_t
       }
 }
 
-// C -= X Y^T for two ranges of rows of the factor in one launch: rows X0 (len0) only where they reach the
-// lower triangle (their first row is the first row of Y), rows X1 (len1) in full; Y: N x K.  64 x 64
+// C -= X Y^T for two ranges of rows in one launch, Y the first N rows of X0: rows X0 (len0) only where they
+// reach the lower triangle, rows X1 (len1, the boundary rows) in full; K columns.  64 x 64
 // tiles with 64-k stages: a rank-NB update is two stages, so two load latencies.
-__global__ __launch_bounds__(256) void k_rank_update(int64_t len0, const double* X0, double* C0, int64_t len1,
-                                                     const double* X1, double* C1, int64_t N, int64_t K,
-                                                     const double* Y, int64_t lda) {
+__global__ __launch_bounds__(256) void k_rank_update(int64_t len0, const double* X0, double* C0, int64_t ld0,
+                                                     int64_t len1, const double* X1, double* C1, int64_t ld1,
+                                                     int64_t N, int64_t K) {
   const int t0 = (int)((len0 + 63) / 64);
   const bool second = (int)blockIdx.x >= t0;
-  dgemm_tile<64, 64, 2, 2, false, true, 64>(second ? len1 : len0, N, K, -1.0, second ? X1 : X0, lda, Y, lda, 1.0,
-                                            second ? C1 : C0, lda, second ? 0 : 1, K, nullptr,
+  const int64_t ld = second ? ld1 : ld0;
+  dgemm_tile<64, 64, 2, 2, false, true, 64>(second ? len1 : len0, N, K, -1.0, second ? X1 : X0, ld, X0, ld0, 1.0,
+                                            second ? C1 : C0, ld, second ? 0 : 1, K, nullptr,
                                             second ? (int)blockIdx.x - t0 : (int)blockIdx.x, blockIdx.y, 0);
 }
 
-static void rank_update(hipStream_t s, double* A, int64_t lda, int64_t j0, int64_t K, int64_t r0, int64_t rend,
-                        int64_t r1, int64_t len1, int64_t cend) {
+// columns [r0, cend) of the rows [r0, rend) of the factor and of the first len1 boundary rows, minus the
+// K columns from j0
+static void rank_update(hipStream_t s, double* A, int64_t lda, const BoundaryRows& bnd, int64_t len1, int64_t j0,
+                        int64_t K, int64_t r0, int64_t rend, int64_t cend) {
   const int64_t N = cend - r0;
   if (N <= 0 || K <= 0) return;
-  const int64_t tiles = cdiv(rend - r0, 64) + cdiv(len1, 64);
-  if (tiles == 0) return;
   RPF_CHECK(cdiv(N, 64) <= 65535, RPF_EINVAL, "potrf: grid too large");
-  hipLaunchKernelGGL(k_rank_update, dim3((unsigned)tiles, (unsigned)cdiv(N, 64)), dim3(256), 0, s, rend - r0,
-                     A + j0 * lda + r0, A + r0 * lda + r0, len1, A + j0 * lda + r1, A + r0 * lda + r1, N, K,
-                     A + j0 * lda + r0, lda);
+  hipLaunchKernelGGL(k_rank_update, dim3((unsigned)(cdiv(rend - r0, 64) + cdiv(len1, 64)), (unsigned)cdiv(N, 64)),
+                     dim3(256), 0, s, rend - r0, A + j0 * lda + r0, A + r0 * lda + r0, lda, len1, bnd.p + j0 * bnd.ld,
+                     bnd.p + r0 * bnd.ld, bnd.ld, N, K);
   RPF_LAUNCH_CHECK();
 }
 
@@ -1959,19 +1961,20 @@ bool gemm_nt_flex(hipStream_t s, int64_t M, int64_t N, int64_t K, double alpha, 
                   const double* Y, int64_t ldy, double beta, double* C, int64_t ldc, bool lower, DevBuf<double>& wa,
                   DevBuf<double>& wb);
 
-void potrf(hipStream_t s, double* A, int64_t lda, int64_t n, int64_t n_fac, const Envelope& env, double* dinv,
-           int* status) {
+void potrf(hipStream_t s, double* A, int64_t lda, int64_t n_fac, const Envelope& env, double* dinv, int* status,
+           const BoundaryRows& bnd) {
   constexpr int64_t PANEL = 2 * NB;
   // rows from which a trailing update goes to the large-problem kernel (which needs copies of its
   // operands): below, its 128 x 128 tiles leave CUs idle
   constexpr int64_t LARGE = 4096;
   const int64_t nblk = cdiv(n_fac, NB);
-  RPF_CHECK((int64_t)env.rend.size() >= nblk, RPF_EINVAL, "potrf: envelope too short");
+  RPF_CHECK((int64_t)env.rend.size() >= nblk && (bnd.n == 0 || (int64_t)bnd.active.size() >= nblk), RPF_EINVAL,
+            "potrf: envelope too short");
   DevBuf<double> wa, wb;  // operand copies of the large rank-PANEL updates
-  const int64_t nbnd = n - n_fac;
   for (int64_t P0 = 0; P0 < n_fac; P0 += PANEL) {
     const int64_t P1 = std::min<int64_t>(P0 + PANEL, n_fac);
     int64_t pend = P1;  // rows (and columns) reached by the panel's envelope
+    int64_t act = 0;    // boundary rows reached by the panel
     for (int64_t j0 = P0; j0 < P1; j0 += NB) {
       const int64_t t = j0 / NB;
       const int jb = (int)std::min<int64_t>(NB, n_fac - j0);
@@ -1981,29 +1984,30 @@ void potrf(hipStream_t s, double* A, int64_t lda, int64_t n, int64_t n_fac, cons
       const int64_t r0 = j0 + jb;
       const int64_t rend = std::max<int64_t>(r0, std::min<int64_t>(env.rend[t], n_fac));
       pend = std::max(pend, rend);
-      const int64_t tiles = cdiv(rend - r0, 32) + cdiv(nbnd, 32);
+      act = bnd.n ? bnd.active[t] : 0;
+      const int64_t tiles = cdiv(rend - r0, 32) + cdiv(act, 32);
       if (tiles > 0) {
-        hipLaunchKernelGGL(k_panel, dim3((unsigned)tiles), dim3(256), 0, s, A + j0 * lda, lda, r0, rend - r0, n_fac,
-                           nbnd, jb, dt);
+        hipLaunchKernelGGL(k_panel, dim3((unsigned)tiles), dim3(256), 0, s, A + j0 * lda + r0, lda, rend - r0,
+                           bnd.p + j0 * bnd.ld, bnd.ld, act, jb, dt);
         RPF_LAUNCH_CHECK();
       }
       // the remaining columns of this panel (rows within the envelope, boundary rows)
-      rank_update(s, A, lda, j0, jb, r0, rend, n_fac, nbnd, std::min(rend, P1));
+      rank_update(s, A, lda, bnd, act, j0, jb, r0, rend, std::min(rend, P1));
     }
     // rank-PANEL update of everything right of the panel (the boundary-boundary block is deferred);
     // rows of a step's columns past its own envelope end are zero, so one product over the
     // panel's whole envelope is exact
     if (pend > P1) {
-      const int64_t K = P1 - P0;
-      double* pc = A + P0 * lda;
-      const bool big0 = pend - P1 >= LARGE, big1 = nbnd >= LARGE;
-      const bool done0 = big0 && gemm_nt_flex(s, pend - P1, pend - P1, K, -1.0, pc + P1, lda, pc + P1, lda, 1.0,
-                                              A + P1 * lda + P1, lda, true, wa, wb);
-      const bool done1 = big1 && gemm_nt_flex(s, nbnd, pend - P1, K, -1.0, pc + n_fac, lda, pc + P1, lda, 1.0,
-                                              A + P1 * lda + n_fac, lda, false, wa, wb);
-      if (!done0) rank_update(s, A, lda, P0, K, P1, pend, n_fac, done1 ? 0 : nbnd, pend);
-      else if (!done1 && nbnd > 0)
-        dgemm(s, false, true, nbnd, pend - P1, K, -1.0, pc + n_fac, lda, pc + P1, lda, 1.0, A + P1 * lda + n_fac, lda);
+      const int64_t K = P1 - P0, N = pend - P1;
+      double* pc = A + P0 * lda + P1;
+      const bool done0 = N >= LARGE && gemm_nt_flex(s, N, N, K, -1.0, pc, lda, pc, lda, 1.0, A + P1 * lda + P1, lda, true,
+                                                    wa, wb);
+      const bool done1 = act >= LARGE && gemm_nt_flex(s, act, N, K, -1.0, bnd.p + P0 * bnd.ld, bnd.ld, pc, lda, 1.0,
+                                                      bnd.p + P1 * bnd.ld, bnd.ld, false, wa, wb);
+      if (!done0)
+        rank_update(s, A, lda, bnd, done1 ? 0 : act, P0, K, P1, pend, pend);
+      else if (!done1 && act > 0)
+        dgemm(s, false, true, act, N, K, -1.0, bnd.p + P0 * bnd.ld, bnd.ld, pc, lda, 1.0, bnd.p + P1 * bnd.ld, bnd.ld);
     }
   }
   RPF_HIP(hipStreamSynchronize(s));  // the operand copies are freed on return
@@ -2052,19 +2056,23 @@ bool gemm_nt_flex(hipStream_t s, int64_t M, int64_t N, int64_t K, double alpha, 
   return dgemm_flex(s, M, N, K, alpha, Ause, lda, wb.p, ldb, beta, C, ldc, lower);
 }
 
-void schur_update(hipStream_t s, double* A, int64_t lda, int64_t n, int64_t n_fac) {
-  const int64_t nb = n - n_fac;
-  if (nb <= 0 || n_fac <= 0) return;
-  const double* Lbi = A + n_fac;  // boundary rows of the factor, nb x n_fac with ld lda
-  // lower tiles only: S is symmetric and only its lower triangle is read afterwards
+// The boundary rows are sorted by the first interior column that they reach, so the columns of a group
+// meet a prefix of them: the product is taken group by group on that prefix.  On the 20^3 brick that is
+// a third of the flops of one product over all rows and columns (1,069 GFLOP).
+void schur_update(hipStream_t s, double* S, int64_t lds, int64_t n_fac, const BoundaryRows& bnd) {
+  constexpr int64_t GROUP = 8 * NB;  // S is read and written once per group
   DevBuf<double> wa, wb;
-  const bool done = gemm_nt_flex(s, nb, nb, n_fac, -1.0, Lbi, lda, Lbi, lda, 1.0, A + n_fac * lda + n_fac, lda, true,
-                                 wa, wb);
-  if (done) {
-    RPF_HIP(hipStreamSynchronize(s));  // the copies are freed on return
-    return;
+  for (int64_t c0 = 0; c0 < n_fac; c0 += GROUP) {
+    const int64_t K = std::min<int64_t>(GROUP, n_fac - c0);
+    // an even count for the large-problem kernel (rows past the prefix are zero in these columns)
+    const int64_t act = std::min(bnd.n, bnd.active[(c0 + K - 1) / NB] + (bnd.active[(c0 + K - 1) / NB] & 1));
+    if (act == 0) continue;
+    const double* X = bnd.p + c0 * bnd.ld;
+    // lower tiles only: S is symmetric and only its lower triangle is read afterwards
+    if (!gemm_nt_flex(s, act, act, K, -1.0, X, bnd.ld, X, bnd.ld, 1.0, S, lds, true, wa, wb))
+      dgemm(s, false, true, act, act, K, -1.0, X, bnd.ld, X, bnd.ld, 1.0, S, lds, true);
   }
-  dgemm(s, false, true, nb, nb, n_fac, -1.0, Lbi, lda, Lbi, lda, 1.0, A + n_fac * lda + n_fac, lda, true);
+  RPF_HIP(hipStreamSynchronize(s));  // the copies are freed on return
 }
 
 // Panel triangular solve for many right-hand sides: one workgroup owns PW = 16 H columns of B and

@@ -1053,7 +1053,7 @@ void ensure_coarse(rpf_problem pb, const rpf_pattern* pats, hipStream_t s) {
   DevBuf<double> dinv((size_t)cdiv(nG, NB) * NB * NB);
   DevBuf<int> st(1);
   RPF_HIP(hipMemsetAsync(st.p, 0, sizeof(int), s));
-  potrf(s, GtG.p, nG, nG, nG, env, dinv.p, st.p);
+  potrf(s, GtG.p, nG, nG, env, dinv.p, st.p);
   pb->Ginv.alloc((size_t)nG * nG);
   potri_lower(s, GtG.p, nG, nG, dinv.p, pb->Ginv.p, nG);
   mirror_lower(s, pb->Ginv.p, nG, nG);
@@ -1492,7 +1492,7 @@ void ensure_coarse_M(rpf_problem pb, const rpf_pattern* pats, int kind, hipStrea
   RPF_LAUNCH_CHECK();
   RPF_HIP(hipMemsetAsync(st.p, 0, sizeof(int), s));
   const Envelope env = Envelope::dense(nG);
-  potrf(s, H.p, nG, nG, nG, env, dinv.p, st.p);
+  potrf(s, H.p, nG, nG, env, dinv.p, st.p);
   hipLaunchKernelGGL(k_get_diag, dim3((unsigned)cdiv(nG, 256)), dim3(256), 0, s, nG, H.p, (int64_t)nG, dg.p + nG);
   RPF_LAUNCH_CHECK();
   pb->Hinv.alloc((size_t)nG * nG);

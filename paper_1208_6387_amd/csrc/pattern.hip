@@ -18,15 +18,27 @@ namespace {
 
 constexpr int KDET = 8;  // block size of the kernel detection (kernel dimension <= KDET - 1)
 
-__global__ void k_scatter_csr(int n, const int* rowptr, const int* colind, const double* val, const int* pos,
-                              double* L, int64_t ld) {
+// lower triangle of the reordered K: interior block, boundary rows (below it) and boundary block
+__global__ void k_scatter_csr(int n, int n_i, const int* rowptr, const int* colind, const double* val, const int* pos,
+                              double* Lii, int64_t ldi, double* Lbi, int64_t ldb, double* S, int64_t lds) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const int pi = pos[i];
   for (int e = rowptr[i]; e < rowptr[i + 1]; ++e) {
     const int pj = pos[colind[e]];
-    if (pi >= pj) L[(int64_t)pj * ld + pi] = val[e];
+    if (pi < pj) continue;
+    if (pi < n_i) Lii[(int64_t)pj * ldi + pi] = val[e];
+    else if (pj < n_i) Lbi[(int64_t)pj * ldb + (pi - n_i)] = val[e];
+    else S[(int64_t)(pj - n_i) * lds + (pi - n_i)] = val[e];
   }
+}
+
+// S (full) from the lower triangle of its reordered form: S(r, c) = Sp(ord[r], ord[c])
+__global__ void k_unsort(int64_t n, const int* ord, const double* Sp, double* S) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n * n) return;
+  const int64_t a = ord[i % n], b = ord[i / n];
+  S[i] = Sp[min(a, b) * n + max(a, b)];
 }
 
 __global__ void k_gather_vals(int64_t count, const int* src, const double* val, double* out) {
@@ -204,12 +216,45 @@ extern "C" rpf_status pattern_factor(int32_t n, const int32_t* rowptr, const int
     DevBuf<int> d_rowptr, d_colind, d_pos, d_src;
     d_rowptr.upload(rowptr, n + 1, s);
     d_colind.upload(colind, nnz, s);
+    // boundary rows sorted by the first interior column that they reach, and how many reach each block
+    std::vector<int> bfirst(n_b, n_i), ord(n_b), at(n_b);
+    for (int b = 0; b < n_b; ++b)
+      for (int e = kbi_ptr[b]; e < kbi_ptr[b + 1]; ++e) bfirst[b] = std::min(bfirst[b], kbi_col[e]);
+    for (int b = 0; b < n_b; ++b) at[b] = b;
+    std::stable_sort(at.begin(), at.end(), [&](int x, int y) { return bfirst[x] < bfirst[y]; });
+    bool sorted = true;
+    for (int b = 0; b < n_b; ++b) {
+      ord[at[b]] = b;
+      sorted = sorted && at[b] == b;
+    }
+    BoundaryRows bnd;
+    bnd.n = n_b;
+    bnd.ld = n_b + (n_b & 1);
+    bnd.active.assign(nblk, 0);
+    for (int64_t t = 0, a = 0; t < nblk; ++t) {
+      while (a < n_b && bfirst[at[a]] < (t + 1) * NB) ++a;
+      bnd.active[t] = a;
+    }
+    for (int b = 0; b < n_b; ++b) pos[bdofs[b]] = n_i + ord[b];
+    // interior factor: in a band where that is smaller (TRI_BW: the widest block read as a rectangle)
+    int64_t hw = TRI_BW;
+    for (int64_t t = 0; t < nblk; ++t) hw = std::max(hw, P->env_ii.rend[t] - t * NB + TRI_BW);
+    const bool band = 2 * hw - 1 < n_i;
+    P->ld = band ? 2 * hw - 1 : n_i;
+    P->l_off = band ? hw : 0;
+    const int64_t llen = P->ld * n_i + (band ? 2 * hw : 0);
     d_pos.upload(pos.data(), n, s);
-    P->ld = n;
-    P->L.alloc((size_t)n * n);
-    fill(s, P->L.p, (int64_t)n * n, 0.0);
-    hipLaunchKernelGGL(k_scatter_csr, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, n, d_rowptr.p, d_colind.p, val,
-                       d_pos.p, P->L.p, P->ld);
+    P->L.alloc((size_t)llen);
+    fill(s, P->L.p, llen, 0.0);
+    DevBuf<double> Lbi((size_t)bnd.ld * n_i), Sp;
+    bnd.p = Lbi.p;
+    fill(s, Lbi.p, bnd.ld * n_i, 0.0);
+    P->S.alloc((size_t)n_b * n_b);
+    if (!sorted) Sp.alloc((size_t)n_b * n_b);
+    double* Sw = sorted ? P->S.p : Sp.p;
+    fill(s, Sw, (int64_t)n_b * n_b, 0.0);
+    hipLaunchKernelGGL(k_scatter_csr, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, n, n_i, d_rowptr.p, d_colind.p, val,
+                       d_pos.p, P->Lii(), P->ld, Lbi.p, bnd.ld, Sw, (int64_t)n_b);
     RPF_LAUNCH_CHECK();
     auto upload_csr = [&](DevBuf<int>& dptr, DevBuf<int>& dcol, DevBuf<double>& dval, const std::vector<int>& hp,
                           const std::vector<int>& hc, const std::vector<int>& hs) {
@@ -232,16 +277,23 @@ extern "C" rpf_status pattern_factor(int32_t n, const int32_t* rowptr, const int
 
     if (n_i > 0) {
       P->dinv_ii.alloc((size_t)nblk * NB * NB);
-      potrf(s, P->L.p, P->ld, n, n_i, P->env_ii, P->dinv_ii.p, P->status.p);
-      build_tri_inv(s, P->L.p, P->ld, n_i, P->dinv_ii.p, P->inv_ii);
-      schur_update(s, P->L.p, P->ld, n, n_i);
+      potrf(s, P->Lii(), P->ld, n_i, P->env_ii, P->dinv_ii.p, P->status.p, bnd);
+      build_tri_inv(s, P->Lii(), P->ld, n_i, P->dinv_ii.p, P->inv_ii);
+      schur_update(s, Sw, n_b, n_i, bnd);
       // L_ii^T in the (otherwise unused) upper triangle: the backward solves read it row-contiguous
-      mirror_envelope(s, P->L.p, P->ld, n_i, P->env_ii);
+      mirror_envelope(s, P->Lii(), P->ld, n_i, P->env_ii);
       P->L_upper = true;
     }
-    P->S.alloc((size_t)n_b * n_b);
-    copy_matrix(s, P->L.p + (int64_t)n_i * P->ld + n_i, P->ld, P->S.p, n_b, n_b, n_b);
-    mirror_lower(s, P->S.p, n_b, n_b);
+    if (sorted) {
+      mirror_lower(s, P->S.p, n_b, n_b);
+    } else {
+      DevBuf<int> d_ord;
+      d_ord.upload(ord.data(), n_b, s);
+      hipLaunchKernelGGL(k_unsort, dim3((unsigned)cdiv((int64_t)n_b * n_b, 256)), dim3(256), 0, s, (int64_t)n_b, d_ord.p,
+                         Sp.p, P->S.p);
+      RPF_LAUNCH_CHECK();
+      RPF_HIP(hipStreamSynchronize(s));  // the order is freed here
+    }
     check_status(s, P->status.p, "pattern_factor (interior stiffness K_ii)");
 
     // ---- kernel detection: shifted block inverse iteration + Rayleigh-Ritz
@@ -259,7 +311,7 @@ extern "C" rpf_status pattern_factor(int32_t n, const int32_t* rowptr, const int
         W((size_t)n_b * kb), H(kb * kb), U(kb * kb), theta(kb);
     add_outer(s, n_b, P->S.p, n_b, 0, nullptr, 0.0, sigma, C.p, n_b, false);
     const Envelope envC = Envelope::dense(n_b);
-    potrf(s, C.p, n_b, n_b, n_b, envC, dinvC.p, P->status.p);
+    potrf(s, C.p, n_b, n_b, envC, dinvC.p, P->status.p);
     TriInv invC;
     build_tri_inv(s, C.p, n_b, n_b, dinvC.p, invC);
     check_status(s, P->status.p, "pattern_factor (Schur complement S + sigma I)");
@@ -310,7 +362,7 @@ extern "C" rpf_status pattern_condense(rpf_pattern p, int32_t prec, void* stream
       add_outer(s, nb, p->S.p, nb, p->k, p->Z.p, 1.0, 0.0, M.p, nb, false);
       const Envelope env = Envelope::dense(nb);
       RPF_HIP(hipMemsetAsync(p->status.p, 0, sizeof(int), s));
-      potrf(s, M.p, nb, nb, nb, env, dinv.p, p->status.p);
+      potrf(s, M.p, nb, nb, env, dinv.p, p->status.p);
       p->Splus.alloc((size_t)nb * nb);
       potri_lower(s, M.p, nb, nb, dinv.p, p->Splus.p, nb);
       add_outer(s, nb, p->Splus.p, nb, p->k, p->Z.p, -1.0, 0.0, p->Splus.p, nb, true);
@@ -390,7 +442,7 @@ extern "C" rpf_status rpf_dposv(int64_t n, double* A, int64_t lda, int64_t nrhs,
     DevBuf<int> st(1);
     RPF_HIP(hipMemsetAsync(st.p, 0, sizeof(int), s));
     const Envelope env = Envelope::dense(n);
-    potrf(s, A, lda, n, n, env, dinv.p, st.p);
+    potrf(s, A, lda, n, env, dinv.p, st.p);
     if (nrhs > 0) {
       TriInv inv;
       build_tri_inv(s, A, lda, n, dinv.p, inv);
