@@ -98,6 +98,11 @@ rpf_status guarded(F&& f) {
 }
 
 // ----------------------------------------------------------------------------- device memory
+// Device memory for DevBuf on the current device (nullptr on failure); large released blocks are kept, up
+// to a bound, for later allocations.
+void* dev_alloc(size_t bytes);
+void dev_free(void* p);
+
 template <class T>
 struct DevBuf {
   T* p = nullptr;
@@ -115,17 +120,14 @@ struct DevBuf {
   void alloc(size_t count) {
     release();
     if (count == 0) return;
-    hipError_t e = hipMalloc((void**)&p, count * sizeof(T));
-    if (e != hipSuccess) {
-      p = nullptr;
-      throw Error(RPF_ENOMEM, "hipMalloc of " + std::to_string(count * sizeof(T)) + " bytes failed");
-    }
+    p = (T*)dev_alloc(count * sizeof(T));
+    if (!p) throw Error(RPF_ENOMEM, "hipMalloc of " + std::to_string(count * sizeof(T)) + " bytes failed");
     n = count;
   }
   // grow-only reallocation (contents are not preserved)
   void ensure(size_t count) { if (count > n) alloc(count); }
   void release() {
-    if (p) (void)hipFree(p);
+    dev_free(p);
     p = nullptr;
     n = 0;
   }
