@@ -251,6 +251,9 @@ struct TriInv {
   DevBuf<double> lo, up;
 };
 void build_tri_inv(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double* dinv, TriInv& inv);
+// C (M x c, column-major) = beta C + alpha op(A) X with few columns c, op(A) M x K (A stored K x M when ta)
+void few_columns(hipStream_t s, bool ta, int64_t M, int64_t c, int64_t K, double alpha, const double* A, int64_t lda,
+                 const double* X, int64_t ldx, double beta, double* C, int64_t ldc);
 // B <- (L L^T)^{-1} B, L = leading n x n of a factor with its inverted NB blocks (dinv, see potrf) and
 // TRI_BW blocks (inv).
 // upper: the strict upper triangle of L's envelope holds L^T (mirror_envelope has run on it), so the

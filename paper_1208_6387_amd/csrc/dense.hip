@@ -2435,9 +2435,9 @@ __global__ __launch_bounds__(256) void k_skinny(int64_t M, int64_t c, int64_t K,
   }
 }
 
-// up to this many columns k_skinny is the faster one (64 x 64 tiles re-read less of A above)
+// C = beta C + alpha op(A) X for a few columns: up to this many k_skinny is the faster one (64 x 64 tiles re-read less of A above)
 constexpr int64_t SKINNY = 96;
-static void tri_product(hipStream_t s, bool ta, int64_t M, int64_t c, int64_t K, double alpha, const double* A,
+void few_columns(hipStream_t s, bool ta, int64_t M, int64_t c, int64_t K, double alpha, const double* A,
                         int64_t lda, const double* X, int64_t ldx, double beta, double* C, int64_t ldc) {
   if (M <= 0 || c <= 0 || K <= 0) return;
   if (c > SKINNY) {
@@ -2492,15 +2492,15 @@ void potrs(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double*
   for (int64_t t = 0; t < nT; ++t) {
     const int64_t j0 = t * TRI_BW, jb = std::min(TRI_BW, n - j0), r0 = j0 + jb;
     const int64_t rend = std::min(env.rend[std::min((t + 1) * per, nblk) - 1], n);
-    tri_product(s, false, jb, nrhs, jb, 1.0, inv.lo.p + t * TRI_BW * TRI_BW, TRI_BW, B + j0, ldb, 0.0, F.p + j0, n);
-    tri_product(s, false, rend - r0, nrhs, jb, -1.0, L + j0 * ldl + r0, ldl, F.p + j0, n, 1.0, B + r0, ldb);
+    few_columns(s, false, jb, nrhs, jb, 1.0, inv.lo.p + t * TRI_BW * TRI_BW, TRI_BW, B + j0, ldb, 0.0, F.p + j0, n);
+    few_columns(s, false, rend - r0, nrhs, jb, -1.0, L + j0 * ldl + r0, ldl, F.p + j0, n, 1.0, B + r0, ldb);
   }
   for (int64_t t = nT - 1; t >= 0; --t) {
     const int64_t j0 = t * TRI_BW, jb = std::min(TRI_BW, n - j0);
     int64_t cs = j0;
     for (int64_t q = t * per; q < std::min((t + 1) * per, nblk); ++q) cs = std::min(cs, std::max<int64_t>(0, env.cstart[q]));
-    tri_product(s, false, jb, nrhs, jb, 1.0, inv.up.p + t * TRI_BW * TRI_BW, TRI_BW, F.p + j0, n, 0.0, B + j0, ldb);
-    tri_product(s, !upper, j0 - cs, nrhs, jb, -1.0, upper ? L + j0 * ldl + cs : L + cs * ldl + j0, ldl, B + j0, ldb, 1.0,
+    few_columns(s, false, jb, nrhs, jb, 1.0, inv.up.p + t * TRI_BW * TRI_BW, TRI_BW, F.p + j0, n, 0.0, B + j0, ldb);
+    few_columns(s, !upper, j0 - cs, nrhs, jb, -1.0, upper ? L + j0 * ldl + cs : L + cs * ldl + j0, ldl, B + j0, ldb, 1.0,
                 F.p + cs, n);
   }
   RPF_HIP(hipStreamSynchronize(s));  // the second buffer is freed on return
@@ -2808,9 +2808,103 @@ __global__ __launch_bounds__(1024) void k_mgs2(double* Y, int64_t n, int64_t ld,
   }
 }
 
+// Sums over the workgroup of v[0..7] (16 waves), to every thread.  Halving exchanges leave each lane with
+// one of the eight sums over its wave, so 13 cross-lane moves and one barrier serve all of them; the
+// caller alternates between the two buffers.
+__device__ inline void block_sum8(const double (&v)[8], double (*red)[8], double (&out)[8]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double a[4], b[2], c;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const bool hi = lane & 32;
+    a[i] = (hi ? v[i + 4] : v[i]) + __shfl_xor(hi ? v[i] : v[i + 4], 32, 64);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const bool hi = lane & 16;
+    b[i] = (hi ? a[i + 2] : a[i]) + __shfl_xor(hi ? a[i] : a[i + 2], 16, 64);
+  }
+  {
+    const bool hi = lane & 8;
+    c = (hi ? b[1] : b[0]) + __shfl_xor(hi ? b[0] : b[1], 8, 64);
+  }
+#pragma unroll
+  for (int off = 4; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
+  if ((lane & 7) == 0) red[wave][lane >> 3] = c;
+  __syncthreads();
+  double t = red[lane & 7][lane >> 3] + red[8 + (lane & 7)][lane >> 3];
+#pragma unroll
+  for (int off = 4; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) out[i] = __shfl(t, 8 * i, 64);
+}
+
+// Up to 8 columns of at most 1024 R rows in registers: classical Gram-Schmidt with every projection taken
+// twice (as orthogonal as the modified form taken twice), three reductions a column.  It is bound by
+// the reductions (24 of about 0.6 us); the general kernel below re-reads the columns for each of its
+// 64 (160 us at 2,598 rows, 74 us at 64).
+template <int R>
+__global__ __launch_bounds__(1024) void k_gs2(double* Y, int64_t n, int64_t ld, int k) {
+  __shared__ double red[2][16][8];
+  const int tid = threadIdx.x;
+  double v[8][R];
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int64_t row = tid + 1024 * r;
+      const double x = Y[(int64_t)min(j, k - 1) * ld + min(row, n - 1)];
+      v[j][r] = (j < k && row < n) ? x : 0.0;
+    }
+  int buf = 0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    if (j < k) {
+      double d[8], p[8];
+#pragma unroll
+      for (int pass = 0; pass < (j > 0 ? 2 : 0); ++pass) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          p[i] = 0.0;
+          if (i < j) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) p[i] += v[i][r] * v[j][r];
+          }
+        }
+        block_sum8(p, red[buf], d);
+        buf ^= 1;
+#pragma unroll
+        for (int i = 0; i < j; ++i)
+#pragma unroll
+          for (int r = 0; r < R; ++r) v[j][r] -= d[i] * v[i][r];
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) p[i] = 0.0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) p[0] += v[j][r] * v[j][r];
+      block_sum8(p, red[buf], d);
+      buf ^= 1;
+      const double inv = d[0] > 0.0 ? 1.0 / sqrt(d[0]) : 0.0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        v[j][r] *= inv;
+        const int64_t row = tid + 1024 * r;
+        if (row < n) Y[(int64_t)j * ld + row] = v[j][r];
+      }
+    }
+  }
+}
+
 void orthonormalize(hipStream_t s, double* Y, int64_t n, int64_t ld, int k) {
   if (k <= 0 || n <= 0) return;
-  hipLaunchKernelGGL(k_mgs2, dim3(1), dim3(1024), 0, s, Y, n, ld, k);
+  if (k <= 8 && n <= 1024)
+    hipLaunchKernelGGL(k_gs2<1>, dim3(1), dim3(1024), 0, s, Y, n, ld, k);
+  else if (k <= 8 && n <= 2048)
+    hipLaunchKernelGGL(k_gs2<2>, dim3(1), dim3(1024), 0, s, Y, n, ld, k);
+  else if (k <= 8 && n <= 4096)
+    hipLaunchKernelGGL(k_gs2<4>, dim3(1), dim3(1024), 0, s, Y, n, ld, k);
+  else
+    hipLaunchKernelGGL(k_mgs2, dim3(1), dim3(1024), 0, s, Y, n, ld, k);
   RPF_LAUNCH_CHECK();
 }
 

@@ -323,8 +323,8 @@ extern "C" rpf_status pattern_factor(int32_t n, const int32_t* rowptr, const int
       potrs(s, C.p, n_b, n_b, dinvC.p, invC, envC, V.p, n_b, kb);
       orthonormalize(s, V.p, n_b, n_b, kb);
     }
-    dgemm(s, false, false, n_b, kb, n_b, 1.0, P->S.p, n_b, V.p, n_b, 0.0, W.p, n_b);
-    dgemm(s, true, false, kb, kb, n_b, 1.0, V.p, n_b, W.p, n_b, 0.0, H.p, kb);
+    few_columns(s, false, n_b, kb, n_b, 1.0, P->S.p, n_b, V.p, n_b, 0.0, W.p, n_b);
+    few_columns(s, true, kb, kb, n_b, 1.0, V.p, n_b, W.p, n_b, 0.0, H.p, kb);
     syev_small(s, H.p, kb, U.p, theta.p, 1);
     std::vector<double> th(kb), hU(kb * kb);
     RPF_HIP(hipMemcpyAsync(th.data(), theta.p, kb * sizeof(double), hipMemcpyDeviceToHost, s));
@@ -342,7 +342,7 @@ extern "C" rpf_status pattern_factor(int32_t n, const int32_t* rowptr, const int
     P->k = k;
     if (k > 0) {
       P->Z.alloc((size_t)n_b * k);
-      dgemm(s, false, false, n_b, k, kb, 1.0, V.p, n_b, U.p, kb, 0.0, P->Z.p, n_b);
+      few_columns(s, false, n_b, k, kb, 1.0, V.p, n_b, U.p, kb, 0.0, P->Z.p, n_b);
       orthonormalize(s, P->Z.p, n_b, n_b, k);
     }
     RPF_HIP(hipStreamSynchronize(s));
