@@ -3,7 +3,7 @@
 // applied to all occurrences of a pattern as one product S+ W (section 3.2),
 // and the coarse projector Q = I - G (G^T G)^{-1} G^T with G = [A^(s) Z] and
 // the identity preconditioner (section 2, projector and initialisation).
-#include "problem.hpp"
+#include "scatter.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -67,60 +67,6 @@ __global__ __launch_bounds__(128) void k_gather(int nbn, const int* occ_list, co
 #pragma unroll
         for (int c = 0; c < DPN; ++c) col[c] = acc[c][j];
       }
-    }
-  }
-}
-
-// A^(s): Y[(mult*DPN + c)*ldy + j] = beta Y + sum over endpoints of sign * (O Y_loc)[c]
-template <int DPN>
-__global__ __launch_bounds__(128) void k_scatter(int n_mult, const int* ep_q, const int* ep_bn,
-                                                 const int8_t* ep_pat, const int8_t* ep_sign, const int* ep_occ,
-                                                 const double* rot, YLoc yl, int m, double* Y, int64_t ldy,
-                                                 double beta) {
-  const int mult = blockIdx.x * blockDim.x + threadIdx.x;
-  if (mult >= n_mult) return;
-  for (int j0 = 0; j0 < m; j0 += JB) {
-    const int jn = min(JB, m - j0);
-    double acc[DPN][JB];
-#pragma unroll
-    for (int c = 0; c < DPN; ++c)
-#pragma unroll
-      for (int j = 0; j < JB; ++j) acc[c][j] = 0.0;
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int q = ep_q[2 * mult + e];
-      if (q < 0) continue;
-      const int p = ep_pat[2 * mult + e];
-      const double sg = (double)ep_sign[2 * mult + e];
-      const int64_t ld = yl.ld[p], slab = yl.slab[p];
-      const int nsp = yl.nsplit[p];
-      const double* base = yl.base[p] + ((int64_t)q * m + j0) * ld + (int64_t)ep_bn[2 * mult + e] * DPN;
-      double O[9];
-      if (DPN == 3) load_rot<DPN>(rot, ep_occ[2 * mult + e], O);
-#pragma unroll
-      for (int j = 0; j < JB; ++j) {
-        if (j >= jn) break;
-        double v[DPN];
-#pragma unroll
-        for (int c = 0; c < DPN; ++c) v[c] = base[j * ld + c];
-        for (int z = 1; z < nsp; ++z)
-#pragma unroll
-          for (int c = 0; c < DPN; ++c) v[c] += base[z * slab + j * ld + c];
-        if (DPN == 3) {
-#pragma unroll
-          for (int c = 0; c < 3; ++c) acc[c][j] += sg * (O[3 * c] * v[0] + O[3 * c + 1] * v[1 % DPN] + O[3 * c + 2] * v[2 % DPN]);
-        } else {
-#pragma unroll
-          for (int c = 0; c < DPN; ++c) acc[c][j] += sg * v[c];
-        }
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < DPN; ++c) {
-      double* row = Y + ((int64_t)mult * DPN + c) * ldy + j0;
-#pragma unroll
-      for (int j = 0; j < JB; ++j)
-        if (j < jn) row[j] = (beta == 0.0) ? acc[c][j] : acc[c][j] + beta * row[j];
     }
   }
 }
@@ -756,18 +702,7 @@ void scatter_all(rpf_problem pb, const YLoc& yl, int m, double* Y, int64_t ldy, 
     wscatter(pb, w, m, Y, ldy, s);
     return;
   }
-  dim3 grid((unsigned)cdiv(pb->n_mult, 128));
-  const double* rot = pb->has_rot ? pb->d_rot.p : nullptr;
-#define RPF_SCATTER(D)                                                                                        \
-  hipLaunchKernelGGL(k_scatter<D>, grid, dim3(128), 0, s, pb->n_mult, pb->d_ep_q.p, pb->d_ep_bn.p,             \
-                     pb->d_ep_pat.p, pb->d_ep_sign.p, pb->d_ep_occ.p, rot, yl, m, Y, ldy, beta)
-  switch (pb->dpn) {
-    case 1: RPF_SCATTER(1); break;
-    case 2: RPF_SCATTER(2); break;
-    default: RPF_SCATTER(3);
-  }
-#undef RPF_SCATTER
-  RPF_LAUNCH_CHECK();
+  launch_scatter_cols(pb, yl, m, Y, ldy, beta, s);
 }
 
 Schedule schedule_for(rpf_problem pb, int m, int prec) {

@@ -3,7 +3,7 @@
 // operands (v_mfma_f32_16x16x32_bf16, three cross products hi*hi + hi*lo + lo*hi),
 // FP32 accumulation in both cases.  The gather writes the W format directly in
 // the low-precision layout and the scatter reads FP32 and assembles in FP64.
-#include "problem.hpp"
+#include "scatter.hpp"
 
 namespace rpf {
 
@@ -641,84 +641,8 @@ struct YLoc32 {
   int64_t slab[MAXP];
   int nsplit[MAXP];
   int rowmajor[MAXP];
+  __device__ bool by_rows(int p) const { return rowmajor[p] != 0; }
 };
-
-// JB columns per pass (8: the whole pass stays in registers)
-template <int DPN, int JB>
-__global__ __launch_bounds__(128) void k_scatter_f32(int n_mult, const int* ep_q, const int* ep_bn,
-                                                     const int8_t* ep_pat, const int8_t* ep_sign, const int* ep_occ,
-                                                     const double* rot, YLoc32 yl, int m, double* Y, int64_t ldy) {
-  const int mult = blockIdx.x * blockDim.x + threadIdx.x;
-  if (mult >= n_mult) return;
-  for (int j0 = 0; j0 < m; j0 += JB) {
-    const int jn = min(JB, m - j0);
-    double acc[DPN][JB];
-#pragma unroll
-    for (int c = 0; c < DPN; ++c)
-#pragma unroll
-      for (int j = 0; j < JB; ++j) acc[c][j] = 0.0;
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int q = ep_q[2 * mult + e];
-      if (q < 0) continue;
-      const int p = ep_pat[2 * mult + e];
-      const double sg = (double)ep_sign[2 * mult + e];
-      const int64_t ld = yl.ld[p];
-      const bool rm = yl.rowmajor[p] != 0;
-      const int64_t bn = ep_bn[2 * mult + e];
-      const float* base = rm ? yl.base[p] + bn * DPN * ld + (int64_t)q * m + j0
-                             : yl.base[p] + ((int64_t)q * m + j0) * ld + bn * DPN;
-      // element (c, j) of this endpoint: base[c sc + j sj]
-      const int64_t sc = rm ? ld : 1, sj = rm ? 1 : ld;
-      double O[9];
-      const int s = ep_occ[2 * mult + e];
-#pragma unroll
-      for (int i = 0; i < 9; ++i) O[i] = rot ? rot[9 * s + i] : ((i % 4 == 0) ? 1.0 : 0.0);
-      // row-major with whole, 16-byte aligned groups: JB / 4 vector loads per dof
-      float yv[DPN][JB];
-      if (rm && jn == JB && (m & 3) == 0) {
-#pragma unroll
-        for (int c = 0; c < DPN; ++c)
-#pragma unroll
-          for (int v4 = 0; v4 < JB / 4; ++v4) {
-            const f32x4 t = *reinterpret_cast<const f32x4*>(base + c * ld + 4 * v4);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) yv[c][4 * v4 + u] = t[u];
-          }
-      } else {
-#pragma unroll
-        for (int c = 0; c < DPN; ++c)
-#pragma unroll
-          for (int j = 0; j < JB; ++j) yv[c][j] = j < jn ? base[c * sc + j * sj] : 0.f;
-      }
-#pragma unroll
-      for (int j = 0; j < JB; ++j) {
-        if (j >= jn) break;
-        double v[DPN];
-#pragma unroll
-        for (int c = 0; c < DPN; ++c) v[c] = (double)yv[c][j];
-        for (int z = 1; z < yl.nsplit[p]; ++z)
-#pragma unroll
-          for (int c = 0; c < DPN; ++c) v[c] += (double)base[z * yl.slab[p] + c * sc + j * sj];
-        if (DPN == 3) {
-#pragma unroll
-          for (int c = 0; c < 3; ++c)
-            acc[c % DPN][j] += sg * (O[3 * c] * v[0] + O[3 * c + 1] * v[1 % DPN] + O[3 * c + 2] * v[2 % DPN]);
-        } else {
-#pragma unroll
-          for (int c = 0; c < DPN; ++c) acc[c][j] += sg * v[c];
-        }
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < DPN; ++c) {
-      double* row = Y + ((int64_t)mult * DPN + c) * ldy + j0;
-#pragma unroll
-      for (int j = 0; j < JB; ++j)
-        if (j < jn) row[j] = acc[c][j];
-    }
-  }
-}
 
 // Scatter from the row-major result of the 256 x 256 kernel with one thread per (multiplier, 4
 // consecutive columns): per endpoint one 16-byte load per dof row, the output rows leave as
@@ -1022,7 +946,6 @@ void apply_F_lowprec(rpf_problem pb, const rpf_pattern* pats, int m, const doubl
     wscatter(pb, w, m, Y, ldy, s);
     return;
   }
-  dim3 grid((unsigned)cdiv(pb->n_mult, 128));
   const double* rot = pb->has_rot ? pb->d_rot.p : nullptr;
   bool all_rm = true;
   for (int p = 0; p < pb->n_pat; ++p) all_rm &= yl.rowmajor[p] != 0 || pb->occ_of_pat[p].empty();
@@ -1040,16 +963,7 @@ void apply_F_lowprec(rpf_problem pb, const rpf_pattern* pats, int m, const doubl
     RPF_LAUNCH_CHECK();
     return;
   }
-#define RPF_SF(D, JB)                                                                                          \
-  hipLaunchKernelGGL((k_scatter_f32<D, JB>), grid, dim3(128), 0, s, pb->n_mult, pb->d_ep_q.p, pb->d_ep_bn.p,    \
-                     pb->d_ep_pat.p, pb->d_ep_sign.p, pb->d_ep_occ.p, rot, yl, m, Y, ldy)
-  switch (pb->dpn) {
-    case 1: RPF_SF(1, 8); break;
-    case 2: RPF_SF(2, 8); break;
-    default: RPF_SF(3, 8);
-  }
-#undef RPF_SF
-  RPF_LAUNCH_CHECK();
+  launch_scatter_cols(pb, yl, m, Y, ldy, 0.0, s);
 }
 
 }  // namespace rpf

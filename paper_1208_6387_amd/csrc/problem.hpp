@@ -17,6 +17,7 @@ struct YLoc {
   int64_t ld[MAXP];
   int64_t slab[MAXP];
   int nsplit[MAXP];
+  __device__ bool by_rows(int) const { return false; }
 };
 // Every pattern's flexibility product in one persistent launch: per pattern its operands and
 // shape, its tile grid (tm x tn tiles of the kernel's size, K split into pieces of kchunk) and the
