@@ -203,13 +203,14 @@ bool dgemm_flex(hipStream_t s, int64_t M, int64_t N, int64_t K, double alpha, co
 // M1 and M2 column-major with a rows.  Returns false (nothing launched) for other shapes.
 bool rows_orth_lam(hipStream_t s, int64_t N, int a, int b, int c, const double* X, int64_t ldx, const double* M1,
                    const double* R, int64_t ldr, double* Z, int64_t ldz, const double* M2, double* Lam, int64_t ldl);
-// Y = beta Y + alpha X M (a, b <= 16, b divides 256), and from the same pass: sq[c * ldsq] = the
-// squared column norms of the new Y (skipped when sq is NULL) and G (a x b, column-major) =
-// X^T Y_new.  sqpart and gpart are workspaces of (cdiv(N, 256) + 256) * b and
-// (cdiv(N, 256) + 256) * a * b doubles.  Returns false (nothing launched) when the shape is not supported.
+// Y = beta Y + alpha X M (N x a, a = b <= 16), and from the same pass what the next block step starts from:
+// sq[c * ldsq] = the squared column norms of the new Y (skipped when sq is NULL), C = X^T Y_new,
+// Bo = T^T C (its diagonal only with diag) and Mo = T Bo, a x a column-major.  part: a workspace of
+// update_gram_workspace doubles.  Returns false (nothing launched) when the shape is not supported.
+size_t update_gram_workspace(int64_t N, int a, int b);
 bool rows_update_gram(hipStream_t s, int64_t N, int a, int b, const double* M, const double* X, int64_t ldx,
-                      double alpha, double beta, double* Y, int64_t ldy, double* sqpart, double* sq, int64_t ldsq,
-                      double* gpart, double* G);
+                      double alpha, double beta, double* Y, int64_t ldy, double* sq, int64_t ldsq, double* part,
+                      const double* T, bool diag, double* Bo, double* Mo);
 bool rows_gemm2_sq(hipStream_t s, int64_t N, int a, int b, const double* M, double alpha1, const double* X1,
                    int64_t ldx1, double beta1, double* Y1, int64_t ldy1, double alpha2, const double* X2,
                    int64_t ldx2, double beta2, double* Y2, int64_t ldy2, double* part, double* sq, int64_t ldsq);
@@ -281,10 +282,11 @@ void add_outer(hipStream_t s, int64_t n, const double* A, int64_t lda, int k, co
 // Symmetric eigen-decomposition of small m x m matrices (m <= 64), one
 // workgroup each: A (m x m, ld m, column-major) -> V (columns), w ascending.
 void syev_small(hipStream_t s, const double* A, int m, double* V, double* w, int batch = 1);
-// Block-solver normalisation T = V diag(w^{-1/2}) over the kept eigenpairs of eta (w_i > tau *
-// max(w_max, state[1])), skipped when state[0] != 0; drops counted, flag0/flag1 set when none kept.
-void eta_eigen_T(hipStream_t s, const double* eta, int m, const double* state, double tau, double* T, int* drops,
-                 double* flag0, double* flag1);
+// Small matrices of a block step: the normalisation T (m x m) of a block from eta and alpha = T (T^T zr)
+// (m x nr) to alpha and, unless NULL, alpha2; see k_block_coef.
+void block_coef(hipStream_t s, int m, int nr, const double* eta, const double* zr, bool diag_only, int ka,
+                const double* B, double tau, double* T, int* drops, double* flag0, double* flag1, double* alpha,
+                double* alpha2);
 
 // Orthonormalise the k columns of Y (n x k, ld) in place (modified Gram-Schmidt, twice).
 void orthonormalize(hipStream_t s, double* Y, int64_t n, int64_t ld, int k);

@@ -1176,40 +1176,28 @@ __global__ __launch_bounds__(256) void k_rows_tile(int64_t N, int a, int b, cons
 // MFMA over its 64 rows) and the four waves are summed in LDS.
 __global__ __launch_bounds__(256) void k_rows_update_gram(int64_t N, int a, int b, const double* Mm,
                                                           const double* X, int64_t ldx, double alpha, double beta,
-                                                          double* Y, int64_t ldy, double* sqpart, double* gpart) {
+                                                          double* Y, int64_t ldy, double* part) {
   __shared__ double sm[16][16];
   __shared__ double xs[256][17];
   __shared__ double ys[256][17];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  {
-    const int i = tid >> 4, j = tid & 15;
-    sm[i][j] = (i < a && j < b) ? Mm[i + (int64_t)a * j] : 0.0;
-  }
-  double myq = 0.0;
+  const int er = tid >> 4, ec = tid & 15;  // element (er + 16 u, ec) of the tile in pass u
   const int64_t r0 = (int64_t)blockIdx.x * 256;
   const int rows = (int)min<int64_t>(256, N - r0);
-  // whole tile of 16 columns: Y's old values are loaded together with X (one memory latency
-  // instead of two in a row)
-  const bool pre = rows == 256 && a == 16 && b == 16 && beta != 0.0;
+  // every load of the tile at clamped (always valid) addresses, in flight together, masked afterwards
   double zv[16];
-  if (rows == 256 && a == 16) {
+  {
     double t[16];
+    const double mv = Mm[min(er, a - 1) + (int64_t)a * min(ec, b - 1)];
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
-      const int e = tid + u * 256;
-      t[u] = X[(r0 + (e >> 4)) * ldx + (e & 15)];
-      if (pre) zv[u] = Y[(r0 + (e >> 4)) * ldy + (e & 15)];
+      const int64_t row = r0 + min(er + 16 * u, rows - 1);
+      t[u] = X[row * ldx + min(ec, a - 1)];
+      if (beta != 0.0) zv[u] = Y[row * ldy + min(ec, b - 1)];
     }
+    sm[er][ec] = (er < a && ec < b) ? mv : 0.0;
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = tid + u * 256;
-      xs[e >> 4][e & 15] = t[u];
-    }
-  } else {
-    for (int e = tid; e < 256 * 16; e += 256) {
-      const int rr = e >> 4, cc = e & 15;
-      xs[rr][cc] = (rr < rows && cc < a) ? X[(r0 + rr) * ldx + cc] : 0.0;
-    }
+    for (int u = 0; u < 16; ++u) xs[er + 16 * u][ec] = (er + 16 * u < rows && ec < a) ? t[u] : 0.0;
   }
   __syncthreads();
   {
@@ -1226,38 +1214,16 @@ __global__ __launch_bounds__(256) void k_rows_update_gram(int64_t N, int a, int 
     for (int j = 0; j < 16; ++j) ys[tid][j] = acc[j];
   }
   __syncthreads();
-  if (rows == 256 && b == 16) {
-    if (beta != 0.0 && !pre) {
+  double myq = 0.0;
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int e = tid + u * 256;
-        zv[u] = Y[(r0 + (e >> 4)) * ldy + (e & 15)];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = tid + u * 256;
-      const double v = alpha * ys[e >> 4][e & 15];
-      const double out = (beta == 0.0) ? v : beta * zv[u] + v;
-      Y[(r0 + (e >> 4)) * ldy + (e & 15)] = out;
-      ys[e >> 4][e & 15] = out;
-      myq += out * out;
-    }
-  } else {
-    for (int e = tid; e < 256 * b; e += 256) {
-      const int rr = e / b, cc = e - rr * b;
-      double out = 0.0;  // rows past N count as zero in the Gram
-      if (rr < rows) {
-        double* y = Y + (r0 + rr) * ldy + cc;
-        const double v = alpha * ys[rr][cc];
-        out = (beta == 0.0) ? v : beta * *y + v;
-        *y = out;
-      }
-      ys[rr][cc] = out;
-      myq += out * out;
-    }
-    for (int e = tid; e < 256 * 16; e += 256)
-      if ((e & 15) >= b) ys[e >> 4][e & 15] = 0.0;
+  for (int u = 0; u < 16; ++u) {
+    const int rr = er + 16 * u;
+    const double v = alpha * ys[rr][ec];
+    const bool in = rr < rows && ec < b;  // the rest counts as zero in the Gram
+    const double out = in ? ((beta == 0.0) ? v : beta * zv[u] + v) : 0.0;
+    if (in) Y[(r0 + rr) * ldy + ec] = out;
+    ys[rr][ec] = out;
+    myq += out * out;
   }
   __syncthreads();
   // Gram partial over this tile's rows: wave w takes rows 64 w .. 64 w + 63
@@ -1274,16 +1240,14 @@ __global__ __launch_bounds__(256) void k_rows_update_gram(int64_t N, int a, int 
   for (int r = 0; r < 4; ++r) red[wave * 256 + ((lane >> 4) + 4 * r) * 16 + (lane & 15)] = g[r];
   red[1024 + tid] = myq;
   __syncthreads();
-  {
-    const int i = tid >> 4, j = tid & 15;
-    if (i < a && j < b)
-      gpart[((int64_t)blockIdx.x * b + j) * a + i] = red[tid] + red[256 + tid] + red[512 + tid] + red[768 + tid];
-  }
-  // every element a thread wrote lies in column tid % b (b divides 256)
+  // record: the Gram (a x b, column-major), then the squared norms of the b columns
+  double* rec = part + (int64_t)blockIdx.x * (a * b + b);
+  if (er < a && ec < b) rec[ec * a + er] = red[tid] + red[256 + tid] + red[512 + tid] + red[768 + tid];
   if (tid < b) {
     double t = 0.0;
-    for (int k = tid; k < 256; k += b) t += red[1024 + k];
-    sqpart[(int64_t)blockIdx.x * b + tid] = t;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) t += red[1024 + tid + 16 * k];
+    rec[a * b + tid] = t;
   }
 }
 
@@ -1497,48 +1461,67 @@ bool rows_gemm2_sq(hipStream_t s, int64_t N, int a, int b, const double* M, doub
   return true;
 }
 
-// Sum of nrec records of len <= 256 doubles (record r at part[r * len]): workgroup g sums the
-// records g per .. g per + per - 1 with thread t on element t (coalesced) and writes element t
-// to out[g * rstride + t * inc].  record_sum runs it over groups of records, then sums the groups
-// with k_recsum_final; the order of every sum is fixed (deterministic).
-__global__ __launch_bounds__(256) void k_recsum(int nrec, int len, int per, const double* part, double* out,
-                                                int64_t rstride, int64_t inc) {
+// Sums groups of `per` of the nrec records of len doubles (record r at part[r len]): workgroup g the
+// records g per .. g per + per - 1, thread t element t, eight loads in flight, in a fixed order.
+__global__ __launch_bounds__(320) void k_recsum(int nrec, int len, int per, const double* part, double* out) {
   const int t = threadIdx.x;
   if (t >= len) return;
   const int r0 = blockIdx.x * per, r1 = min(nrec, r0 + per);
-  double v0 = 0.0, v1 = 0.0, v2 = 0.0, v3 = 0.0;
-  int r = r0;
-  for (; r + 4 <= r1; r += 4) {
-    v0 += part[(int64_t)r * len + t];
-    v1 += part[(int64_t)(r + 1) * len + t];
-    v2 += part[(int64_t)(r + 2) * len + t];
-    v3 += part[(int64_t)(r + 3) * len + t];
+  double v[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) v[u] = 0.0;
+  for (int r = r0; r < r1; r += 8) {
+    double x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = part[(int64_t)min(r + u, r1 - 1) * len + t];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (r + u < r1) v[u] += x[u];
   }
-  for (; r < r1; ++r) v0 += part[(int64_t)r * len + t];
-  out[(int64_t)blockIdx.x * rstride + t * inc] = (v0 + v1) + (v2 + v3);
+  out[(int64_t)blockIdx.x * len + t] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
 }
 
-// Final pass: one wavefront per element (lane l sums the records l, l + 64, ..., then a fixed
-// butterfly across the lanes), so the records' loads of an element are all in flight together.
-__global__ __launch_bounds__(256) void k_recsum_final(int nrec, int len, const double* part, double* out,
-                                                      int64_t inc) {
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (t >= len) return;
+// The records of rows_update_gram (n of them left) to what the next block step starts from, in one
+// workgroup: C = P^T R (m x m) and the squared norms (to sq, stride ldsq, unless NULL), then B = T^T C
+// (its diagonal only with diag) and M = T B.
+__global__ __launch_bounds__(1024) void k_recsum_coef(int n, int m, const double* rec, const double* T, int diag,
+                                                      double* sq, int64_t ldsq, double* B, double* M) {
+  __shared__ double c[16 * 17], st[256], sb[256];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int len = m * m + m;
+  if (tid < m * m) st[tid] = T[tid];
+  // wave w sums the elements w, w + 16, ..: lane l the records l, l + 64, then across the lanes
+  for (int e0 = wave; e0 < len; e0 += 64) {
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int e = min(e0 + 16 * u, len - 1);
+      v[u] = 0.0;
+      for (int r = lane; r < n; r += 64) v[u] += rec[(int64_t)r * len + e];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) v[u] += __shfl_xor(v[u], off, 64);
+      if (lane == 0 && e0 + 16 * u < len) c[e0 + 16 * u] = v[u];
+    }
+  }
+  __syncthreads();
+  if (sq && tid < m) sq[tid * ldsq] = c[m * m + tid];
+  const int r = tid % m, col = tid / m;
   double v = 0.0;
-  for (int r = lane; r < nrec; r += 64) v += part[(int64_t)r * len + t];
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  if (lane == 0) out[t * inc] = v;
-}
-
-// out[t * inc] = sum of the nrec records; tmp holds 256 records
-void record_sum(hipStream_t s, int nrec, int len, const double* part, double* tmp, double* out, int64_t inc) {
-  const int groups = std::min(256, std::max(1, nrec));
-  const int per = (int)cdiv(nrec, groups);
-  const int g = (int)cdiv(nrec, per);
-  hipLaunchKernelGGL(k_recsum, dim3((unsigned)g), dim3(256), 0, s, nrec, len, per, part, tmp, (int64_t)len,
-                     (int64_t)1);
-  hipLaunchKernelGGL(k_recsum_final, dim3((unsigned)cdiv(len, 4)), dim3(256), 0, s, g, len, tmp, out, inc);
-  RPF_LAUNCH_CHECK();
+  if (tid < m * m && (!diag || r == col))
+    for (int k = 0; k < m; ++k) v += st[k + r * m] * c[k + col * m];
+  if (tid < m * m) {
+    sb[tid] = v;
+    B[tid] = v;
+  }
+  __syncthreads();
+  if (tid < m * m) {
+    v = 0.0;
+    for (int k = 0; k < m; ++k) v += st[r + k * m] * sb[k + col * m];
+    M[tid] = v;
+  }
 }
 
 bool rows_orth_lam(hipStream_t s, int64_t N, int a, int b, int c, const double* X, int64_t ldx, const double* M1,
@@ -1550,17 +1533,28 @@ bool rows_orth_lam(hipStream_t s, int64_t N, int a, int b, int c, const double* 
   return true;
 }
 
+constexpr int UPD_GROUPS = 64;  // records left for the last, single workgroup
+size_t update_gram_workspace(int64_t N, int a, int b) { return (size_t)(cdiv(N, 256) + UPD_GROUPS) * (a * b + b); }
+
 bool rows_update_gram(hipStream_t s, int64_t N, int a, int b, const double* M, const double* X, int64_t ldx,
-                      double alpha, double beta, double* Y, int64_t ldy, double* sqpart, double* sq, int64_t ldsq,
-                      double* gpart, double* G) {
-  if (N <= 0 || a <= 0 || b <= 0 || a > 16 || b > 16 || 256 % b != 0) return false;
-  const int nwg = (int)cdiv(N, 256);
+                      double alpha, double beta, double* Y, int64_t ldy, double* sq, int64_t ldsq, double* part,
+                      const double* T, bool diag, double* Bo, double* Mo) {
+  if (N <= 0 || a <= 0 || a > 16 || b != a) return false;
+  const int nwg = (int)cdiv(N, 256), len = a * b + b;
   hipLaunchKernelGGL(k_rows_update_gram, dim3((unsigned)nwg), dim3(256), 0, s, N, a, b, M, X, ldx, alpha, beta, Y,
-                     ldy, sqpart, gpart);
+                     ldy, part);
   RPF_LAUNCH_CHECK();
-  // the first-pass sums go past the partials (the workspaces hold 256 records more)
-  if (sq) record_sum(s, nwg, b, sqpart, sqpart + (int64_t)nwg * b, sq, ldsq);
-  record_sum(s, nwg, a * b, gpart, gpart + (int64_t)nwg * a * b, G, 1);
+  const double* rec = part;
+  int n = nwg;
+  if (nwg > UPD_GROUPS) {
+    const int per = (int)cdiv(nwg, UPD_GROUPS);
+    n = (int)cdiv(nwg, per);
+    double* tmp = part + (int64_t)nwg * len;
+    hipLaunchKernelGGL(k_recsum, dim3((unsigned)n), dim3(320), 0, s, nwg, len, per, part, tmp);
+    rec = tmp;
+  }
+  hipLaunchKernelGGL(k_recsum_coef, dim3(1), dim3(1024), 0, s, n, a, rec, T, diag ? 1 : 0, sq, ldsq, Bo, Mo);
+  RPF_LAUNCH_CHECK();
   return true;
 }
 
@@ -2604,35 +2598,17 @@ void mirror_lower(hipStream_t s, double* A, int64_t lda, int64_t n) {
 // m-1 steps per sweep), one workgroup per matrix, m <= 64.
 constexpr int EIG_MAX = 64;
 
-// TMODE: the matrix is eta of the block solver and the kernel writes T = V diag(w^{-1/2}) over the
-// kept eigenpairs (w_i > tau * max(w_max, state[1]); the others are counted in *drops and, when
-// none is kept, 1 is written to flag0 and flag1); it returns at once when state[0] != 0 (T was
-// already formed from a Cholesky factor of eta).
-template <bool TMODE>
-__global__ __launch_bounds__(256) void k_syev_jacobi(const double* Ain, int m, double* Vout, double* wout,
-                                                     const double* state, double tau, double* T, int* drops,
-                                                     double* flag0, double* flag1) {
-  if (TMODE && state[0] != 0.0) return;
-  __shared__ double a[EIG_MAX][EIG_MAX + 1];
-  __shared__ double v[EIG_MAX][EIG_MAX + 1];
-  __shared__ int pp[EIG_MAX / 2], qq[EIG_MAX / 2];
-  __shared__ double cc[EIG_MAX / 2], ss[EIG_MAX / 2];
-
-  __shared__ int order[EIG_MAX];
-  const int tid = threadIdx.x;
-  const double* A = Ain + (int64_t)blockIdx.x * m * m;
-  double* V = Vout + (int64_t)blockIdx.x * m * m;
-  double* w = wout + (int64_t)blockIdx.x * m;
-  const int nth = blockDim.x;
-  for (int i = tid; i < m * m; i += nth) {
-    const int r = i % m, c = i / m;
-    a[r][c] = 0.5 * (A[c * m + r] + A[r * m + c]);
-    v[r][c] = (r == c) ? 1.0 : 0.0;
-  }
+struct JacobiShared {
+  int pp[EIG_MAX / 2], qq[EIG_MAX / 2], order[EIG_MAX], nrot;
+  double cc[EIG_MAX / 2], ss[EIG_MAX / 2], floor_abs;
+};
+// Eigenpairs of the symmetric m x m matrix a (row stride ld, LDS), by every thread of the workgroup:
+// the eigenvalues are left on its diagonal, the vectors in the columns of v (the identity on entry),
+// their ascending order in sh.order.
+__device__ void jacobi_eigen(double* a, double* v, int ld, int m, JacobiShared& sh) {
+  const int tid = threadIdx.x, nth = blockDim.x;
   const int me = m + (m & 1);  // even count for the round-robin schedule
   const int npair = me / 2;
-  __shared__ int nrot;
-  __shared__ double floor_abs;
   __syncthreads();
   // threshold Jacobi: a pair is rotated only while |a_pq| > 1e-13 sqrt(|a_pp a_qq|) (relative
   // accuracy of the eigenvalues to about 1e-13, ample for eta^{-1/2}) and |a_pq| > 1e-15
@@ -2641,10 +2617,10 @@ __global__ __launch_bounds__(256) void k_syev_jacobi(const double* Ain, int m, d
   // sweep rotates nothing
   for (int sweep = 0; sweep < 30 && m >= 2; ++sweep) {
     if (tid == 0) {
-      nrot = 0;
+      sh.nrot = 0;
       double d = 0.0;
-      for (int i = 0; i < m; ++i) d = fmax(d, fabs(a[i][i]));
-      floor_abs = fmax(1e-15 * d, 1e-300);
+      for (int i = 0; i < m; ++i) d = fmax(d, fabs(a[(i) * ld + (i)]));
+      sh.floor_abs = fmax(1e-15 * d, 1e-300);
     }
     __syncthreads();
     for (int step = 0; step < me - 1; ++step) {
@@ -2661,109 +2637,342 @@ __global__ __launch_bounds__(256) void k_syev_jacobi(const double* Ain, int m, d
         const int p = i < j ? i : j, q = i < j ? j : i;
         double c = 1.0, sn = 0.0;
         if (q < m) {
-          const double apq = a[p][q];
-          if (fabs(apq) > 1e-13 * sqrt(fabs(a[p][p] * a[q][q])) && fabs(apq) > floor_abs) {
-            atomicAdd(&nrot, 1);
-            const double theta = (a[q][q] - a[p][p]) / (2.0 * apq);
+          const double apq = a[(p) * ld + (q)];
+          if (fabs(apq) > 1e-13 * sqrt(fabs(a[(p) * ld + (p)] * a[(q) * ld + (q)])) && fabs(apq) > sh.floor_abs) {
+            atomicAdd(&sh.nrot, 1);
+            const double theta = (a[(q) * ld + (q)] - a[(p) * ld + (p)]) / (2.0 * apq);
             const double t = (theta >= 0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(1.0 + theta * theta));
             c = 1.0 / sqrt(1.0 + t * t);
             sn = t * c;
           }
         }
-        pp[tid] = p;
-        qq[tid] = q;
-        cc[tid] = c;
-        ss[tid] = sn;
+        sh.pp[tid] = p;
+        sh.qq[tid] = q;
+        sh.cc[tid] = c;
+        sh.ss[tid] = sn;
       }
       __syncthreads();
       // columns: A <- A J, V <- V J
       for (int idx = tid; idx < npair * m; idx += nth) {
         const int k = idx / m, r = idx % m;
-        const int p = pp[k], q = qq[k];
+        const int p = sh.pp[k], q = sh.qq[k];
         if (q >= m) continue;
-        const double c = cc[k], sn = ss[k];
-        const double x = a[r][p], y = a[r][q];
-        a[r][p] = c * x - sn * y;
-        a[r][q] = sn * x + c * y;
-        const double vx = v[r][p], vy = v[r][q];
-        v[r][p] = c * vx - sn * vy;
-        v[r][q] = sn * vx + c * vy;
+        const double c = sh.cc[k], sn = sh.ss[k];
+        const double x = a[(r) * ld + (p)], y = a[(r) * ld + (q)];
+        a[(r) * ld + (p)] = c * x - sn * y;
+        a[(r) * ld + (q)] = sn * x + c * y;
+        const double vx = v[(r) * ld + (p)], vy = v[(r) * ld + (q)];
+        v[(r) * ld + (p)] = c * vx - sn * vy;
+        v[(r) * ld + (q)] = sn * vx + c * vy;
       }
       __syncthreads();
       // rows: A <- J^T A
       for (int idx = tid; idx < npair * m; idx += nth) {
         const int k = idx / m, col = idx % m;
-        const int p = pp[k], q = qq[k];
+        const int p = sh.pp[k], q = sh.qq[k];
         if (q >= m) continue;
-        const double c = cc[k], sn = ss[k];
-        const double x = a[p][col], y = a[q][col];
-        a[p][col] = c * x - sn * y;
-        a[q][col] = sn * x + c * y;
+        const double c = sh.cc[k], sn = sh.ss[k];
+        const double x = a[(p) * ld + (col)], y = a[(q) * ld + (col)];
+        a[(p) * ld + (col)] = c * x - sn * y;
+        a[(q) * ld + (col)] = sn * x + c * y;
       }
       __syncthreads();
     }
-    if (nrot == 0) break;  // uniform: read after the last barrier of the sweep
+    if (sh.nrot == 0) break;  // uniform: read after the last barrier of the sweep
     __syncthreads();
   }
   __syncthreads();
   if (tid == 0) {
-    for (int i = 0; i < m; ++i) order[i] = i;
+    for (int i = 0; i < m; ++i) sh.order[i] = i;
     for (int i = 0; i < m; ++i) {
       int best = i;
       for (int j = i + 1; j < m; ++j)
-        if (a[order[j]][order[j]] < a[order[best]][order[best]]) best = j;
-      const int t = order[i];
-      order[i] = order[best];
-      order[best] = t;
+        if (a[(sh.order[j]) * ld + (sh.order[j])] < a[(sh.order[best]) * ld + (sh.order[best])]) best = j;
+      const int t = sh.order[i];
+      sh.order[i] = sh.order[best];
+      sh.order[best] = t;
     }
   }
   __syncthreads();
-  if (!TMODE) {
-    for (int i = tid; i < m * m; i += nth) {
-      const int r = i % m, c = i / m;
-      V[c * m + r] = v[r][order[c]];
-    }
-    for (int i = tid; i < m; i += nth) w[i] = a[order[i]][order[i]];
-  } else {
-    __shared__ double scale[EIG_MAX];
-    __shared__ int kept;
-    if (tid == 0) kept = 0;
-    __syncthreads();
-    const double ref = fmax(a[order[m - 1]][order[m - 1]], state[1]);
-    if (tid < m) {
-      const double wi = a[order[tid]][order[tid]];
-      const bool keep = wi > 0.0 && wi > tau * ref;
-      scale[tid] = keep ? 1.0 / sqrt(wi) : 0.0;
-      if (keep) atomicAdd(&kept, 1);
-      else atomicAdd(drops, 1);
-    }
-    __syncthreads();
-    if (tid == 0 && kept == 0) {
-      flag0[0] = 1.0;
-      flag1[0] = 1.0;
-    }
-    for (int i = tid; i < m * m; i += nth) {
-      const int r = i % m, c = i / m;
-      T[c * m + r] = v[r][order[c]] * scale[c];
-    }
+}
+
+__global__ __launch_bounds__(256) void k_syev_jacobi(const double* Ain, int m, double* Vout, double* wout) {
+  __shared__ double a[EIG_MAX * (EIG_MAX + 1)];
+  __shared__ double v[EIG_MAX * (EIG_MAX + 1)];
+  __shared__ JacobiShared sh;
+  const int ld = EIG_MAX + 1;
+  const double* A = Ain + (int64_t)blockIdx.x * m * m;
+  double* V = Vout + (int64_t)blockIdx.x * m * m;
+  double* w = wout + (int64_t)blockIdx.x * m;
+  for (int i = threadIdx.x; i < m * m; i += blockDim.x) {
+    const int r = i % m, c = i / m;
+    a[r * ld + c] = 0.5 * (A[c * m + r] + A[r * m + c]);
+    v[r * ld + c] = (r == c) ? 1.0 : 0.0;
   }
+  jacobi_eigen(a, v, ld, m, sh);
+  for (int i = threadIdx.x; i < m * m; i += blockDim.x) {
+    const int r = i % m, c = i / m;
+    V[c * m + r] = v[r * ld + sh.order[c]];
+  }
+  for (int i = threadIdx.x; i < m; i += blockDim.x) w[i] = a[sh.order[i] * (ld + 1)];
 }
 
 void syev_small(hipStream_t s, const double* A, int m, double* V, double* w, int batch) {
   RPF_CHECK(m >= 1 && m <= EIG_MAX, RPF_EINVAL, "syev_small: m out of range");
   // one wavefront is enough (and its barriers are cheapest) while m/2 * m <= 128 work items
   const int threads = (m <= 16) ? 64 : 256;
-  hipLaunchKernelGGL(k_syev_jacobi<false>, dim3(batch), dim3(threads), 0, s, A, m, V, w, (const double*)nullptr, 0.0,
-                     (double*)nullptr, (int*)nullptr, (double*)nullptr, (double*)nullptr);
+  hipLaunchKernelGGL(k_syev_jacobi, dim3(batch), dim3(threads), 0, s, A, m, V, w);
   RPF_LAUNCH_CHECK();
 }
 
-void eta_eigen_T(hipStream_t s, const double* eta, int m, const double* state, double tau, double* T, int* drops,
-                 double* flag0, double* flag1) {
-  RPF_CHECK(m >= 1 && m <= EIG_MAX, RPF_EINVAL, "eta_eigen_T: m out of range");
-  const int threads = (m <= 16) ? 64 : 256;
-  hipLaunchKernelGGL(k_syev_jacobi<true>, dim3(1), dim3(threads), 0, s, eta, m, (double*)nullptr, (double*)nullptr,
-                     state, tau, T, drops, flag0, flag1);
+// LDS written by one lane of a wavefront, read by others of it
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// The small matrices of a block step, in one workgroup.  Normalisation of the new block (section 3.3): T
+// with T^T eta T = I on the kept directions.
+// The energy of column c before the orthogonalisation is |B_c|^2 + eta_cc (B = P_stored^T Z,
+// ka x m, ld ka; F-orthonormal stored blocks).  Diagonal form (classical CG per load case):
+// T = diag(eta_cc^{-1/2}) keeping eta_cc > tau * energy_c.  Block form: the eigen rule keeps w_i >
+// tau * max(w_max, max_c energy_c); when a Cholesky factor eta = L L^T exists with
+// 1 / |L^{-1}|_F^2 (a lower bound of w_min) above tau * max(trace eta, max_c energy_c) (an upper
+// bound of that reference), no eigenpair would be dropped and T = L^{-T} spans the same
+// directions, so it is used; otherwise T = V diag(w^{-1/2}) over the kept eigenpairs.  When nothing is
+// kept, 1 goes to flag0 and flag1.  Then alpha = T (T^T zr) (m x nr; the diagonal of T^T zr only in the
+// diagonal form), to one or two places.  MM >= m is the unrolled register length; the first wave forms
+// T, the four of them the eigenpairs and the products (as separate launches, these took 4.5 us each).
+template <int MM>
+__global__ __launch_bounds__(256) void k_block_coef(int m, int nr, const double* eta, const double* zr, int diag_only,
+                                                    int ka, const double* B, double tau, double* T, int* drops,
+                                                    double* flag0, double* flag1, double* alpha, double* alpha2) {
+  __shared__ double epre[64];
+  __shared__ double Ls[MM][MM + 1];  // the factor; the Jacobi iteration's matrix
+  __shared__ double Vs[MM][MM + 1];  // its vectors; T^T zr
+  __shared__ double es[MM * MM];     // eta; T
+  __shared__ double zs[MM * MM];
+  __shared__ double rdiag[MM];
+  __shared__ JacobiShared sh;
+  __shared__ double emax_s, trace_s;
+  __shared__ int bad_s, ok_s, kept_s;
+  const int tid = threadIdx.x, t = tid & 63, wave = tid >> 6;
+  for (int e = tid; e < m * nr; e += 256) zs[e] = zr[e];
+  if (wave == 0) {
+  // eta staged in LDS, and B read, by loads at clamped (always valid) addresses whose values are
+  // masked afterwards: no load sits behind a branch, so each group is issued together and waited
+  // for once instead of one global-memory round trip at a time
+  {
+    constexpr int EU = (MM * MM + 63) / 64;
+    double ev[EU];
+    const int mm = m * m;
+#pragma unroll
+    for (int u = 0; u < EU; ++u) ev[u] = eta[min(t + 64 * u, mm - 1)];
+#pragma unroll
+    for (int u = 0; u < EU; ++u)
+      if (t + 64 * u < MM * MM) es[t + 64 * u] = (t + 64 * u < mm) ? ev[u] : 0.0;
+  }
+  wave_sync();
+  {
+    // squared column norms of B: every column's loads of a 64-row chunk are issued together
+    double part[MM];
+#pragma unroll
+    for (int c = 0; c < MM; ++c) part[c] = 0.0;
+    for (int i0 = 0; i0 < ka; i0 += 64) {
+      const int i = i0 + t;
+      const int ic = min(i, ka - 1);
+      double bv[MM];
+#pragma unroll
+      for (int c = 0; c < MM; ++c) bv[c] = B[(int64_t)min(c, m - 1) * ka + ic];
+#pragma unroll
+      for (int c = 0; c < MM; ++c) {
+        const double b = (c < m && i < ka) ? bv[c] : 0.0;
+        part[c] += b * b;
+      }
+    }
+    // lane t holds eta_tt; every reduction below is a butterfly across the wave (no serial loops
+    // of dependent loads on one lane)
+    const double dg = t < m ? es[t * m + t] : 0.0;
+    // all MM butterflies in straight-line code (columns past m are zeros), so they interleave
+    double mine = 0.0;
+#pragma unroll
+    for (int c = 0; c < MM; ++c) {
+      double acc = part[c];
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+      acc += __shfl(dg, c, 64);
+      if (t == c) mine = acc;
+    }
+    if (t < m) epre[t] = mine;
+    double me = mine, tr = fmax(dg, 0.0);
+    for (int off = 32; off > 0; off >>= 1) {
+      me = fmax(me, __shfl_xor(me, off, 64));
+      tr += __shfl_xor(tr, off, 64);
+    }
+    if (t == 0) {
+      emax_s = me;
+      trace_s = tr;
+      bad_s = 0;
+    }
+  }
+  wave_sync();
+  if (diag_only) {
+    bool keep = false;
+    if (t < m) {
+      const double wi = es[t * m + t];
+      keep = wi > 0.0 && wi > tau * epre[t];
+      if (!keep) atomicAdd(drops, 1);
+    }
+    const bool any = __any(keep);
+    const double tc = keep ? 1.0 / sqrt(es[t * m + t]) : 0.0;
+    wave_sync();
+    for (int i = t; i < m * m; i += 64) {
+      es[i] = 0.0;
+      T[i] = 0.0;
+    }
+    wave_sync();
+    if (t < m) {
+      es[t * m + t] = tc;
+      T[t * m + t] = tc;
+    }
+    if (t == 0) {
+      if (!any) {
+        flag0[0] = 1.0;
+        flag1[0] = 1.0;
+      }
+      ok_s = 1;
+    }
+  } else {
+  // Cholesky, lane t owns row t
+  double a[MM];
+#pragma unroll
+  for (int c = 0; c < MM; ++c) a[c] = (t < m && c < m && c <= t) ? 0.5 * (es[c * m + t] + es[t * m + c]) : 0.0;
+  // (fully unrolled with compile-time indices into a[]: a loop left with a runtime bound would index
+  // the register array dynamically; the column of L is read from LDS in one independent batch)
+#pragma unroll
+  for (int j = 0; j < MM; ++j) {
+    if (j < m) {
+      if (t == j) {
+        double d = a[j];
+        if (!(d > 0.0)) {
+          bad_s = 1;
+          d = 1.0;
+        }
+        a[j] = sqrt(d);
+        rdiag[j] = 1.0 / a[j];
+      }
+      wave_sync();
+      if (t > j && t < m) {
+        a[j] *= rdiag[j];
+        Ls[t][j] = a[j];
+      }
+      wave_sync();
+      double lc[MM];
+#pragma unroll
+      for (int c = j + 1; c < MM; ++c) lc[c] = Ls[c][j];
+      if (t > j && t < m) {
+        const double ltj = a[j];
+#pragma unroll
+        for (int c = j + 1; c < MM; ++c)
+          if (c <= t) a[c] -= ltj * lc[c];
+      }
+    }
+  }
+  wave_sync();
+  // column t of L^{-1}, right-looking
+  double x[MM];
+#pragma unroll
+  for (int r = 0; r < MM; ++r) x[r] = (r == t) ? 1.0 : 0.0;
+#pragma unroll
+  for (int k = 0; k < MM; ++k) {
+    if (k < m) {
+      x[k] *= rdiag[k];
+      const double xk = x[k];
+#pragma unroll
+      for (int r = k + 1; r < MM; ++r)
+        if (r < m) x[r] -= Ls[r][k] * xk;
+    }
+  }
+  double fro = 0.0;
+#pragma unroll
+  for (int r = 0; r < MM; ++r) fro += (t < m && r < m) ? x[r] * x[r] : 0.0;
+  for (int off = 32; off > 0; off >>= 1) fro += __shfl_xor(fro, off, 64);
+  const double ref_up = fmax(trace_s, emax_s);
+  const bool ok = bad_s == 0 && fro > 0.0 && (1.0 / fro) > tau * ref_up;
+  if (ok && t < m) {
+    // T = L^{-T}: T[c + m r] = (L^{-1})[r][c] = x[r] of lane c
+#pragma unroll
+    for (int r = 0; r < MM; ++r)
+      if (r < m) {
+        T[t + (int64_t)m * r] = x[r];
+        es[t + m * r] = x[r];
+      }
+  }
+  if (t == 0) ok_s = ok ? 1 : 0;
+  }
+  }
+  __syncthreads();
+  if (!ok_s) {
+    // the factor did not settle it: eigenpairs of eta
+    for (int i = tid; i < m * m; i += 256) {
+      const int r = i % m, c = i / m;
+      Ls[r][c] = 0.5 * (eta[c * m + r] + eta[r * m + c]);
+      Vs[r][c] = (r == c) ? 1.0 : 0.0;
+    }
+    if (tid == 0) kept_s = 0;
+    jacobi_eigen(&Ls[0][0], &Vs[0][0], MM + 1, m, sh);
+    const double ref = fmax(Ls[sh.order[m - 1]][sh.order[m - 1]], emax_s);
+    if (tid < m) {
+      const double wi = Ls[sh.order[tid]][sh.order[tid]];
+      const bool keep = wi > 0.0 && wi > tau * ref;
+      rdiag[tid] = keep ? 1.0 / sqrt(wi) : 0.0;
+      if (keep) atomicAdd(&kept_s, 1);
+      else atomicAdd(drops, 1);
+    }
+    __syncthreads();
+    if (tid == 0 && kept_s == 0) {
+      flag0[0] = 1.0;
+      flag1[0] = 1.0;
+    }
+    for (int i = tid; i < m * m; i += 256) {
+      const int r = i % m, c = i / m;
+      const double v = Vs[r][sh.order[c]] * rdiag[c];
+      T[c * m + r] = v;
+      es[c * m + r] = v;
+    }
+    __syncthreads();
+  }
+  double* gs = &Vs[0][0];
+  for (int e = tid; e < m * nr; e += 256) {
+    const int r = e % m, col = e / m;
+    double v = 0.0;
+    if (!diag_only || r == col)
+      for (int k = 0; k < m; ++k) v += es[k + r * m] * zs[k + col * m];
+    gs[e] = v;
+  }
+  __syncthreads();
+  for (int e = tid; e < m * nr; e += 256) {
+    const int r = e % m, col = e / m;
+    double v = 0.0;
+    for (int k = 0; k < m; ++k) v += es[r + k * m] * gs[k + col * m];
+    alpha[e] = v;
+    if (alpha2) alpha2[e] = v;
+  }
+}
+
+void block_coef(hipStream_t s, int m, int nr, const double* eta, const double* zr, bool diag_only, int ka,
+                const double* B, double tau, double* T, int* drops, double* flag0, double* flag1, double* alpha,
+                double* alpha2) {
+  RPF_CHECK(m >= 1 && m <= EIG_MAX && nr <= m, RPF_EINVAL, "block_coef: block width");
+#define RPF_BC(MM)                                                                                                   \
+  hipLaunchKernelGGL(k_block_coef<MM>, dim3(1), dim3(256), 0, s, m, nr, eta, zr, diag_only ? 1 : 0, ka, B, tau, T, drops, \
+                     flag0, flag1, alpha, alpha2)
+  if (m <= 8) RPF_BC(8);
+  else if (m <= 16) RPF_BC(16);
+  else if (m <= 32) RPF_BC(32);
+  else RPF_BC(64);
+#undef RPF_BC
   RPF_LAUNCH_CHECK();
 }
 

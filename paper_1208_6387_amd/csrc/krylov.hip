@@ -62,189 +62,33 @@ __global__ void k_permute(int64_t n_lambda, int dpn, int n_mult, int nr, int np,
   }
 }
 
-// Normalisation of a new block (section 3.3): T with T^T eta T = I on the kept directions.
-// The energy of column c before the orthogonalisation is |B_c|^2 + eta_cc (B = P_stored^T Z,
-// ka x m, ld ka; F-orthonormal stored blocks).  Diagonal form (classical CG per load case):
-// T = diag(eta_cc^{-1/2}) keeping eta_cc > tau * energy_c.  Block form: the eigen rule keeps w_i >
-// tau * max(w_max, max_c energy_c); when a Cholesky factor eta = L L^T exists with
-// 1 / |L^{-1}|_F^2 (a lower bound of w_min) above tau * max(trace eta, max_c energy_c) (an upper
-// bound of that reference), no eigenpair would be dropped and T = L^{-T} spans the same
-// directions, so it is used and state[0] = 1; otherwise state[0] = 0, state[1] = max_c energy_c
-// and the eigen form (eta_eigen_T) decides.  When nothing is kept, 1 goes to flag0 and flag1.
-// One wavefront; MM >= m is the unrolled register length.
-template <int MM>
-__global__ __launch_bounds__(64) void k_eta_chol(int m, const double* eta, int diag_only, int ka, const double* B,
-                                                 double tau, double* T, int* drops, double* flag0, double* flag1,
-                                                 double* state) {
-  __shared__ double epre[64];
-  __shared__ double Ls[MM][MM + 1];
-  __shared__ double es[MM * MM];
-  __shared__ double rdiag[MM];
-  __shared__ double emax_s, trace_s;
-  __shared__ int bad_s;
-  const int t = threadIdx.x;
-  // eta staged in LDS, and B read, by loads at clamped (always valid) addresses whose values are
-  // masked afterwards: no load sits behind a branch, so each group is issued together and waited
-  // for once instead of one global-memory round trip at a time
-  {
-    constexpr int EU = (MM * MM + 63) / 64;
-    double ev[EU];
-    const int mm = m * m;
-#pragma unroll
-    for (int u = 0; u < EU; ++u) ev[u] = eta[min(t + 64 * u, mm - 1)];
-#pragma unroll
-    for (int u = 0; u < EU; ++u)
-      if (t + 64 * u < MM * MM) es[t + 64 * u] = (t + 64 * u < mm) ? ev[u] : 0.0;
-  }
-  __syncthreads();
-  {
-    // squared column norms of B: every column's loads of a 64-row chunk are issued together
-    double part[MM];
-#pragma unroll
-    for (int c = 0; c < MM; ++c) part[c] = 0.0;
-    for (int i0 = 0; i0 < ka; i0 += 64) {
-      const int i = i0 + t;
-      const int ic = min(i, ka - 1);
-      double bv[MM];
-#pragma unroll
-      for (int c = 0; c < MM; ++c) bv[c] = B[(int64_t)min(c, m - 1) * ka + ic];
-#pragma unroll
-      for (int c = 0; c < MM; ++c) {
-        const double b = (c < m && i < ka) ? bv[c] : 0.0;
-        part[c] += b * b;
-      }
-    }
-    // lane t holds eta_tt; every reduction below is a butterfly across the wave (no serial loops
-    // of dependent loads on one lane)
-    const double dg = t < m ? es[t * m + t] : 0.0;
-    // all MM butterflies in straight-line code (columns past m are zeros), so they interleave
-    double mine = 0.0;
-#pragma unroll
-    for (int c = 0; c < MM; ++c) {
-      double acc = part[c];
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-      acc += __shfl(dg, c, 64);
-      if (t == c) mine = acc;
-    }
-    if (t < m) epre[t] = mine;
-    double me = mine, tr = fmax(dg, 0.0);
-    for (int off = 32; off > 0; off >>= 1) {
-      me = fmax(me, __shfl_xor(me, off, 64));
-      tr += __shfl_xor(tr, off, 64);
-    }
-    if (t == 0) {
-      emax_s = me;
-      trace_s = tr;
-      bad_s = 0;
-    }
-  }
-  __syncthreads();
-  if (diag_only) {
-    bool keep = false;
-    if (t < m) {
-      const double wi = es[t * m + t];
-      keep = wi > 0.0 && wi > tau * epre[t];
-      if (!keep) atomicAdd(drops, 1);
-    }
-    const bool any = __any(keep);
-    for (int i = t; i < m * m; i += 64) {
-      const int r = i % m, c = i / m;
-      const double wc = es[c * m + c];
-      T[i] = (r == c && wc > 0.0 && wc > tau * epre[c]) ? 1.0 / sqrt(wc) : 0.0;
-    }
-    if (t == 0) {
-      if (!any) {
-        flag0[0] = 1.0;
-        flag1[0] = 1.0;
-      }
-      state[0] = 1.0;
-    }
-    return;
-  }
-  // Cholesky, lane t owns row t
-  double a[MM];
-#pragma unroll
-  for (int c = 0; c < MM; ++c) a[c] = (t < m && c < m && c <= t) ? 0.5 * (es[c * m + t] + es[t * m + c]) : 0.0;
-  // (fully unrolled with compile-time indices into a[]: a loop left with a runtime bound would index
-  // the register array dynamically; the column of L is read from LDS in one independent batch)
-#pragma unroll
-  for (int j = 0; j < MM; ++j) {
-    if (j < m) {
-      if (t == j) {
-        double d = a[j];
-        if (!(d > 0.0)) {
-          bad_s = 1;
-          d = 1.0;
-        }
-        a[j] = sqrt(d);
-        rdiag[j] = 1.0 / a[j];
-      }
-      __syncthreads();
-      if (t > j && t < m) {
-        a[j] *= rdiag[j];
-        Ls[t][j] = a[j];
-      }
-      __syncthreads();
-      double lc[MM];
-#pragma unroll
-      for (int c = j + 1; c < MM; ++c) lc[c] = Ls[c][j];
-      if (t > j && t < m) {
-        const double ltj = a[j];
-#pragma unroll
-        for (int c = j + 1; c < MM; ++c)
-          if (c <= t) a[c] -= ltj * lc[c];
-      }
-    }
-  }
-  __syncthreads();
-  // column t of L^{-1}, right-looking
-  double x[MM];
-#pragma unroll
-  for (int r = 0; r < MM; ++r) x[r] = (r == t) ? 1.0 : 0.0;
-#pragma unroll
-  for (int k = 0; k < MM; ++k) {
-    if (k < m) {
-      x[k] *= rdiag[k];
-      const double xk = x[k];
-#pragma unroll
-      for (int r = k + 1; r < MM; ++r)
-        if (r < m) x[r] -= Ls[r][k] * xk;
-    }
-  }
-  double fro = 0.0;
-#pragma unroll
-  for (int r = 0; r < MM; ++r) fro += (t < m && r < m) ? x[r] * x[r] : 0.0;
-  for (int off = 32; off > 0; off >>= 1) fro += __shfl_xor(fro, off, 64);
-  const double ref_up = fmax(trace_s, emax_s);
-  const bool ok = bad_s == 0 && fro > 0.0 && (1.0 / fro) > tau * ref_up;
-  if (ok) {
-    // T = L^{-T}: T[c + m r] = (L^{-1})[r][c] = x[r] of lane c
-    if (t < m) {
-#pragma unroll
-      for (int r = 0; r < MM; ++r)
-        if (r < m) T[t + (int64_t)m * r] = x[r];
-    }
-  }
-  if (t == 0) {
-    state[0] = ok ? 1.0 : 0.0;
-    state[1] = emax_s;
-  }
-}
-
-// Y_i = op(T_i) X_i for nb blocks: T_i is m x m column-major at Ts + i m m (op = transpose when
-// trans), X and Y are (nb m) x c column-major with ld nb m.  One workgroup per block.
-__global__ __launch_bounds__(256) void k_tblocks(int nb, int m, int c, const double* Ts, int trans, const double* X,
-                                                 double* Y) {
+// For nb blocks i, column-major: B_i = T_i^T C_i and M_i = T_i B_i, T_i m x m at Ts + i m m; C, B and M
+// are (nb m) x m with ld nb m.  diag: B_i keeps its diagonal only.  One workgroup per block, B_i through LDS.
+__global__ __launch_bounds__(256) void k_tblocks(int nb, int m, const double* Ts, int diag, const double* C, double* B,
+                                                 double* M) {
+  extern __shared__ double sh[];  // T_i and C_i, then B_i in place of C_i
+  double *st = sh, *sc = sh + m * m, *sb = sh + 2 * m * m;
   const int i = blockIdx.x;
   const int64_t ld = (int64_t)nb * m;
-  const double* Ti = Ts + (int64_t)i * m * m;
-  for (int e = threadIdx.x; e < m * c; e += blockDim.x) {
+  for (int e = threadIdx.x; e < m * m; e += blockDim.x) {
+    st[e] = Ts[(int64_t)i * m * m + e];
+    sc[e] = C[(int64_t)(e / m) * ld + (int64_t)i * m + e % m];
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < m * m; e += blockDim.x) {
     const int r = e % m, col = e / m;
     double v = 0.0;
-    for (int k = 0; k < m; ++k)
-      v += (trans ? Ti[k + (int64_t)r * m] : Ti[r + (int64_t)k * m]) * X[(int64_t)col * ld + (int64_t)i * m + k];
-    Y[(int64_t)col * ld + (int64_t)i * m + r] = v;
+    if (!diag || r == col)
+      for (int k = 0; k < m; ++k) v += st[k + r * m] * sc[k + col * m];
+    sb[e] = v;
+    B[(int64_t)col * ld + (int64_t)i * m + r] = v;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < m * m; e += blockDim.x) {
+    const int r = e % m, col = e / m;
+    double v = 0.0;
+    for (int k = 0; k < m; ++k) v += st[r + k * m] * sb[k + col * m];
+    M[(int64_t)col * ld + (int64_t)i * m + r] = v;
   }
 }
 
@@ -257,14 +101,6 @@ __global__ void k_fill_hash(int64_t n, double* x) {
   h *= 0xBF58476D1CE4E5B9ull;
   h ^= h >> 29;
   x[i] = (double)(h >> 11) * (1.0 / 9007199254740992.0) - 0.5;
-}
-
-// keep only the diagonal of an m x n column-major matrix (ld)
-__global__ void k_mask_diag(double* A, int m, int n, int64_t ld) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= m * n) return;
-  const int r = i % m, c = i / m;
-  if (r != c) A[c * ld + r] = 0.0;
 }
 
 __global__ void k_axpby(int64_t count, double a, const double* x, double b, double* y) {
@@ -437,7 +273,7 @@ struct Solver {
   int64_t ldW = 0;
   int max_blocks = 0;
   // small matrices
-  DevBuf<double> eta, V, w, T, alpha, gam, Bt, Cb, Mo, nrm, ws, estate, sqpart, gpart, alpha_prev;
+  DevBuf<double> eta, alpha, Bt, Cb, Mo, nrm, ws, sqpart, gpart, alpha_prev;
   DevBuf<int> drops;
   std::vector<double> r0n;  // ||r0_c||^2 of the FP64 residual
   int iterations = 0, rank_drops = 0;
@@ -538,7 +374,7 @@ struct Solver {
     for (int nb = 1; nb <= top; ++nb) most = std::max(most, (size_t)gram_chunks(N, nb * m, m) * nb * m * m);
     ws.ensure(most);
     sqpart.ensure((size_t)(cdiv(N, 256) + 256) * nr);
-    if (upd_gram) gpart.ensure((size_t)(cdiv(N, 256) + 256) * m * nr);
+    if (upd_gram) gpart.ensure(update_gram_workspace(N, m, nr));
     if (np > 1 && pc != RPF_PRECOND_NONE) Zp.ensure((size_t)N * nr);
     if (np > 1 && periodic) Pz.ensure((size_t)N * nr);
   }
@@ -571,13 +407,8 @@ struct Solver {
     dlam.ensure((size_t)N * nr);
     tmp.ensure((size_t)N * std::max(nr, m));
     eta.ensure((size_t)m * (m + nr));
-    V.ensure((size_t)m * m);
-    w.ensure(m);
-    T.ensure((size_t)m * m);
     alpha.ensure((size_t)m * nr);
-    gam.ensure((size_t)m * nr);
     drops.ensure(1);
-    estate.ensure(2);
   }
 
   void alloc_store(int want_blocks) {
@@ -632,7 +463,7 @@ struct Solver {
     // which reads the same direction block (flushed when the loop ends)
     // (not with a preconditioner: the next block is then Q F~^{-1} R, not R)
     const bool upd_gram =
-        pc == RPF_PRECOND_NONE && cq == RPF_PRECOND_NONE && method != RPF_ORTHODIR && np == 1 && m <= 16 && nr <= 16 && 256 % nr == 0;
+        pc == RPF_PRECOND_NONE && cq == RPF_PRECOND_NONE && method != RPF_ORTHODIR && np == 1 && m <= 16 && nr <= 16;
     bool have_gram = false, lam_pending = false;
     const double* lam_dir = nullptr;  // the direction block of the pending update
     if (upd_gram) alpha_prev.ensure((size_t)m * nr);
@@ -700,14 +531,13 @@ struct Solver {
         // F-orthogonalise against the stored blocks: with W_i = Z_i T_i and F W_i = P_i T_i,
         // B = [F W_i]^T Z = T_i^T (P_i^T Z) and Z -= sum_i Z_i (T_i B_i)
         const int ka = nb * m;
-        if (!(fused && have_gram)) gram(Pall.p + (int64_t)first * m, ldW, ka, zsrc, ldzs, m, Cb.p);
-        hipLaunchKernelGGL(k_tblocks, dim3(nb), dim3(256), 0, s, nb, m, m, Tall.p + (int64_t)first * m * m, 1, Cb.p,
-                           Bt.p);
-        if (diag_only)
-          hipLaunchKernelGGL(k_mask_diag, dim3(nblocks((int64_t)ka * m)), dim3(256), 0, s, Bt.p, ka, m, (int64_t)ka);
-        hipLaunchKernelGGL(k_tblocks, dim3(nb), dim3(256), 0, s, nb, m, m, Tall.p + (int64_t)first * m * m, 0, Bt.p,
-                           Mo.p);
-        RPF_LAUNCH_CHECK();
+        // (block CG with one permutation: the previous step's residual update left both)
+        if (!(fused && have_gram)) {
+          gram(Pall.p + (int64_t)first * m, ldW, ka, zsrc, ldzs, m, Cb.p);
+          hipLaunchKernelGGL(k_tblocks, dim3(nb), dim3(256), 3 * m * m * sizeof(double), s, nb, m,
+                             Tall.p + (int64_t)first * m * m, diag_only ? 1 : 0, Cb.p, Bt.p, Mo.p);
+          RPF_LAUNCH_CHECK();
+        }
         if (fused && lam_pending) {
           // Z_j = R - Z_{j-1} Mo and lambda += Z_{j-1} alpha_{j-1} in one pass over Z_{j-1}
           RPF_CHECK(lam_dir == Zall.p + (int64_t)first * m, RPF_EINVAL, "block step: deferred update source");
@@ -739,43 +569,23 @@ struct Solver {
       }
       double* zr = eta.p + (int64_t)m * m;
       double* Tj = Tall.p + (int64_t)slot * m * m;
-      {
-        double* f0 = nrm2[0].p + (size_t)nr * nr;
-        double* f1 = nrm2[1].p + (size_t)nr * nr;
-        const int dg = diag_only ? 1 : 0;
-#define RPF_ETA(MM)                                                                                             \
-  hipLaunchKernelGGL(k_eta_chol<MM>, dim3(1), dim3(64), 0, s, m, eta.p, dg, nb * m, Bt.p, tau, Tj, drops.p, f0, f1, \
-                     estate.p)
-        if (m <= 8) RPF_ETA(8);
-        else if (m <= 16) RPF_ETA(16);
-        else if (m <= 32) RPF_ETA(32);
-        else RPF_ETA(64);
-#undef RPF_ETA
-        RPF_LAUNCH_CHECK();
-        if (!diag_only) eta_eigen_T(s, eta.p, m, estate.p, tau, Tj, drops.p, f0, f1);
-      }
-      // alpha = W^T R = T^T (Z^T R); gamma = T alpha; lambda += Z gamma; R -= P gamma
-      hipLaunchKernelGGL(k_tblocks, dim3(1), dim3(256), 0, s, 1, m, nr, Tj, 1, zr, gam.p);
-      if (diag_only) hipLaunchKernelGGL(k_mask_diag, dim3(nblocks((int64_t)m * nr)), dim3(256), 0, s, gam.p, m, nr, (int64_t)m);
-      hipLaunchKernelGGL(k_tblocks, dim3(1), dim3(256), 0, s, 1, m, nr, Tj, 0, gam.p, alpha.p);
-      RPF_LAUNCH_CHECK();
+      // T, and alpha = W^T R = T^T (Z^T R); gamma = T alpha; lambda += Z gamma; R -= P gamma
+      block_coef(s, m, nr, eta.p, zr, diag_only, nb * m, Bt.p, tau, Tj, drops.p, nrm2[0].p + (size_t)nr * nr,
+                 nrm2[1].p + (size_t)nr * nr, alpha.p, upd_gram ? alpha_prev.p : nullptr);
       // the residual update also returns the squared column norms (into the check slot)
-      sqpart.ensure((size_t)cdiv(N, 256) * nr);
       bool have_sq = false;
       have_gram = false;
       if (upd_gram) {
-        gpart.ensure((size_t)(cdiv(N, 256) + 256) * m * nr);
-        sqpart.ensure((size_t)(cdiv(N, 256) + 256) * nr);
-        // lambda += Z_j alpha_j is deferred to the next step (or the flush below); the copy is a
-        // kernel, so that a captured iteration holds kernels only
-        copy_matrix(s, alpha.p, m, alpha_prev.p, m, m, nr);
+        gpart.ensure(update_gram_workspace(N, m, nr));
+        // lambda += Z_j alpha_j is deferred to the next step (or the flush below)
         lam_pending = true;
         lam_dir = Zs;
-        have_gram = rows_update_gram(s, N, m, nr, alpha.p, Ps, ldW, -1.0, 1.0, Rs.p, nr, sqpart.p,
-                                     check ? nrm_out : nullptr, nr + 1, gpart.p, Cb.p);
+        have_gram = rows_update_gram(s, N, m, nr, alpha.p, Ps, ldW, -1.0, 1.0, Rs.p, nr, check ? nrm_out : nullptr,
+                                     nr + 1, gpart.p, Tj, diag_only, Bt.p, Mo.p);
         RPF_CHECK(have_gram, RPF_EINVAL, "block step: residual update shape");
         have_sq = check;
       } else {
+        sqpart.ensure((size_t)cdiv(N, 256) * nr);
         have_sq = check && rows_gemm2_sq(s, N, m, nr, alpha.p, 1.0, Zs, ldW, 1.0, dlam.p, nr, -1.0, Ps, ldW, 1.0,
                                          Rs.p, nr, sqpart.p, nrm_out, nr + 1);
         if (!have_sq)
