@@ -199,6 +199,10 @@ void rows_gemm_from(hipStream_t s, int64_t N, int a, int b, double alpha, const 
 // false (nothing launched) when those conditions do not hold.
 bool dgemm_flex(hipStream_t s, int64_t M, int64_t N, int64_t K, double alpha, const double* A, int64_t lda,
                 const double* B, int64_t ldb, double beta, double* C, int64_t ldc, bool lower = false);
+// The same kernel with K split into pieces of kchunk (a multiple of 32), each into its own M x N slab of
+// part, column-major.
+bool dgemm_flex_partials(hipStream_t s, int64_t M, int64_t N, int64_t K, const double* A, int64_t lda, const double* B,
+                         int64_t ldb, double* part, int64_t kchunk);
 // Z = R - X M1 (b columns) and Lam += X M2 (c columns) from one read of X (N x a); a, b, c <= 16,
 // M1 and M2 column-major with a rows.  Returns false (nothing launched) for other shapes.
 bool rows_orth_lam(hipStream_t s, int64_t N, int a, int b, int c, const double* X, int64_t ldx, const double* M1,
@@ -255,6 +259,9 @@ void build_tri_inv(hipStream_t s, const double* L, int64_t ldl, int64_t n, const
 // C (M x c, column-major) = beta C + alpha op(A) X with few columns c, op(A) M x K (A stored K x M when ta)
 void few_columns(hipStream_t s, bool ta, int64_t M, int64_t c, int64_t K, double alpha, const double* A, int64_t lda,
                  const double* X, int64_t ldx, double beta, double* C, int64_t ldc);
+// C = A X for row-major X (K x c) and C (M x c), A M x K column-major
+void few_columns_rows(hipStream_t s, int64_t M, int64_t c, int64_t K, const double* A, int64_t lda, const double* X,
+                      int64_t ldx, double* C, int64_t ldc);
 // B <- (L L^T)^{-1} B, L = leading n x n of a factor with its inverted NB blocks (dinv, see potrf) and
 // TRI_BW blocks (inv).
 // upper: the strict upper triangle of L's envelope holds L^T (mirror_envelope has run on it), so the

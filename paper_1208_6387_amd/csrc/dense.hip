@@ -166,7 +166,16 @@ __global__ __launch_bounds__(256) void k_dgemm_group(const DGroup g) {
 template <bool BETA>
 __global__ __launch_bounds__(512) void k_dgemm_big(int M, int N, int K, double alpha, const double* __restrict__ A,
                                                    int64_t lda, const double* __restrict__ B, int64_t ldb, double beta,
-                                                   double* __restrict__ C, int64_t ldc, int lower) {
+                                                   double* __restrict__ C, int64_t ldc, int lower, int kchunk,
+                                                   int64_t slab) {
+  // K split z: its columns of A and rows of B, into a slab of its own (kchunk a multiple of the stage)
+  {
+    const int k0 = (int)blockIdx.z * kchunk;
+    K = min(K - k0, kchunk);
+    A += (int64_t)k0 * lda;
+    B += k0;
+    C += (int64_t)blockIdx.z * slab;
+  }
   constexpr int BK = 32, RA = 128 + 16, SA = BK * RA, SB = 128 * BK;
   __shared__ __attribute__((aligned(1024))) double lA0[SA];
   __shared__ __attribute__((aligned(1024))) double lA1[SA];
@@ -255,18 +264,31 @@ __global__ __launch_bounds__(512) void k_dgemm_big(int M, int N, int K, double a
 }
 
 
+static bool flex_shape(int64_t M, int64_t N, int64_t K, const double* A, int64_t lda, const double* B, int64_t ldb) {
+  return M >= 2 && N >= 1 && K >= 1 && !(M & 1) && !(lda & 1) && ldb % 32 == 0 && K <= ldb && M <= INT32_MAX &&
+         N <= INT32_MAX && K <= INT32_MAX && !((uintptr_t)A & 15) && !((uintptr_t)B & 15);
+}
+
 bool dgemm_flex(hipStream_t s, int64_t M, int64_t N, int64_t K, double alpha, const double* A, int64_t lda,
                 const double* B, int64_t ldb, double beta, double* C, int64_t ldc, bool lower) {
-  if (M < 2 || N < 1 || K < 1 || (M & 1) || (lda & 1) || (ldb % 32) || K > ldb || M > INT32_MAX || N > INT32_MAX ||
-      ((uintptr_t)A & 15) || ((uintptr_t)B & 15))
-    return false;
+  if (!flex_shape(M, N, K, A, lda, B, ldb)) return false;
   const dim3 grid((unsigned)cdiv(M, 128), (unsigned)cdiv(N, 128));
+  const int kc = (int)(cdiv(K, 32) * 32);
   if (beta == 0.0)
     RPF_TIMED_LAUNCH((k_dgemm_big<false>), grid, dim3(512), 0, s, (int)M, (int)N, (int)K, alpha, A, lda, B, ldb, beta,
-                     C, ldc, lower ? 1 : 0);
+                     C, ldc, lower ? 1 : 0, kc, (int64_t)0);
   else
     RPF_TIMED_LAUNCH((k_dgemm_big<true>), grid, dim3(512), 0, s, (int)M, (int)N, (int)K, alpha, A, lda, B, ldb, beta,
-                     C, ldc, lower ? 1 : 0);
+                     C, ldc, lower ? 1 : 0, kc, (int64_t)0);
+  RPF_LAUNCH_CHECK();
+  return true;
+}
+
+bool dgemm_flex_partials(hipStream_t s, int64_t M, int64_t N, int64_t K, const double* A, int64_t lda, const double* B,
+                         int64_t ldb, double* part, int64_t kchunk) {
+  if (!flex_shape(M, N, K, A, lda, B, ldb) || kchunk < 32 || kchunk % 32) return false;
+  RPF_TIMED_LAUNCH((k_dgemm_big<false>), dim3((unsigned)cdiv(M, 128), (unsigned)cdiv(N, 128), (unsigned)cdiv(K, kchunk)),
+                   dim3(512), 0, s, (int)M, (int)N, (int)K, 1.0, A, lda, B, ldb, 0.0, part, M, 0, (int)kchunk, M * N);
   RPF_LAUNCH_CHECK();
   return true;
 }
@@ -1265,78 +1287,25 @@ __global__ __launch_bounds__(256) void k_rows_orth_lam(int64_t N, int a, int b, 
   __shared__ double sm2[16][16];
   __shared__ double xs[256][17];
   __shared__ double ys[256][17];
-  const int tid = threadIdx.x;
-  {
-    const int i = tid >> 4, j = tid & 15;
-    sm1[i][j] = (i < a && j < b) ? M1[i + (int64_t)a * j] : 0.0;
-    sm2[i][j] = (i < a && j < c) ? M2[i + (int64_t)a * j] : 0.0;
-  }
+  const int tid = threadIdx.x, er = tid >> 4, ec = tid & 15;
   const int64_t r0 = (int64_t)blockIdx.x * 256;
   const int rows = (int)min<int64_t>(256, N - r0);
-  if (rows == 256 && a == 16 && b == 16 && c == 16) {
-    // whole tile, 16 columns everywhere: the loads of X, R and Lam are all issued before anything
-    // waits (one memory latency per workgroup instead of three in a row)
-    double t[16], rv[16], lv[16];
+  // the loads of X, R and Lam, at clamped (always valid) places, are all issued before anything waits:
+  // one memory latency per workgroup (10 us at 76,080 x 8, where loads behind width tests took 16)
+  double t[16], rv[16], lv[16];
+  const double v1 = M1[min(er, a - 1) + (int64_t)a * min(ec, b - 1)];
+  const double v2 = M2[min(er, a - 1) + (int64_t)a * min(ec, c - 1)];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int64_t row = r0 + ((tid + u * 256) >> 4);
-      const int col = (tid + u * 256) & 15;
-      t[u] = X[row * ldx + col];
-      rv[u] = R[row * ldr + col];
-      lv[u] = Lam[row * ldl + col];
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = tid + u * 256;
-      xs[e >> 4][e & 15] = t[u];
-    }
-    __syncthreads();
-    double acc1[16], acc2[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) acc1[j] = acc2[j] = 0.0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const double xv = xs[tid][i];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        acc1[j] += xv * sm1[i][j];
-        acc2[j] += xv * sm2[i][j];
-      }
-    }
-    __syncthreads();  // xs is reused for the first product
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      xs[tid][j] = acc1[j];
-      ys[tid][j] = acc2[j];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = tid + u * 256;
-      const int64_t row = r0 + (e >> 4);
-      Z[row * ldz + (e & 15)] = rv[u] - xs[e >> 4][e & 15];
-      Lam[row * ldl + (e & 15)] = lv[u] + ys[e >> 4][e & 15];
-    }
-    return;
+  for (int u = 0; u < 16; ++u) {
+    const int64_t row = r0 + min(er + 16 * u, rows - 1);
+    t[u] = X[row * ldx + min(ec, a - 1)];
+    rv[u] = R[row * ldr + min(ec, b - 1)];
+    lv[u] = Lam[row * ldl + min(ec, c - 1)];
   }
-  if (rows == 256 && a == 16) {
-    double t[16];
+  sm1[er][ec] = (er < a && ec < b) ? v1 : 0.0;
+  sm2[er][ec] = (er < a && ec < c) ? v2 : 0.0;
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = tid + u * 256;
-      t[u] = X[(r0 + (e >> 4)) * ldx + (e & 15)];
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = tid + u * 256;
-      xs[e >> 4][e & 15] = t[u];
-    }
-  } else {
-    for (int e = tid; e < 256 * 16; e += 256) {
-      const int rr = e >> 4, cc = e & 15;
-      xs[rr][cc] = (rr < rows && cc < a) ? X[(r0 + rr) * ldx + cc] : 0.0;
-    }
-  }
+  for (int u = 0; u < 16; ++u) xs[er + 16 * u][ec] = ec < a ? t[u] : 0.0;
   __syncthreads();
   double acc1[16], acc2[16];
 #pragma unroll
@@ -1357,41 +1326,12 @@ __global__ __launch_bounds__(256) void k_rows_orth_lam(int64_t N, int a, int b, 
     ys[tid][j] = acc2[j];
   }
   __syncthreads();
-  if (rows == 256 && b == 16) {
-    double rv[16];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = tid + u * 256;
-      rv[u] = R[(r0 + (e >> 4)) * ldr + (e & 15)];
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = tid + u * 256;
-      Z[(r0 + (e >> 4)) * ldz + (e & 15)] = rv[u] - xs[e >> 4][e & 15];
-    }
-  } else {
-    for (int e = tid; e < rows * b; e += 256) {
-      const int rr = e / b, cc = e - rr * b;
-      Z[(r0 + rr) * ldz + cc] = R[(r0 + rr) * ldr + cc] - xs[rr][cc];
-    }
-  }
-  if (rows == 256 && c == 16) {
-    double lv[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = tid + u * 256;
-      lv[u] = Lam[(r0 + (e >> 4)) * ldl + (e & 15)];
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = tid + u * 256;
-      Lam[(r0 + (e >> 4)) * ldl + (e & 15)] = lv[u] + ys[e >> 4][e & 15];
-    }
-  } else {
-    for (int e = tid; e < rows * c; e += 256) {
-      const int rr = e / c, cc = e - rr * c;
-      Lam[(r0 + rr) * ldl + cc] += ys[rr][cc];
-    }
+  for (int u = 0; u < 16; ++u) {
+    const int rr = er + 16 * u;
+    if (rr >= rows) continue;
+    if (ec < b) Z[(r0 + rr) * ldz + ec] = rv[u] - xs[rr][ec];
+    if (ec < c) Lam[(r0 + rr) * ldl + ec] = lv[u] + ys[rr][ec];
   }
 }
 
@@ -2356,23 +2296,24 @@ void build_tri_inv(hipStream_t s, const double* L, int64_t ldl, int64_t n, const
   RPF_LAUNCH_CHECK();
 }
 
-// C (M x c, column-major) = beta C + alpha op(A) X with few columns (16 per workgroup): a workgroup takes
-// 32 rows, its four waves a quarter of K each, 32 k at a time with the next 32 on their way, and the
-// four partial results are added in LDS.  TA: op(A) = A^T, A stored K x M.  A walk over a 512-row block
+// C (M x c) = beta C + alpha op(A) X with few columns (16 per workgroup): a workgroup takes
+// 16 R rows, its four waves a quarter of K each, 32 k at a time with the next 32 on their way, and the
+// four partial results are added in LDS.  TA: op(A) = A^T, A stored K x M.  X(k, j) is X[k xk + j xj], C(m, j)
+// is C[m cm + j cj].  A walk over a 512-row block
 // is four load latencies a wave (5 us at 6,700 rows and 8 columns), where the general product has 32
 // dependent k-stages of 16 (14 to 17 us at K = 128 alone).
-template <bool TA>
+template <bool TA, int R>
 __global__ __launch_bounds__(256) void k_skinny(int64_t M, int64_t c, int64_t K, double alpha, const double* A,
-                                                int64_t lda, const double* X, int64_t ldx, double beta, double* C,
-                                                int64_t ldc) {
-  constexpr int R = 2, U = 8;  // row tiles of a workgroup, MFMA steps of a batch
+                                                int64_t lda, const double* X, int64_t xk, int64_t xj, double beta,
+                                                double* C, int64_t cm, int64_t cj) {
+  constexpr int U = 8;  // MFMA steps of a batch
   __shared__ double red[4][16 * R][17];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int fl = lane & 15, fk = lane >> 4;
   const int64_t m0 = (int64_t)blockIdx.x * 16 * R, c0 = (int64_t)blockIdx.y * 16;
-  const int64_t kc = (K + 127) / 128 * 32;  // a wave's quarter, whole batches
+  const int64_t kc = (K + 31) / 32 * 8;  // a wave's quarter
   const int64_t kb = min(w * kc, K), ke = min(kb + kc, K);
-  const double* Xc = X + min(c0 + fl, c - 1) * ldx;
+  const double* Xc = X + min(c0 + fl, c - 1) * xj;
   const double* Ar[R];
 #pragma unroll
   for (int i = 0; i < R; ++i) {
@@ -2389,7 +2330,7 @@ __global__ __launch_bounds__(256) void k_skinny(int64_t M, int64_t c, int64_t K,
       const int64_t k = k0 + 4 * u + fk, kk = min(k, K - 1);
 #pragma unroll
       for (int i = 0; i < R; ++i) pa[i][u] = TA ? Ar[i][kk] : Ar[i][kk * lda];
-      px[u] = Xc[kk];
+      px[u] = Xc[kk * xk];
     }
   };
   if (kb < ke) load(kb, a, x);
@@ -2419,31 +2360,44 @@ __global__ __launch_bounds__(256) void k_skinny(int64_t M, int64_t c, int64_t K,
     for (int r = 0; r < 4; ++r) red[w][16 * i + fl][fk + 4 * r] = acc[i][r];
   __syncthreads();
 #pragma unroll
-  for (int u = 0; u < 2 * R; ++u) {
+  for (int u = 0; u < R; ++u) {
     const int row = tid & (16 * R - 1), col = (tid / (16 * R)) + u * (256 / (16 * R));
-    if (col < 16 && m0 + row < M && c0 + col < c) {
+    if (m0 + row < M && c0 + col < c) {
       const double v = alpha * (red[0][row][col] + red[1][row][col] + red[2][row][col] + red[3][row][col]);
-      double* o = C + (c0 + col) * ldc + m0 + row;
+      double* o = C + (c0 + col) * cj + (m0 + row) * cm;
       *o = beta == 0.0 ? v : v + beta * *o;
     }
   }
 }
 
-// C = beta C + alpha op(A) X for a few columns: up to this many k_skinny is the faster one (64 x 64 tiles re-read less of A above)
-constexpr int64_t SKINNY = 96;
-void few_columns(hipStream_t s, bool ta, int64_t M, int64_t c, int64_t K, double alpha, const double* A,
-                        int64_t lda, const double* X, int64_t ldx, double beta, double* C, int64_t ldc) {
-  if (M <= 0 || c <= 0 || K <= 0) return;
-  if (c > SKINNY) {
-    dgemm(s, ta, false, M, c, K, alpha, A, lda, X, ldx, beta, C, ldc);
-    return;
-  }
-  const dim3 g((unsigned)cdiv(M, 32), (unsigned)cdiv(c, 16));
-  if (ta)
-    hipLaunchKernelGGL(k_skinny<true>, g, dim3(256), 0, s, M, c, K, alpha, A, lda, X, ldx, beta, C, ldc);
-  else
-    hipLaunchKernelGGL(k_skinny<false>, g, dim3(256), 0, s, M, c, K, alpha, A, lda, X, ldx, beta, C, ldc);
+// two row tiles a workgroup where that still gives every CU one
+static void launch_skinny(hipStream_t s, bool ta, int64_t M, int64_t c, int64_t K, double alpha, const double* A,
+                          int64_t lda, const double* X, int64_t xk, int64_t xj, double beta, double* C, int64_t cm,
+                          int64_t cj) {
+  const bool two = cdiv(M, 32) * cdiv(c, 16) >= 256;
+  const dim3 g((unsigned)cdiv(M, two ? 32 : 16), (unsigned)cdiv(c, 16));
+#define RPF_SK(TA, R) \
+  RPF_TIMED_LAUNCH((k_skinny<TA, R>), g, dim3(256), 0, s, M, c, K, alpha, A, lda, X, xk, xj, beta, C, cm, cj)
+  if (ta && two) RPF_SK(true, 2);
+  else if (ta) RPF_SK(true, 1);
+  else if (two) RPF_SK(false, 2);
+  else RPF_SK(false, 1);
+#undef RPF_SK
   RPF_LAUNCH_CHECK();
+}
+
+// up to this many columns k_skinny is the faster one (64 x 64 tiles re-read less of A above)
+constexpr int64_t SKINNY = 96;
+void few_columns(hipStream_t s, bool ta, int64_t M, int64_t c, int64_t K, double alpha, const double* A, int64_t lda,
+                 const double* X, int64_t ldx, double beta, double* C, int64_t ldc) {
+  if (M <= 0 || c <= 0 || K <= 0) return;
+  if (c > SKINNY) dgemm(s, ta, false, M, c, K, alpha, A, lda, X, ldx, beta, C, ldc);
+  else launch_skinny(s, ta, M, c, K, alpha, A, lda, X, 1, ldx, beta, C, 1, ldc);
+}
+
+void few_columns_rows(hipStream_t s, int64_t M, int64_t c, int64_t K, const double* A, int64_t lda, const double* X,
+                      int64_t ldx, double* C, int64_t ldc) {
+  if (M > 0 && c > 0 && K > 0) launch_skinny(s, false, M, c, K, 1.0, A, lda, X, ldx, 1, 0.0, C, ldc, 1);
 }
 
 // The serial chain of a solve is its diagonal blocks: they are taken TRI_BW = 512 rows at a time through

@@ -718,18 +718,39 @@ int64_t group_kchunk(int64_t nb_rows, int64_t K, int64_t cols, int tile, int wor
   return cdiv(cdiv(K, sp), (int64_t)align) * align;
 }
 
-F64Plan plan_F64(rpf_problem pb, const rpf_pattern* pats, int m, const Schedule& sc) {
-  // W-format workspace: one slab per pattern (times the K splits for the results).  When the
-  // 128 x 128 tiles alone fill the chip (or the schedule asks for it), a pattern's product runs on
-  // the large-problem kernel, whose W blocks have their leading dimension padded to a multiple of
-  // 32 with zero rows.  A grouped schedule puts every pattern's product in one launch.
+bool many_small_products(rpf_problem pb, const rpf_pattern* pats, int m, int tile, int full) {
+  int used = 0;
+  for (int p = 0; p < pb->n_pat; ++p) {
+    const int64_t cols = (int64_t)pb->occ_of_pat[p].size() * m;
+    if (cols == 0) continue;
+    ++used;
+    if (cdiv(pats[p]->n_b, (int64_t)tile) * cdiv(cols, (int64_t)tile) >= full) return false;
+  }
+  return used > 1;
+}
+
+F64Plan plan_F64(rpf_problem pb, const rpf_pattern* pats, int m, const Schedule& sc, bool narrow) {
+  // W-format workspace: one slab per pattern (times the K splits for the results).  The size rule
+  // (no schedule):
+  // - several small patterns: one grouped launch of 64 x 64 tiles (the uneven three-pattern batch at 8
+  //   columns: 45 us an application against 82 us in a launch per pattern);
+  // - a small pattern with few columns: the product for few columns, which waits for memory a few times
+  //   instead of once per 16 k (51 rows and 12 columns: 4 us against 7.6);
+  // - where the 128 x 128 tiles of the large-problem kernel, times K pieces of at least 256, fill
+  //   three quarters of the 256 CUs or more: that kernel, with the number of pieces that leaves
+  //   the last round fullest (2,598 rows and 512 columns: see below for both sides); its W blocks
+  //   have their leading dimension padded to a multiple of 32 with zero rows;
+  // - else 64 x 64 tiles with K split until there are about four workgroups per CU.
+  constexpr int CUS = 256;
   F64Plan pl{};
-  pl.tile = (sc.tile == 64 || sc.tile == 128) ? sc.tile : 0;
+  Schedule use = sc;
+  if (sc.tile == 0 && !narrow && many_small_products(pb, pats, m, 128, CUS)) use = Schedule{64, 1024};
+  pl.tile = (use.tile == 64 || use.tile == 128) ? use.tile : 0;
   for (int p = 0; p < pb->n_pat; ++p) {
     const int nb = pats[p]->n_b;
     const int64_t cols = (int64_t)pb->occ_of_pat[p].size() * m;
     if (pl.tile) {
-      pl.kchunk[p] = group_kchunk(nb, nb, cols, pl.tile, sc.work, 16);
+      pl.kchunk[p] = group_kchunk(nb, nb, cols, pl.tile, use.work, 16);
       pl.nsp[p] = pl.alloc_sp[p] = (int)cdiv(nb, pl.kchunk[p]);
       pl.big[p] = 0;
       pl.ldw[p] = nb;
@@ -740,15 +761,35 @@ F64Plan plan_F64(rpf_problem pb, const rpf_pattern* pats, int m, const Schedule&
       sp = std::min(sp, 8);
       pl.nsp[p] = splits_used(nb, sp);
       pl.alloc_sp[p] = sp;
-      if (sc.tile == 256 && nb % 2 == 0) {
+      pl.kchunk[p] = 0;
+      const int64_t tiles128 = cdiv(nb, 128) * cdiv(cols, (int64_t)128);
+      if (use.tile == 0 && !narrow && cols <= 96 && nb <= 512) {
+        pl.nsp[p] = pl.alloc_sp[p] = 1;
+        pl.few[p] = 1;
+      } else if (use.tile == 256 && nb % 2 == 0) {
         // the schedule asks for the large-problem kernel whatever the tile count
         pl.nsp[p] = pl.alloc_sp[p] = 1;
         pl.big[p] = 1;
       } else {
-        pl.big[p] = pl.nsp[p] == 1 && nb % 2 == 0 && cdiv(nb, 128) * cdiv(cols, (int64_t)128) >= 256;
+        pl.big[p] = pl.nsp[p] == 1 && nb % 2 == 0 && tiles128 >= CUS;
+        const int most = (int)std::min<int64_t>(8, nb / 256);
+        if (!pl.big[p] && !narrow && nb % 2 == 0 && tiles128 * most >= 3 * CUS / 4) {
+          double best = 0.0;
+          for (int q = 1; q <= most; ++q) {
+            const int64_t kc = cdiv(cdiv((int64_t)nb, q), 32) * 32, got = cdiv((int64_t)nb, kc);
+            const int64_t wgs = tiles128 * got, rounds = cdiv(wgs, CUS);
+            // useful stages of a round's longest piece; a piece costs about three stages to start and end
+            const double fill = (double)tiles128 * nb / ((double)rounds * CUS * (kc + 96));
+            if (fill > 1.02 * best) {
+              best = fill;
+              pl.kchunk[p] = kc;
+              pl.nsp[p] = pl.alloc_sp[p] = (int)got;
+              pl.big[p] = 1;
+            }
+          }
+        }
       }
       pl.ldw[p] = pl.big[p] ? cdiv(nb, 32) * 32 : nb;
-      pl.kchunk[p] = 0;
     }
     pl.off[p + 1] = pl.off[p] + pl.ldw[p] * cols;
     pl.yoff[p + 1] = pl.yoff[p] + (int64_t)nb * cols * pl.alloc_sp[p];
@@ -815,7 +856,12 @@ YLoc run_F64(rpf_problem pb, const rpf_pattern* pats, const F64Plan& pl, int m, 
     }
     // the tracer times the flexibility products only
     void* tok = (trace && op == OP_FLEX) ? trace_begin(s, RPF_FP64) : nullptr;
-    if (pl.nsp[p] > 1) {
+    if (pl.few[p]) {
+      few_columns(s, false, nb, cols, nb, 1.0, Mp, nb, xp, lw, 0.0, yp, nb);
+    } else if (pl.big[p] && pl.nsp[p] > 1) {
+      RPF_CHECK(dgemm_flex_partials(s, nb, cols, nb, Mp, nb, xp, lw, yp, pl.kchunk[p]), RPF_EINVAL,
+                "flexibility product: large-problem layout");
+    } else if (pl.nsp[p] > 1) {
       dgemm_partials(s, nb, cols, nb, Mp, nb, xp, lw, yp, pl.alloc_sp[p]);
     } else if (!(pl.big[p] && dgemm_flex(s, nb, cols, nb, 1.0, Mp, nb, xp, lw, 0.0, yp, nb))) {
       dgemm(s, false, false, nb, cols, nb, 1.0, Mp, nb, xp, lw, 0.0, yp, nb);
@@ -1126,20 +1172,13 @@ void project_block(rpf_problem pb, double* x, int64_t ldx, int m, hipStream_t s)
   coarse_g(pb, pb->ybuf.p, m, -1.0, x, ldx, 1.0, s);
 }
 
-// y = (G^T G)^{-1} c for n_G x m row-major blocks, with the explicit (symmetric) inverse.  Large
-// coarse spaces go through the split-K FP64 MFMA product y^T (m x n_G) = c^T Ginv; small ones
-// through the row product.
-// y = inv c for the explicit symmetric inverse of a coarse matrix (n_G x m row-major c and y)
+// y = (G^T G)^{-1} c for n_G x m row-major blocks, with the explicit (symmetric) inverse: bound by reading
+// it once per 16 columns (75 MB at n_G = 3,072; before, 31 + 5 us on a split-K product with 16 output
+// rows there, and 11.5 us with one wave per row at n_G = 384)
 static void coarse_solve_with(rpf_problem pb, const double* inv, const double* c, double* y, int m, hipStream_t s) {
   const int nG = pb->n_G;
   if (nG == 0) return;
-  if (nG >= 1024) {
-    const int sp = gemm_splitk_count(m, nG, nG);
-    pb->cws.ensure((size_t)sp * m * nG);
-    dgemm_splitk(s, false, false, m, nG, nG, 1.0, c, m, inv, nG, 0.0, y, m, pb->cws.p, sp);
-  } else {
-    rows_gemm(s, nG, nG, m, 1.0, inv, nG, c, 0.0, y, m, m);
-  }
+  few_columns_rows(s, nG, m, nG, inv, nG, c, m, y, m);
 }
 
 void coarse_solve(rpf_problem pb, const double* c, double* y, int m, hipStream_t s) {

@@ -767,7 +767,10 @@ void apply_F_lowprec(rpf_problem pb, const rpf_pattern* pats, int m, const doubl
   std::vector<int> nsp(pb->n_pat, 1), kch(pb->n_pat, 0), tile_m(pb->n_pat, 64), tile_n(pb->n_pat, 64);
   // a grouped schedule (bf16 forms only) runs every pattern's product in one persistent launch of
   // its tile, each pattern's K split set by the schedule's work target
-  const Schedule sc = schedule_for(pb, m, prec);
+  Schedule sc = schedule_for(pb, m, prec);
+  // without a schedule, several small patterns share one launch too (the uneven three-pattern batch at 8
+  // columns: 36 us an application against 64 us in a launch per pattern)
+  if (split && sc.tile == 0 && many_small_products(pb, pats, m, 256, 240)) sc = Schedule{64, 1024};
   const int gtile = (split && (sc.tile == 64 || sc.tile == 128)) ? sc.tile : 0;
   for (int p = 0; p < pb->n_pat; ++p) {
     const int nb = pats[p]->n_b;

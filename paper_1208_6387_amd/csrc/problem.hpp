@@ -116,7 +116,7 @@ struct rpf_problem_s {
   rpf::DevBuf<int> d_ep_goff;
   int g_km = 0;
   rpf::DevBuf<const double*> d_Zp;
-  rpf::DevBuf<double> Ginv, cbuf, ybuf, cpart, cws;
+  rpf::DevBuf<double> Ginv, cbuf, ybuf, cpart;
   // coarse space with a preconditioner F~^{-1} in the projector: (G^T F~^{-1} G)^{-1}, built for the
   // pattern handles and preconditioner kind in hkey, and an N_lambda x m workspace
   std::vector<uint64_t> hkey;
@@ -145,13 +145,17 @@ enum LocalOp { OP_FLEX = 0, OP_SCHUR = 1 };
 struct F64Plan {
   int64_t off[MAXP + 1], yoff[MAXP + 1], ldw[MAXP], kchunk[MAXP];
   int nsp[MAXP], alloc_sp[MAXP];
-  char big[MAXP];
+  char big[MAXP], few[MAXP];
   int tile;  // 64 or 128: every pattern in one grouped launch of that tile; 0: per-pattern launches
   int64_t xneed, yneed;
 };
 // the schedule installed for (m, prec), or the size rule (tile 0)
 Schedule schedule_for(rpf_problem pb, int m, int prec);
-F64Plan plan_F64(rpf_problem pb, const rpf_pattern* pats, int m, const Schedule& sc);
+// narrow: the size rule without the large-problem kernel's padded blocks and without grouping (the plan
+// with the least workspace)
+F64Plan plan_F64(rpf_problem pb, const rpf_pattern* pats, int m, const Schedule& sc, bool narrow = false);
+// several patterns, none of which fills the chip with `tile`-sized tiles (at least `full` of them) by itself
+bool many_small_products(rpf_problem pb, const rpf_pattern* pats, int m, int tile, int full);
 // grouped persistent launches of the flexibility products (tile 64 or 128)
 void dgemm_group(hipStream_t s, int tile, const DGroup& g);
 void gemm_bf16_group(hipStream_t s, int tile, bool x3, const BfGroup& g);
