@@ -191,7 +191,7 @@ void rows_gemm(hipStream_t s, int64_t N, int a, int b, double alpha, const doubl
 void rows_gemm_from(hipStream_t s, int64_t N, int a, int b, double alpha, const double* X, int64_t ldx,
                     const double* M, double beta, const double* Z, int64_t ldz, double* Y, int64_t ldy);
 // The paired product below (a, b <= 16, M column-major) that also returns the column sums of
-// squares of Y2 after the update: sq[c * ldsq], c < b (part: cdiv(N, 256) * b doubles of
+// squares of Y2 after the update: sq[c * ldsq], c < b, and sq[b b] = *raised (part: cdiv(N, 256) * b doubles of
 // workspace).  Returns false, doing nothing, when the block is too wide.
 // C = alpha A B (+ beta C) on the large-problem FP64 kernel (the flexibility product): column-major,
 // M and lda even, A and B 16-byte aligned, ldb a multiple of 32 with B's rows K .. ldb zero in
@@ -208,16 +208,18 @@ bool dgemm_flex_partials(hipStream_t s, int64_t M, int64_t N, int64_t K, const d
 bool rows_orth_lam(hipStream_t s, int64_t N, int a, int b, int c, const double* X, int64_t ldx, const double* M1,
                    const double* R, int64_t ldr, double* Z, int64_t ldz, const double* M2, double* Lam, int64_t ldl);
 // Y = beta Y + alpha X M (N x a, a = b <= 16), and from the same pass what the next block step starts from:
-// sq[c * ldsq] = the squared column norms of the new Y (skipped when sq is NULL), C = X^T Y_new,
+// sq[c * ldsq] = the squared column norms of the new Y and sq[a a] = *raised (skipped when sq is NULL),
+// C = X^T Y_new,
 // Bo = T^T C (its diagonal only with diag) and Mo = T Bo, a x a column-major.  part: a workspace of
 // update_gram_workspace doubles.  Returns false (nothing launched) when the shape is not supported.
 size_t update_gram_workspace(int64_t N, int a, int b);
 bool rows_update_gram(hipStream_t s, int64_t N, int a, int b, const double* M, const double* X, int64_t ldx,
                       double alpha, double beta, double* Y, int64_t ldy, double* sq, int64_t ldsq, double* part,
-                      const double* T, bool diag, double* Bo, double* Mo);
+                      const double* T, bool diag, const double* raised, double* Bo, double* Mo);
 bool rows_gemm2_sq(hipStream_t s, int64_t N, int a, int b, const double* M, double alpha1, const double* X1,
                    int64_t ldx1, double beta1, double* Y1, int64_t ldy1, double alpha2, const double* X2,
-                   int64_t ldx2, double beta2, double* Y2, int64_t ldy2, double* part, double* sq, int64_t ldsq);
+                   int64_t ldx2, double beta2, double* Y2, int64_t ldy2, double* part, const double* raised, double* sq,
+                   int64_t ldsq);
 // Two such products sharing M in one launch: Y1 = beta1 Y1 + alpha1 X1 M, Y2 = beta2 Y2 + alpha2 X2 M.
 void rows_gemm2(hipStream_t s, int64_t N, int a, int b, const double* M, int64_t mrow, double alpha1,
                 const double* X1, int64_t ldx1, double beta1, double* Y1, int64_t ldy1, double alpha2,
@@ -292,8 +294,7 @@ void syev_small(hipStream_t s, const double* A, int m, double* V, double* w, int
 // Small matrices of a block step: the normalisation T (m x m) of a block from eta and alpha = T (T^T zr)
 // (m x nr) to alpha and, unless NULL, alpha2; see k_block_coef.
 void block_coef(hipStream_t s, int m, int nr, const double* eta, const double* zr, bool diag_only, int ka,
-                const double* B, double tau, double* T, int* drops, double* flag0, double* flag1, double* alpha,
-                double* alpha2);
+                const double* B, double tau, double* T, int* drops, double* raised, double* alpha, double* alpha2);
 
 // Orthonormalise the k columns of Y (n x k, ld) in place (modified Gram-Schmidt, twice).
 void orthonormalize(hipStream_t s, double* Y, int64_t n, int64_t ld, int k);

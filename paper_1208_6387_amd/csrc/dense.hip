@@ -1093,88 +1093,52 @@ __global__ __launch_bounds__(256) void k_rows_tile(int64_t N, int a, int b, cons
                                                    RowsPairs pr) {
   __shared__ double sm[16][16];
   __shared__ double xs[256][17];
-  const int tid = threadIdx.x;
-  {
-    const int i = tid >> 4, j = tid & 15;
-    sm[i][j] = (i < a && j < b) ? (mrow > 0 ? Mm[(int64_t)i * mrow + j] : Mm[i + (int64_t)a * j]) : 0.0;
-  }
+  const int tid = threadIdx.x, er = tid >> 4, ec = tid & 15;  // element (er + 16 u, ec) of the tile in pass u
   const RowsPair& P = pr.p[blockIdx.y];
   const int64_t r0 = (int64_t)blockIdx.x * 256;
   const int rows = (int)min<int64_t>(256, N - r0);
-  // full 256 x 16 tiles (the common case) issue all sixteen loads of a thread before the first
-  // LDS store, so they are in flight together
-  const bool full = rows == 256 && a == 16;
-  if (full) {
-    double t[16];
+  // every load of the tile at clamped (always valid) addresses, in flight together, masked afterwards:
+  // one memory latency (18 us at 76,080 x 8 with loads behind width tests)
+  double t[16], zv[16];
+  const int mi = min(er, a - 1), mj = min(ec, b - 1);
+  const double mv = mrow > 0 ? Mm[(int64_t)mi * mrow + mj] : Mm[mi + (int64_t)a * mj];
+  const double* src = P.Z ? P.Z : P.Y;
+  const int64_t lds = P.Z ? P.ldz : P.ldy;
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = tid + u * 256;
-      t[u] = P.X[(r0 + (e >> 4)) * P.ldx + (e & 15)];
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = tid + u * 256;
-      xs[e >> 4][e & 15] = t[u];
-    }
-  } else {
-    for (int e = tid; e < rows * a; e += 256) {
-      const int rr = e / a, cc = e - rr * a;
-      xs[rr][cc] = P.X[(r0 + rr) * P.ldx + cc];
-    }
+  for (int u = 0; u < 16; ++u) {
+    const int64_t row = r0 + min(er + 16 * u, rows - 1);
+    t[u] = P.X[row * P.ldx + min(ec, a - 1)];
+    if (P.beta != 0.0) zv[u] = src[row * lds + mj];
   }
+  sm[er][ec] = (er < a && ec < b) ? mv : 0.0;
+#pragma unroll
+  for (int u = 0; u < 16; ++u) xs[er + 16 * u][ec] = ec < a ? t[u] : 0.0;
   __syncthreads();
   double acc[16];
 #pragma unroll
   for (int j = 0; j < 16; ++j) acc[j] = 0.0;
-  if (tid < rows) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      if (i < a) {
-        const double xv = xs[tid][i];
+  for (int i = 0; i < 16; ++i) {
+    const double xv = xs[tid][i];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) acc[j] += xv * sm[i][j];
-      }
-    }
+    for (int j = 0; j < 16; ++j) acc[j] += xv * sm[i][j];
   }
   __syncthreads();  // xs is reused for the output rows
-  if (tid < rows) {
 #pragma unroll
-    for (int j = 0; j < 16; ++j)
-      if (j < b) xs[tid][j] = acc[j];
-  }
-  // with colsq (b divides 256), every element a thread writes lies in column tid % b: the thread
-  // sums their squares and the column sums are formed in a fixed order (deterministic)
+  for (int j = 0; j < 16; ++j) xs[tid][j] = acc[j];
+  __syncthreads();
+  // with colsq, a thread sums the squares of its column of the tile and the column sums are formed in a
+  // fixed order (deterministic)
   const bool want_sq = pr.colsq != nullptr && blockIdx.y == 1;
   double myq = 0.0;
-  __syncthreads();
-  if (rows == 256 && b == 16) {
-    // same element order as below; the sixteen beta-term loads go out together
-    double zv[16];
-    if (P.beta != 0.0) {
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int e = tid + u * 256;
-        const int64_t row = r0 + (e >> 4);
-        zv[u] = P.Z ? P.Z[row * P.ldz + (e & 15)] : P.Y[row * P.ldy + (e & 15)];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = tid + u * 256;
-      const double v = P.alpha * xs[e >> 4][e & 15];
-      const double out = (P.beta == 0.0) ? v : P.beta * zv[u] + v;
-      P.Y[(r0 + (e >> 4)) * P.ldy + (e & 15)] = out;
-      myq += out * out;
-    }
-  } else {
-    for (int e = tid; e < rows * b; e += 256) {
-      const int rr = e / b, cc = e - rr * b;
-      double* y = P.Y + (r0 + rr) * P.ldy + cc;
-      const double v = P.alpha * xs[rr][cc];
-      const double out = (P.beta == 0.0) ? v : P.beta * (P.Z ? P.Z[(r0 + rr) * P.ldz + cc] : *y) + v;
-      *y = out;
-      myq += out * out;
-    }
+  for (int u = 0; u < 16; ++u) {
+    const int rr = er + 16 * u;
+    if (rr >= rows || ec >= b) continue;
+    const double v = P.alpha * xs[rr][ec];
+    const double out = (P.beta == 0.0) ? v : P.beta * zv[u] + v;
+    P.Y[(r0 + rr) * P.ldy + ec] = out;
+    myq += out * out;
   }
   if (want_sq) {
     __syncthreads();
@@ -1182,9 +1146,10 @@ __global__ __launch_bounds__(256) void k_rows_tile(int64_t N, int a, int b, cons
     red[tid] = myq;
     __syncthreads();
     if (tid < b) {
-      double t = 0.0;
-      for (int k = tid; k < 256; k += b) t += red[k];
-      pr.colsq[(int64_t)blockIdx.x * b + tid] = t;
+      double q = 0.0;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) q += red[tid + 16 * k];
+      pr.colsq[(int64_t)blockIdx.x * b + tid] = q;
     }
   }
 }
@@ -1370,7 +1335,8 @@ void rows_gemm_from(hipStream_t s, int64_t N, int a, int b, double alpha, const 
 
 // out[c * ldo] = sum_z part[z * b + c]: one workgroup per column c, a fixed partition of z over the
 // threads and a fixed tree (deterministic).
-__global__ __launch_bounds__(256) void k_colsum(int nz, int b, const double* part, double* out, int64_t ldo) {
+__global__ __launch_bounds__(256) void k_colsum(int nz, int b, const double* part, const double* raised, double* out,
+                                                int64_t ldo) {
   __shared__ double red[256];
   const int c = blockIdx.x, tid = threadIdx.x;
   double v = 0.0;
@@ -1382,12 +1348,14 @@ __global__ __launch_bounds__(256) void k_colsum(int nz, int b, const double* par
     __syncthreads();
   }
   if (tid == 0) out[(int64_t)c * ldo] = red[0];
+  if (tid == 0 && c == 0) out[(int64_t)b * b] = *raised;
 }
 
 bool rows_gemm2_sq(hipStream_t s, int64_t N, int a, int b, const double* M, double alpha1, const double* X1,
                    int64_t ldx1, double beta1, double* Y1, int64_t ldy1, double alpha2, const double* X2,
-                   int64_t ldx2, double beta2, double* Y2, int64_t ldy2, double* part, double* sq, int64_t ldsq) {
-  if (N <= 0 || b <= 0 || a > 16 || b > 16 || 256 % b != 0) return false;
+                   int64_t ldx2, double beta2, double* Y2, int64_t ldy2, double* part, const double* raised, double* sq,
+                   int64_t ldsq) {
+  if (N <= 0 || b <= 0 || a > 16 || b > 16) return false;
   RowsPairs pr{};
   pr.p[0] = {X1, Y1, ldx1, ldy1, alpha1, beta1, nullptr, 0};
   pr.p[1] = {X2, Y2, ldx2, ldy2, alpha2, beta2, nullptr, 0};
@@ -1396,7 +1364,7 @@ bool rows_gemm2_sq(hipStream_t s, int64_t N, int a, int b, const double* M, doub
   hipLaunchKernelGGL(k_rows_tile, dim3(nwg, 2), dim3(256), 0, s, N, a, b, M, (int64_t)0, pr);
   RPF_LAUNCH_CHECK();
   // sq[c * ldsq] = sum over workgroups of part[wg * b + c]
-  hipLaunchKernelGGL(k_colsum, dim3((unsigned)b), dim3(256), 0, s, (int)nwg, b, part, sq, ldsq);
+  hipLaunchKernelGGL(k_colsum, dim3((unsigned)b), dim3(256), 0, s, (int)nwg, b, part, raised, sq, ldsq);
   RPF_LAUNCH_CHECK();
   return true;
 }
@@ -1422,10 +1390,12 @@ __global__ __launch_bounds__(320) void k_recsum(int nrec, int len, int per, cons
 }
 
 // The records of rows_update_gram (n of them left) to what the next block step starts from, in one
-// workgroup: C = P^T R (m x m) and the squared norms (to sq, stride ldsq, unless NULL), then B = T^T C
+// workgroup: C = P^T R (m x m) and the squared norms (to sq, stride ldsq, unless NULL, with *raised after
+// the m x m entries), then B = T^T C
 // (its diagonal only with diag) and M = T B.
 __global__ __launch_bounds__(1024) void k_recsum_coef(int n, int m, const double* rec, const double* T, int diag,
-                                                      double* sq, int64_t ldsq, double* B, double* M) {
+                                                      const double* raised, double* sq, int64_t ldsq, double* B,
+                                                      double* M) {
   __shared__ double c[16 * 17], st[256], sb[256];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int len = m * m + m;
@@ -1448,6 +1418,7 @@ __global__ __launch_bounds__(1024) void k_recsum_coef(int n, int m, const double
   }
   __syncthreads();
   if (sq && tid < m) sq[tid * ldsq] = c[m * m + tid];
+  if (sq && tid == 0) sq[(int64_t)m * m] = *raised;
   const int r = tid % m, col = tid / m;
   double v = 0.0;
   if (tid < m * m && (!diag || r == col))
@@ -1478,7 +1449,7 @@ size_t update_gram_workspace(int64_t N, int a, int b) { return (size_t)(cdiv(N, 
 
 bool rows_update_gram(hipStream_t s, int64_t N, int a, int b, const double* M, const double* X, int64_t ldx,
                       double alpha, double beta, double* Y, int64_t ldy, double* sq, int64_t ldsq, double* part,
-                      const double* T, bool diag, double* Bo, double* Mo) {
+                      const double* T, bool diag, const double* raised, double* Bo, double* Mo) {
   if (N <= 0 || a <= 0 || a > 16 || b != a) return false;
   const int nwg = (int)cdiv(N, 256), len = a * b + b;
   hipLaunchKernelGGL(k_rows_update_gram, dim3((unsigned)nwg), dim3(256), 0, s, N, a, b, M, X, ldx, alpha, beta, Y,
@@ -1493,7 +1464,8 @@ bool rows_update_gram(hipStream_t s, int64_t N, int a, int b, const double* M, c
     hipLaunchKernelGGL(k_recsum, dim3((unsigned)n), dim3(320), 0, s, nwg, len, per, part, tmp);
     rec = tmp;
   }
-  hipLaunchKernelGGL(k_recsum_coef, dim3(1), dim3(1024), 0, s, n, a, rec, T, diag ? 1 : 0, sq, ldsq, Bo, Mo);
+  hipLaunchKernelGGL(k_recsum_coef, dim3(1), dim3(1024), 0, s, n, a, rec, T, diag ? 1 : 0, raised, sq, ldsq,
+                     Bo, Mo);
   RPF_LAUNCH_CHECK();
   return true;
 }
@@ -2695,13 +2667,13 @@ __device__ inline void wave_sync() {
 // 1 / |L^{-1}|_F^2 (a lower bound of w_min) above tau * max(trace eta, max_c energy_c) (an upper
 // bound of that reference), no eigenpair would be dropped and T = L^{-T} spans the same
 // directions, so it is used; otherwise T = V diag(w^{-1/2}) over the kept eigenpairs.  When nothing is
-// kept, 1 goes to flag0 and flag1.  Then alpha = T (T^T zr) (m x nr; the diagonal of T^T zr only in the
+// kept, 1 goes to raised.  Then alpha = T (T^T zr) (m x nr; the diagonal of T^T zr only in the
 // diagonal form), to one or two places.  MM >= m is the unrolled register length; the first wave forms
 // T, the four of them the eigenpairs and the products (as separate launches, these took 4.5 us each).
 template <int MM>
 __global__ __launch_bounds__(256) void k_block_coef(int m, int nr, const double* eta, const double* zr, int diag_only,
                                                     int ka, const double* B, double tau, double* T, int* drops,
-                                                    double* flag0, double* flag1, double* alpha, double* alpha2) {
+                                                    double* raised, double* alpha, double* alpha2) {
   __shared__ double epre[64];
   __shared__ double Ls[MM][MM + 1];  // the factor; the Jacobi iteration's matrix
   __shared__ double Vs[MM][MM + 1];  // its vectors; T^T zr
@@ -2791,10 +2763,7 @@ __global__ __launch_bounds__(256) void k_block_coef(int m, int nr, const double*
       T[t * m + t] = tc;
     }
     if (t == 0) {
-      if (!any) {
-        flag0[0] = 1.0;
-        flag1[0] = 1.0;
-      }
+      if (!any) raised[0] = 1.0;
       ok_s = 1;
     }
   } else {
@@ -2885,10 +2854,7 @@ __global__ __launch_bounds__(256) void k_block_coef(int m, int nr, const double*
       else atomicAdd(drops, 1);
     }
     __syncthreads();
-    if (tid == 0 && kept_s == 0) {
-      flag0[0] = 1.0;
-      flag1[0] = 1.0;
-    }
+    if (tid == 0 && kept_s == 0) raised[0] = 1.0;
     for (int i = tid; i < m * m; i += 256) {
       const int r = i % m, c = i / m;
       const double v = Vs[r][sh.order[c]] * rdiag[c];
@@ -2916,12 +2882,11 @@ __global__ __launch_bounds__(256) void k_block_coef(int m, int nr, const double*
 }
 
 void block_coef(hipStream_t s, int m, int nr, const double* eta, const double* zr, bool diag_only, int ka,
-                const double* B, double tau, double* T, int* drops, double* flag0, double* flag1, double* alpha,
-                double* alpha2) {
+                const double* B, double tau, double* T, int* drops, double* raised, double* alpha, double* alpha2) {
   RPF_CHECK(m >= 1 && m <= EIG_MAX && nr <= m, RPF_EINVAL, "block_coef: block width");
 #define RPF_BC(MM)                                                                                                   \
   hipLaunchKernelGGL(k_block_coef<MM>, dim3(1), dim3(256), 0, s, m, nr, eta, zr, diag_only ? 1 : 0, ka, B, tau, T, drops, \
-                     flag0, flag1, alpha, alpha2)
+                     raised, alpha, alpha2)
   if (m <= 8) RPF_BC(8);
   else if (m <= 16) RPF_BC(16);
   else if (m <= 32) RPF_BC(32);

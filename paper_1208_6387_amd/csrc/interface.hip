@@ -76,77 +76,15 @@ __device__ inline double wave_sum(double v) {
   return v;
 }
 
-// Partial sums of (Z^T A^(s)T x)[r][j]: workgroup (s, sp) covers the boundary
-// dofs [dper sp, dper (sp+1)) of occurrence s.  The contraction over dofs runs on
-// v_mfma_f64_16x16x4_f64: lane l gathers x_loc[d][j] = (A^(s)T x)[d][j] for dof
-// d = d0 + l/16 and column j = j0 + l%16 (sum over the multipliers at the node,
-// rotated to the pattern frame) and loads Z[d][l%16]; the accumulator then holds
-// (modes x columns).  part[((s*nsplit + sp)*KMAX + r)*m + j].
-template <int DPN>
-__global__ __launch_bounds__(256) void k_coarse_gt(const int* occ_pat, const int* slot_off, const int* nbn_p,
-                                                   const double* const* Zp, const int* kp, const int* goff,
-                                                   const int* l2m_ptr, const int* l2m_code, const double* rot,
-                                                   const double* x, int64_t ldx, int m, int nsplit, double* part) {
-  __shared__ double red[4][256];
-  const int s = blockIdx.x, sp = blockIdx.y;
-  const int p = occ_pat[s];
-  const int k = kp[p];
-  const int nd = nbn_p[p] * DPN;
-  const int dper = ((nd + nsplit - 1) / nsplit + 15) / 16 * 16;
-  const int d_beg = sp * dper, d_end = min(nd, d_beg + dper);
-  const double* Z = Zp[p];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r = lane & 15;
-  double O[9];
-  if (DPN == 3) load_rot<DPN>(rot, s, O);
-  for (int j0 = 0; j0 < m; j0 += 16) {
-    const int j = j0 + (lane & 15);
-    const bool jok = j < m;
-    v4d acc = {0.0, 0.0, 0.0, 0.0};
-    for (int d0 = d_beg + 4 * wave; d0 < d_end; d0 += 16) {
-      const int d = d0 + (lane >> 4);
-      const bool dok = d < d_end;
-      double xv = 0.0;
-      if (dok && jok) {
-        const int bn = d / DPN, c2 = d % DPN;
-        const int slot = slot_off[s] + bn;
-        for (int e = l2m_ptr[slot]; e < l2m_ptr[slot + 1]; ++e) {
-          const int code = l2m_code[e];
-          const double sg = (code & 1) ? -1.0 : 1.0;
-          const int64_t mult = code >> 1;
-          if (DPN == 3) {
-            const double* xr = x + mult * 3 * ldx + j;
-            xv += sg * (O[c2] * xr[0] + O[3 + c2] * xr[ldx] + O[6 + c2] * xr[2 * ldx]);
-          } else {
-            xv += sg * x[(mult * DPN + c2) * ldx + j];
-          }
-        }
-      }
-      const double zv = (dok && r < k) ? Z[(int64_t)r * nd + d] : 0.0;
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(zv, xv, acc, 0, 0, 0);
-    }
-    // accumulator item q of lane l: mode l/16 + 4q, column j0 + l%16
-#pragma unroll
-    for (int q = 0; q < 4; ++q) red[wave][((lane >> 4) + 4 * q) * 16 + (lane & 15)] = acc[q];
-    __syncthreads();
-    {
-      const int mi = tid / 16, jj = tid % 16;
-      if (mi < k && j0 + jj < m)
-        part[(((int64_t)s * nsplit + sp) * KMAX + mi) * m + j0 + jj] =
-            red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid];
-    }
-    __syncthreads();
-  }
-}
-
-// Same partial sums with coalesced row reads: a group of JW lanes (lane = interface column j)
+// Partial sums of (Z^T A^(s)T x)[r][j] with coalesced row reads: a group of JW lanes (lane = interface column j)
 // takes (node, multiplier) incidences of the occurrence one at a time, reads the signed
 // multiplier row (JW consecutive doubles), turns it into the pattern frame (O^T) and accumulates
 // the k mode products Z[bn]^T x_loc in registers; the 256/JW groups are summed through LDS at
 // the end.  The incidences of a slice of boundary nodes are one contiguous run of the slot
 // lists, so a group walks them four at a time with all their loads issued together (no
 // per-node chain of dependent loads).  Workgroup (s, sp) covers a slice of the boundary nodes
-// of occurrence s.
+// of occurrence s.  JW is the least power of two that holds the columns, up to 16: few columns get more
+// groups (27 occurrences of 296 nodes and 3 columns: 18 us with 16-column tiles of MFMA before).
 constexpr int GT_MAX_NODES = 128;  // boundary nodes per slice of k_coarse_gt_rows (host-enforced)
 template <int DPN, int JW>
 __global__ __launch_bounds__(256) void k_coarse_gt_rows(const int* occ_pat, const int* slot_off, const int* nbn_p,
@@ -260,14 +198,21 @@ __global__ __launch_bounds__(256) void k_coarse_gt_rows(const int* occ_pat, cons
 #pragma unroll
     for (int r = 0; r < KMAX; ++r) red[g][r][jl] = acc[r];
     __syncthreads();
-    for (int i = tid; i < KMAX * JW; i += 256) {
-      const int r = i / JW, jj = i % JW;
-      if (r < k && j0 + jj < m) {
-        double v = 0.0;
-        for (int gg = 0; gg < NG; ++gg) v += red[gg][r][jj];
-        part[(((int64_t)s * nsplit + sp) * KMAX + r) * m + j0 + jj] = v;
-      }
+    // eight groups to a thread, then those sums
+    constexpr int OUT = KMAX * JW, PARTS = 256 / OUT;
+    static_assert(NG == 8 * PARTS, "eight groups a thread");
+    const int r = (tid % OUT) / JW, jj = tid % JW, h = tid / OUT;
+    double v = 0.0;
+#pragma unroll
+    for (int gg = 0; gg < 8; ++gg) v += red[h * 8 + gg][r][jj];
+    if (PARTS > 1) {
+      __syncthreads();
+      red[h][r][jj] = v;
+      __syncthreads();
+      if (h == 0)
+        for (int q = 1; q < PARTS; ++q) v += red[q][r][jj];
     }
+    if (h == 0 && r < k && j0 + jj < m) part[(((int64_t)s * nsplit + sp) * KMAX + r) * m + j0 + jj] = v;
     __syncthreads();
   }
 }
@@ -735,7 +680,8 @@ F64Plan plan_F64(rpf_problem pb, const rpf_pattern* pats, int m, const Schedule&
   // - several small patterns: one grouped launch of 64 x 64 tiles (the uneven three-pattern batch at 8
   //   columns: 45 us an application against 82 us in a launch per pattern);
   // - a small pattern with few columns: the product for few columns, which waits for memory a few times
-  //   instead of once per 16 k (51 rows and 12 columns: 4 us against 7.6);
+  //   instead of once per 16 k (51 rows and 12 columns: 2.4 us against 7.6; 888
+  //   rows and 81 columns: see below for both sides);
   // - where the 128 x 128 tiles of the large-problem kernel, times K pieces of at least 256, fill
   //   three quarters of the 256 CUs or more: that kernel, with the number of pieces that leaves
   //   the last round fullest (2,598 rows and 512 columns: see below for both sides); its W blocks
@@ -763,7 +709,7 @@ F64Plan plan_F64(rpf_problem pb, const rpf_pattern* pats, int m, const Schedule&
       pl.alloc_sp[p] = sp;
       pl.kchunk[p] = 0;
       const int64_t tiles128 = cdiv(nb, 128) * cdiv(cols, (int64_t)128);
-      if (use.tile == 0 && !narrow && cols <= 96 && nb <= 512) {
+      if (use.tile == 0 && !narrow && cols <= 96 && nb <= 1024) {
         pl.nsp[p] = pl.alloc_sp[p] = 1;
         pl.few[p] = 1;
       } else if (use.tile == 256 && nb % 2 == 0) {
@@ -1075,34 +1021,28 @@ void coarse_gt(rpf_problem pb, const double* x, int64_t ldx, int m, double* c, h
   const int max_nbn = *std::max_element(pb->pat_nbn.begin(), pb->pat_nbn.end());
   const int max_nd = max_nbn * pb->dpn;
   int nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(cdiv(1024, pb->n_occ), cdiv(max_nd, 256)));
-  if (m >= 8) nsplit = std::max<int>(nsplit, (int)cdiv(max_nbn, GT_MAX_NODES));
+  nsplit = std::max<int>(nsplit, (int)cdiv(max_nbn, GT_MAX_NODES));
   pb->cpart.ensure((size_t)pb->n_occ * nsplit * KMAX * m);
   const double* rot = pb->has_rot ? pb->d_rot.p : nullptr;
-  if (m >= 8) {
-    // lanes over interface columns, coalesced row reads
 #define RPF_CGR(D, JW)                                                                                            \
   hipLaunchKernelGGL((k_coarse_gt_rows<D, JW>), dim3(pb->n_occ, nsplit), dim3(256), 0, s, pb->d_occ_pat.p,         \
                      pb->d_slot_off.p, pb->d_nbn.p, pb->d_Zp.p, pb->d_kp.p, pb->d_l2m_ptr.p, pb->d_l2m_code.p,      \
                      pb->d_l2m_bn.p, rot, x, ldx, m, nsplit, pb->cpart.p)
-    const bool w16 = m > 8;
-    switch (pb->dpn) {
-      case 1: if (w16) RPF_CGR(1, 16); else RPF_CGR(1, 8); break;
-      case 2: if (w16) RPF_CGR(2, 16); else RPF_CGR(2, 8); break;
-      default: if (w16) RPF_CGR(3, 16); else RPF_CGR(3, 8);
-    }
-#undef RPF_CGR
-  } else {
-#define RPF_CGT(D)                                                                                             \
-  hipLaunchKernelGGL(k_coarse_gt<D>, dim3(pb->n_occ, nsplit), dim3(256), 0, s, pb->d_occ_pat.p, pb->d_slot_off.p, \
-                     pb->d_nbn.p, pb->d_Zp.p, pb->d_kp.p, pb->d_goff.p, pb->d_l2m_ptr.p, pb->d_l2m_code.p,      \
-                     rot, x, ldx, m, nsplit, pb->cpart.p)
-    switch (pb->dpn) {
-      case 1: RPF_CGT(1); break;
-      case 2: RPF_CGT(2); break;
-      default: RPF_CGT(3);
-    }
-#undef RPF_CGT
+#define RPF_CGD(D)                   \
+  do {                               \
+    if (m > 8) RPF_CGR(D, 16);       \
+    else if (m > 4) RPF_CGR(D, 8);   \
+    else if (m > 2) RPF_CGR(D, 4);   \
+    else if (m > 1) RPF_CGR(D, 2);   \
+    else RPF_CGR(D, 1);              \
+  } while (0)
+  switch (pb->dpn) {
+    case 1: RPF_CGD(1); break;
+    case 2: RPF_CGD(2); break;
+    default: RPF_CGD(3);
   }
+#undef RPF_CGD
+#undef RPF_CGR
   RPF_LAUNCH_CHECK();
   const int64_t tot = (int64_t)pb->n_occ * KMAX * m;
   hipLaunchKernelGGL(k_coarse_gt_reduce, dim3((unsigned)cdiv(tot, 256)), dim3(256), 0, s, pb->n_occ, nsplit,

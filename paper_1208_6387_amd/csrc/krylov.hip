@@ -307,13 +307,15 @@ struct Solver {
     rpf::gram(s, N, a, b, X, ldx, Y, ldy, C, ws.p);
   }
 
-  // lagged convergence check: the norms of iteration i are copied to pinned memory and read
-  // while iteration i+1 is already queued, so the host never drains the stream mid-solve
-  // Each slot holds the nr x nr Gram of the residual and, after it, the "exhausted" flag that
-  // k_make_T raises when a whole block was dropped.
+  // lagged convergence check: the norms of iteration i are read from pinned memory while iteration i+1 is
+  // already queued, so the host never drains the stream mid-solve.  Each slot holds the nr x nr Gram of
+  // the residual (or its diagonal) and, after it, the "exhausted" flag that block_coef raises when
+  // a whole block was dropped.  Where the residual update leaves the norms, it writes the pinned
+  // slot itself (a copy costs 10 us of host time and a kernel); a captured batch writes a device
+  // slot, which is copied after the replay.
   double* hnorm = nullptr;  // pinned, 2 slots of nr*nr + 1
   hipEvent_t nev[2] = {nullptr, nullptr};
-  DevBuf<double> nrm2[2];
+  DevBuf<double> nrm2[2], raised;
 
   size_t slot_len() const { return (size_t)nr * nr + 1; }
   void init_lag() {
@@ -324,22 +326,25 @@ struct Solver {
     }
     for (int k = 0; k < 2; ++k) {
       nrm2[k].ensure(slot_len());
-      fill(s, nrm2[k].p + (size_t)nr * nr, 1, 0.0);
     }
+    raised.ensure(1);
+    fill(s, raised.p, 1, 0.0);
   }
-  // have_sq: the diagonal of nrm2[slot] already holds the squared residual norms
-  void post_norms(const double* X, int slot, bool have_sq = false) {
-    if (!have_sq) gram(X, nr, nr, X, nr, nr, nrm2[slot].p);
-    RPF_HIP(hipMemcpyAsync(hnorm + (size_t)slot * slot_len(), nrm2[slot].p, sizeof(double) * slot_len(),
-                           hipMemcpyDeviceToHost, s));
-    RPF_HIP(hipEventRecord(nev[slot], s));
-  }
-  // norms held in device slot dslot, copied to host slot hslot
+  double* host_slot(int slot) const { return hnorm + (size_t)slot * slot_len(); }
+  // the norms of X, formed in device slot dslot unless have_sq says that they are there, to pinned slot
+  // hslot
   void post_norms_from(const double* X, int dslot, int hslot, bool have_sq) {
-    if (!have_sq) gram(X, nr, nr, X, nr, nr, nrm2[dslot].p);
-    RPF_HIP(hipMemcpyAsync(hnorm + (size_t)hslot * slot_len(), nrm2[dslot].p, sizeof(double) * slot_len(),
-                           hipMemcpyDeviceToHost, s));
+    if (!have_sq) {
+      gram(X, nr, nr, X, nr, nr, nrm2[dslot].p);
+      copy_matrix(s, raised.p, 1, nrm2[dslot].p + (size_t)nr * nr, 1, 1, 1);
+    }
+    RPF_HIP(hipMemcpyAsync(host_slot(hslot), nrm2[dslot].p, sizeof(double) * slot_len(), hipMemcpyDeviceToHost, s));
     RPF_HIP(hipEventRecord(nev[hslot], s));
+  }
+  // after an iteration that was given the pinned slot itself (and filled it where have_sq)
+  void post_norms(const double* X, int slot, bool have_sq) {
+    if (have_sq) RPF_HIP(hipEventRecord(nev[slot], s));
+    else post_norms_from(X, slot, slot, false);
   }
   // captured batches of iterations: one graph for block CG and classical, one per starting place
   // in the restart cycle for ORTHODIR (keyed by that place)
@@ -579,8 +584,8 @@ struct Solver {
       double* zr = eta.p + (int64_t)m * m;
       double* Tj = Tall.p + (int64_t)slot * m * m;
       // T, and alpha = W^T R = T^T (Z^T R); gamma = T alpha; lambda += Z gamma; R -= P gamma
-      block_coef(s, m, nr, eta.p, zr, diag_only, nb * m, Bt.p, tau, Tj, drops.p, nrm2[0].p + (size_t)nr * nr,
-                 nrm2[1].p + (size_t)nr * nr, alpha.p, upd_gram ? alpha_prev.p : nullptr);
+      block_coef(s, m, nr, eta.p, zr, diag_only, nb * m, Bt.p, tau, Tj, drops.p, raised.p, alpha.p,
+                 upd_gram ? alpha_prev.p : nullptr);
       // the residual update also returns the squared column norms (into the check slot)
       bool have_sq = false;
       have_gram = false;
@@ -590,13 +595,13 @@ struct Solver {
         lam_pending = true;
         lam_dir = Zs;
         have_gram = rows_update_gram(s, N, m, nr, alpha.p, Ps, ldW, -1.0, 1.0, Rs.p, nr, check ? nrm_out : nullptr,
-                                     nr + 1, gpart.p, Tj, diag_only, Bt.p, Mo.p);
+                                     nr + 1, gpart.p, Tj, diag_only, raised.p, Bt.p, Mo.p);
         RPF_CHECK(have_gram, RPF_EINVAL, "block step: residual update shape");
         have_sq = check;
       } else {
         sqpart.ensure((size_t)cdiv(N, 256) * nr);
         have_sq = check && rows_gemm2_sq(s, N, m, nr, alpha.p, 1.0, Zs, ldW, 1.0, dlam.p, nr, -1.0, Ps, ldW, 1.0,
-                                         Rs.p, nr, sqpart.p, nrm_out, nr + 1);
+                                         Rs.p, nr, sqpart.p, raised.p, nrm_out, nr + 1);
         if (!have_sq)
           rows_gemm2(s, N, m, nr, alpha.p, 0, 1.0, Zs, ldW, 1.0, dlam.p, nr, -1.0, Ps, ldW, 1.0, Rs.p, nr);
       }
@@ -686,7 +691,7 @@ struct Solver {
       }
       const bool check = (it + 1) % check_every == 0 || it + 1 == max_it;
       const int slot_n = nchk & 1;
-      const bool have_sq = step(it, check, nrm2[slot_n].p);
+      const bool have_sq = step(it, check, host_slot(slot_n));
       ++it;
       if (check) {
         post_norms(Rs.p, slot_n, have_sq);
