@@ -726,13 +726,14 @@ void gram(hipStream_t s, int64_t N, int a, int b, const double* X, int64_t ldx, 
   const int64_t chunk = cdiv(N, g);
   const int gz = (int)cdiv(N, chunk);
   RPF_CHECK(gz <= 65535, RPF_EINVAL, "gram: too many chunks");
+  double* part = gz == 1 ? C : ws;  // a single chunk's partial sums are the result
   if (gram_is_wide(a)) {
     const WideShape w = wide_shape(a);
     const dim3 grid((unsigned)(w.ga * cdiv(b, 16)), (unsigned)gz);
     switch (w.tw) {
 #define RPF_WIDE(TW)                                                                                         \
   case TW:                                                                                                   \
-    hipLaunchKernelGGL(k_gram_wide<TW>, grid, dim3(256), 0, s, N, a, b, X, ldx, Y, ldy, chunk, w.ga, w.wt, ws); \
+    hipLaunchKernelGGL(k_gram_wide<TW>, grid, dim3(256), 0, s, N, a, b, X, ldx, Y, ldy, chunk, w.ga, w.wt, part); \
     break;
       RPF_WIDE(5) RPF_WIDE(6) RPF_WIDE(7) RPF_WIDE(8)
 #undef RPF_WIDE
@@ -742,9 +743,10 @@ void gram(hipStream_t s, int64_t N, int a, int b, const double* X, int64_t ldx, 
   } else {
     const int64_t tiles = cdiv(a, 16) * cdiv(b, 16);
     hipLaunchKernelGGL(k_gram_partial, dim3((unsigned)tiles, (unsigned)gz), dim3(256), 0, s, N, a, b, X, ldx, Y,
-                       ldy, chunk, ws);
+                       ldy, chunk, part);
   }
   RPF_LAUNCH_CHECK();
+  if (gz == 1) return;
   hipLaunchKernelGGL(k_splitk_reduce, dim3((unsigned)cdiv((int64_t)a * b, 16)), dim3(256), 0, s, (int64_t)a,
                      (int64_t)b, gz, ws, 0.0, C, (int64_t)a);
   RPF_LAUNCH_CHECK();
@@ -767,9 +769,11 @@ void gram_pair(hipStream_t s, int64_t N, int a, const double* X, int64_t ldx, in
   }
   const int64_t chunk = gram_pair_rows(N);
   const int gz = gram_pair_chunks(N);
+  // a single chunk's partial sums are the result
   hipLaunchKernelGGL(k_gram_pair, dim3((unsigned)gz), dim3(256), 0, s, N, a, X, ldx, b1, Y1, ldy1, b2, Y2, ldy2,
-                     chunk, ws);
+                     chunk, gz == 1 ? C : ws);
   RPF_LAUNCH_CHECK();
+  if (gz == 1) return;
   hipLaunchKernelGGL(k_splitk_reduce, dim3((unsigned)cdiv((int64_t)a * (b1 + b2), 16)), dim3(256), 0, s, (int64_t)a,
                      (int64_t)(b1 + b2), gz, ws, 0.0, C, (int64_t)a);
   RPF_LAUNCH_CHECK();
@@ -1001,6 +1005,9 @@ struct RowsPair {
 struct RowsPairs {
   RowsPair p[2];
   double* colsq;  // optional: per-workgroup column sums of squares of pair 1's output (k_rows_tile)
+  double* sq;     // optional, one workgroup of rows: those sums at their place, stride ldsq, and *raised after
+  int64_t ldsq;   // the b x b entries
+  const double* raised;
 };
 
 __global__ __launch_bounds__(256) void k_rows_small(int64_t N, int a, int b, const double* Mm, int64_t mrow,
@@ -1149,7 +1156,12 @@ __global__ __launch_bounds__(256) void k_rows_tile(int64_t N, int a, int b, cons
       double q = 0.0;
 #pragma unroll
       for (int k = 0; k < 16; ++k) q += red[tid + 16 * k];
-      pr.colsq[(int64_t)blockIdx.x * b + tid] = q;
+      if (pr.sq) {
+        pr.sq[tid * pr.ldsq] = q;
+        if (tid == 0) pr.sq[b * b] = *pr.raised;
+      } else {
+        pr.colsq[(int64_t)blockIdx.x * b + tid] = q;
+      }
     }
   }
 }
@@ -1361,8 +1373,14 @@ bool rows_gemm2_sq(hipStream_t s, int64_t N, int a, int b, const double* M, doub
   pr.p[1] = {X2, Y2, ldx2, ldy2, alpha2, beta2, nullptr, 0};
   pr.colsq = part;
   const unsigned nwg = (unsigned)cdiv(N, 256);
+  if (nwg == 1) {
+    pr.sq = sq;
+    pr.ldsq = ldsq;
+    pr.raised = raised;
+  }
   hipLaunchKernelGGL(k_rows_tile, dim3(nwg, 2), dim3(256), 0, s, N, a, b, M, (int64_t)0, pr);
   RPF_LAUNCH_CHECK();
+  if (nwg == 1) return true;
   // sq[c * ldsq] = sum over workgroups of part[wg * b + c]
   hipLaunchKernelGGL(k_colsum, dim3((unsigned)b), dim3(256), 0, s, (int)nwg, b, part, raised, sq, ldsq);
   RPF_LAUNCH_CHECK();
@@ -2269,21 +2287,21 @@ void build_tri_inv(hipStream_t s, const double* L, int64_t ldl, int64_t n, const
 }
 
 // C (M x c) = beta C + alpha op(A) X with few columns (16 per workgroup): a workgroup takes
-// 16 R rows, its four waves a quarter of K each, 32 k at a time with the next 32 on their way, and the
-// four partial results are added in LDS.  TA: op(A) = A^T, A stored K x M.  X(k, j) is X[k xk + j xj], C(m, j)
+// 16 R rows, its W waves a part of K each, 32 k at a time with the next 32 on their way, and the
+// W partial results are added in LDS.  TA: op(A) = A^T, A stored K x M.  X(k, j) is X[k xk + j xj], C(m, j)
 // is C[m cm + j cj].  A walk over a 512-row block
 // is four load latencies a wave (5 us at 6,700 rows and 8 columns), where the general product has 32
 // dependent k-stages of 16 (14 to 17 us at K = 128 alone).
-template <bool TA, int R>
-__global__ __launch_bounds__(256) void k_skinny(int64_t M, int64_t c, int64_t K, double alpha, const double* A,
+template <bool TA, int R, int W>
+__global__ __launch_bounds__(64 * W) void k_skinny(int64_t M, int64_t c, int64_t K, double alpha, const double* A,
                                                 int64_t lda, const double* X, int64_t xk, int64_t xj, double beta,
                                                 double* C, int64_t cm, int64_t cj) {
   constexpr int U = 8;  // MFMA steps of a batch
-  __shared__ double red[4][16 * R][17];
+  __shared__ double red[W][16 * R][17];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int fl = lane & 15, fk = lane >> 4;
   const int64_t m0 = (int64_t)blockIdx.x * 16 * R, c0 = (int64_t)blockIdx.y * 16;
-  const int64_t kc = (K + 31) / 32 * 8;  // a wave's quarter
+  const int64_t kc = (K + 8 * W - 1) / (8 * W) * 8;  // a wave's part
   const int64_t kb = min(w * kc, K), ke = min(kb + kc, K);
   const double* Xc = X + min(c0 + fl, c - 1) * xj;
   const double* Ar[R];
@@ -2331,29 +2349,40 @@ __global__ __launch_bounds__(256) void k_skinny(int64_t M, int64_t c, int64_t K,
 #pragma unroll
     for (int r = 0; r < 4; ++r) red[w][16 * i + fl][fk + 4 * r] = acc[i][r];
   __syncthreads();
-#pragma unroll
-  for (int u = 0; u < R; ++u) {
-    const int row = tid & (16 * R - 1), col = (tid / (16 * R)) + u * (256 / (16 * R));
+  for (int e = tid; e < 256 * R; e += 64 * W) {
+    const int row = e & (16 * R - 1), col = e / (16 * R);
     if (m0 + row < M && c0 + col < c) {
-      const double v = alpha * (red[0][row][col] + red[1][row][col] + red[2][row][col] + red[3][row][col]);
+      double v = red[0][row][col];
+#pragma unroll
+      for (int q = 1; q < W; ++q) v += red[q][row][col];
+      v *= alpha;
       double* o = C + (c0 + col) * cj + (m0 + row) * cm;
       *o = beta == 0.0 ? v : v + beta * *o;
     }
   }
 }
 
-// two row tiles a workgroup where that still gives every CU one
+// Two row tiles a workgroup where that still gives every CU one; else the waves that leave each about 64 k
+// (n_G = 3,072, 16 columns: 33 us with four waves)
 static void launch_skinny(hipStream_t s, bool ta, int64_t M, int64_t c, int64_t K, double alpha, const double* A,
                           int64_t lda, const double* X, int64_t xk, int64_t xj, double beta, double* C, int64_t cm,
                           int64_t cj) {
   const bool two = cdiv(M, 32) * cdiv(c, 16) >= 256;
+  const int w = two || K < 256 ? 4 : K < 1024 ? 8 : 16;
   const dim3 g((unsigned)cdiv(M, two ? 32 : 16), (unsigned)cdiv(c, 16));
-#define RPF_SK(TA, R) \
-  RPF_TIMED_LAUNCH((k_skinny<TA, R>), g, dim3(256), 0, s, M, c, K, alpha, A, lda, X, xk, xj, beta, C, cm, cj)
-  if (ta && two) RPF_SK(true, 2);
-  else if (ta) RPF_SK(true, 1);
-  else if (two) RPF_SK(false, 2);
-  else RPF_SK(false, 1);
+#define RPF_SK(TA, R, W) \
+  RPF_TIMED_LAUNCH((k_skinny<TA, R, W>), g, dim3(64 * W), 0, s, M, c, K, alpha, A, lda, X, xk, xj, beta, C, cm, cj)
+  if (ta) {
+    if (two) RPF_SK(true, 2, 4);
+    else if (w == 4) RPF_SK(true, 1, 4);
+    else if (w == 8) RPF_SK(true, 1, 8);
+    else RPF_SK(true, 1, 16);
+  } else {
+    if (two) RPF_SK(false, 2, 4);
+    else if (w == 4) RPF_SK(false, 1, 4);
+    else if (w == 8) RPF_SK(false, 1, 8);
+    else RPF_SK(false, 1, 16);
+  }
 #undef RPF_SK
   RPF_LAUNCH_CHECK();
 }

@@ -91,7 +91,7 @@ __global__ __launch_bounds__(256) void k_coarse_gt_rows(const int* occ_pat, cons
                                                         const double* const* Zp, const int* kp, const int* l2m_ptr,
                                                         const int* l2m_code, const int* l2m_bn, const double* rot,
                                                         const double* x, int64_t ldx, int m, int nsplit,
-                                                        double* part) {
+                                                        double* part, const int* goff, double* c) {
   constexpr int NG = 256 / JW;
   __shared__ double red[NG][KMAX][JW];
   // the slice's mode rows, zl[(bn - n_beg) DPN KMAX + c KMAX + r] = Z[r][bn DPN + c] (zero for r >= k)
@@ -212,7 +212,10 @@ __global__ __launch_bounds__(256) void k_coarse_gt_rows(const int* occ_pat, cons
       if (h == 0)
         for (int q = 1; q < PARTS; ++q) v += red[q][r][jj];
     }
-    if (h == 0 && r < k && j0 + jj < m) part[(((int64_t)s * nsplit + sp) * KMAX + r) * m + j0 + jj] = v;
+    if (h == 0 && r < k && j0 + jj < m) {
+      if (nsplit == 1) c[((int64_t)goff[s] + r) * m + j0 + jj] = v;  // no other slices to add
+      else part[(((int64_t)s * nsplit + sp) * KMAX + r) * m + j0 + jj] = v;
+    }
     __syncthreads();
   }
 }
@@ -382,10 +385,24 @@ __global__ void k_build_grows(int n_mult, int km, const int* ep_occ, const int* 
 // x = beta x + alpha G y from the stored rows of G: one thread per (multiplier, JQ consecutive
 // columns).  With JQ = 4 (m a multiple of 4, 16-byte aligned rows) the G rows of a multiplier
 // are read by 4 threads instead of m and the x and y accesses are 16-byte vectors.
-template <int DPN, int KM, int JQ>
+// SOLVE: y holds c = G^T x and every workgroup first forms (G^T G)^{-1} c itself (n_G m at most SMALL_COARSE):
+// a launch less per projection, which a small structure's iteration consists of.
+constexpr int SMALL_COARSE = 256;
+template <int DPN, int KM, int JQ, bool SOLVE = false>
 __global__ __launch_bounds__(256) void k_coarse_g_rows(int n_mult, const double* Grow, const int* ep_goff, int nG,
                                                        const double* y, int m, double alpha, double* x, int64_t ldx,
-                                                       double beta) {
+                                                       double beta, const double* inv) {
+  __shared__ double ys[SOLVE ? SMALL_COARSE : 1];
+  if (SOLVE) {
+    for (int i = threadIdx.x; i < nG * m; i += 256) {
+      const int r = i / m, j = i % m;
+      double v = 0.0;
+      for (int k = 0; k < nG; ++k) v += inv[(int64_t)k * nG + r] * y[(int64_t)k * m + j];
+      ys[i] = v;
+    }
+    __syncthreads();
+    y = ys;
+  }
   const int mq = m / JQ;
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (int64_t)n_mult * mq) return;
@@ -602,16 +619,23 @@ __global__ void k_zero_rows(double* X, int64_t ld, int nb, int64_t cols) {
 }
 
 void gather_pattern(rpf_problem pb, int p, int nbn, const double* lam, int64_t ldl, int m, double* X,
-                    int64_t ldx, hipStream_t s) {
+                    int64_t ldx, hipStream_t s, int pad) {
   const int nq = (int)pb->occ_of_pat[p].size();
   if (nq == 0 || nbn == 0) return;
+  const bool by_rows = !pb->weighted && m >= 8 && nbn == pb->pat_nbn[p];
+  if (pad > 0 && !by_rows) {
+    const int64_t cols = (int64_t)nq * m;
+    const int nb = nbn * pb->dpn;
+    hipLaunchKernelGGL(k_zero_rows, dim3((unsigned)cdiv(pad * cols, 256)), dim3(256), 0, s, X, ldx, nb, cols);
+    RPF_LAUNCH_CHECK();
+  }
   if (pb->weighted) {
     RPF_CHECK(nbn == pb->pat_nbn[p], RPF_EINVAL, "gather: partial boundary with a non-Boolean assembly");
     wgather(pb, p, lam, ldl, m, 2, X, nullptr, nullptr, nullptr, ldx, s);
     return;
   }
-  if (m >= 8 && nbn == pb->pat_nbn[p]) {
-    gather_rows(pb, p, lam, ldl, m, 2, X, nullptr, nullptr, nullptr, ldx, s);
+  if (by_rows) {
+    gather_rows(pb, p, lam, ldl, m, 2, X, nullptr, nullptr, nullptr, ldx, s, pad);
     return;
   }
   dim3 grid((unsigned)cdiv(nbn, 128), (unsigned)nq);
@@ -681,10 +705,10 @@ F64Plan plan_F64(rpf_problem pb, const rpf_pattern* pats, int m, const Schedule&
   //   columns: 45 us an application against 82 us in a launch per pattern);
   // - a small pattern with few columns: the product for few columns, which waits for memory a few times
   //   instead of once per 16 k (51 rows and 12 columns: 2.4 us against 7.6; 888
-  //   rows and 81 columns: see below for both sides);
+  //   rows and 81 columns: 10 us against 23);
   // - where the 128 x 128 tiles of the large-problem kernel, times K pieces of at least 256, fill
   //   three quarters of the 256 CUs or more: that kernel, with the number of pieces that leaves
-  //   the last round fullest (2,598 rows and 512 columns: see below for both sides); its W blocks
+  //   the last round fullest (2,598 rows and 512 columns: 127 us against 201); its W blocks
   //   have their leading dimension padded to a multiple of 32 with zero rows;
   // - else 64 x 64 tiles with K split until there are about four workgroups per CU.
   constexpr int CUS = 256;
@@ -770,12 +794,7 @@ YLoc run_F64(rpf_problem pb, const rpf_pattern* pats, const F64Plan& pl, int m, 
     double* xp = xw + pl.off[p];
     double* yp = yw + pl.yoff[p];
     const int64_t lw = pl.ldw[p];
-    if (lw > nb) {
-      const int64_t npad = (lw - nb) * cols;
-      hipLaunchKernelGGL(k_zero_rows, dim3((unsigned)cdiv(npad, 256)), dim3(256), 0, s, xp, lw, nb, cols);
-      RPF_LAUNCH_CHECK();
-    }
-    gather_pattern(pb, p, pb->pat_nbn[p], X, ldx, m, xp, lw, s);
+    gather_pattern(pb, p, pb->pat_nbn[p], X, ldx, m, xp, lw, s, (int)(lw - nb));
     if (gsub) rsub_cols(s, nb, cols, gsub[p], nb, xp, lw);
     const double* Mp = op == OP_FLEX ? pats[p]->Splus.p : pats[p]->S.p;
     yl.base[p] = yp;
@@ -1027,7 +1046,7 @@ void coarse_gt(rpf_problem pb, const double* x, int64_t ldx, int m, double* c, h
 #define RPF_CGR(D, JW)                                                                                            \
   hipLaunchKernelGGL((k_coarse_gt_rows<D, JW>), dim3(pb->n_occ, nsplit), dim3(256), 0, s, pb->d_occ_pat.p,         \
                      pb->d_slot_off.p, pb->d_nbn.p, pb->d_Zp.p, pb->d_kp.p, pb->d_l2m_ptr.p, pb->d_l2m_code.p,      \
-                     pb->d_l2m_bn.p, rot, x, ldx, m, nsplit, pb->cpart.p)
+                     pb->d_l2m_bn.p, rot, x, ldx, m, nsplit, pb->cpart.p, pb->d_goff.p, c)
 #define RPF_CGD(D)                   \
   do {                               \
     if (m > 8) RPF_CGR(D, 16);       \
@@ -1044,26 +1063,31 @@ void coarse_gt(rpf_problem pb, const double* x, int64_t ldx, int m, double* c, h
 #undef RPF_CGD
 #undef RPF_CGR
   RPF_LAUNCH_CHECK();
+  if (nsplit == 1) return;
   const int64_t tot = (int64_t)pb->n_occ * KMAX * m;
   hipLaunchKernelGGL(k_coarse_gt_reduce, dim3((unsigned)cdiv(tot, 256)), dim3(256), 0, s, pb->n_occ, nsplit,
                      pb->d_occ_pat.p, pb->d_kp.p, pb->d_goff.p, m, pb->cpart.p, c);
   RPF_LAUNCH_CHECK();
 }
 
-void coarse_g(rpf_problem pb, const double* y, int m, double alpha, double* x, int64_t ldx, double beta,
-              hipStream_t s) {
+// inv: NULL, or y holds c and y = inv c is formed on the way (small coarse spaces with stored rows of G)
+static void coarse_g_from(rpf_problem pb, const double* y, const double* inv, int m, double alpha, double* x,
+                          int64_t ldx, double beta, hipStream_t s) {
   if (pb->n_mult == 0) return;
   dim3 grid((unsigned)cdiv((int64_t)pb->n_mult * m, 256));
   if (pb->d_grow.p && pb->g_km > 0) {
     const bool quad = m % 4 == 0 && ldx % 2 == 0 && ((uintptr_t)x & 15) == 0 && ((uintptr_t)y & 15) == 0;
     dim3 gq((unsigned)cdiv((int64_t)pb->n_mult * (m / 4), 256));
 #define RPF_CGR(D, KM)                                                                                            \
-  if (quad)                                                                                                       \
+  if (inv)                                                                                                        \
+    hipLaunchKernelGGL((k_coarse_g_rows<D, KM, 1, true>), grid, dim3(256), 0, s, pb->n_mult, pb->d_grow.p,       \
+                       pb->d_ep_goff.p, pb->n_G, y, m, alpha, x, ldx, beta, inv);                                 \
+  else if (quad)                                                                                                  \
     hipLaunchKernelGGL((k_coarse_g_rows<D, KM, 4>), gq, dim3(256), 0, s, pb->n_mult, pb->d_grow.p,               \
-                       pb->d_ep_goff.p, pb->n_G, y, m, alpha, x, ldx, beta);                                      \
+                       pb->d_ep_goff.p, pb->n_G, y, m, alpha, x, ldx, beta, inv);                                 \
   else                                                                                                            \
     hipLaunchKernelGGL((k_coarse_g_rows<D, KM, 1>), grid, dim3(256), 0, s, pb->n_mult, pb->d_grow.p,             \
-                       pb->d_ep_goff.p, pb->n_G, y, m, alpha, x, ldx, beta)
+                       pb->d_ep_goff.p, pb->n_G, y, m, alpha, x, ldx, beta, inv)
 #define RPF_CGK(D)                                       \
   switch (pb->g_km) {                                     \
     case 1: RPF_CGR(D, 1); break;                         \
@@ -1102,12 +1126,21 @@ void coarse_g(rpf_problem pb, const double* y, int m, double alpha, double* x, i
   RPF_LAUNCH_CHECK();
 }
 
+void coarse_g(rpf_problem pb, const double* y, int m, double alpha, double* x, int64_t ldx, double beta,
+              hipStream_t s) {
+  coarse_g_from(pb, y, nullptr, m, alpha, x, ldx, beta, s);
+}
+
 void project_block(rpf_problem pb, double* x, int64_t ldx, int m, hipStream_t s) {
   const int nG = pb->n_G;
   if (nG == 0) return;
   pb->cbuf.ensure((size_t)nG * m);
   pb->ybuf.ensure((size_t)nG * m);
   coarse_gt(pb, x, ldx, m, pb->cbuf.p, s);
+  if ((int64_t)nG * m <= SMALL_COARSE && pb->d_grow.p && pb->g_km > 0) {
+    coarse_g_from(pb, pb->cbuf.p, pb->Ginv.p, m, -1.0, x, ldx, 1.0, s);
+    return;
+  }
   coarse_solve(pb, pb->cbuf.p, pb->ybuf.p, m, s);
   coarse_g(pb, pb->ybuf.p, m, -1.0, x, ldx, 1.0, s);
 }

@@ -82,7 +82,7 @@ template <int DPN, int MODE, int JW>
 __global__ __launch_bounds__(256) void k_gather_rows(int nbn, const int* occ_list, const int* slot_off,
                                                      const int* l2m_ptr, const int* l2m_code, const double* rot,
                                                      const double* lam, int64_t ldl, int m, double* X64, float* Xf,
-                                                     uint16_t* Xh, uint16_t* Xl, int64_t ldx) {
+                                                     uint16_t* Xh, uint16_t* Xl, int64_t ldx, int pad) {
   constexpr int NG = 256 / JW, NBK = 64;
   constexpr int NPG = NBK / NG;  // nodes per lane group
   constexpr int UM = 2;          // incidences per node fetched in the batch (faces 1, edges 2, corners 3)
@@ -93,6 +93,19 @@ __global__ __launch_bounds__(256) void k_gather_rows(int nbn, const int* occ_lis
   const int nn = min(NBK, nbn - n0);
   const int tid = threadIdx.x, g = tid / JW, jl = tid % JW;
   const int base_slot = slot_off[s] + n0;
+  // the `pad` rows after the boundary: zeros
+  if (pad > 0 && blockIdx.x == gridDim.x - 1)
+    for (int e = tid; e < pad * m; e += 256) {
+      const int64_t o = ((int64_t)q * m + e / pad) * ldx + (int64_t)nbn * DPN + e % pad;
+      if (MODE == 2) {
+        X64[o] = 0.0;
+      } else if (MODE == 0) {
+        Xf[o] = 0.f;
+      } else {
+        Xh[o] = 0;
+        Xl[o] = 0;
+      }
+    }
   double O[9];
 #pragma unroll
   for (int i = 0; i < 9; ++i) O[i] = rot ? rot[9 * s + i] : ((i % 4 == 0) ? 1.0 : 0.0);
@@ -219,7 +232,7 @@ __global__ void k_zero_pad(uint16_t* Xh, uint16_t* Xl, int64_t ld, int nb, int c
 }
 
 void gather_rows(rpf_problem pb, int p, const double* lam, int64_t ldl, int m, int mode, double* X64, float* Xf,
-                 uint16_t* Xh, uint16_t* Xl, int64_t ldx, hipStream_t s) {
+                 uint16_t* Xh, uint16_t* Xl, int64_t ldx, hipStream_t s, int pad) {
   const int nq = (int)pb->occ_of_pat[p].size(), nbn = pb->pat_nbn[p];
   if (nq == 0 || nbn == 0) return;
   dim3 grid((unsigned)cdiv(nbn, 64), (unsigned)nq);
@@ -228,7 +241,7 @@ void gather_rows(rpf_problem pb, int p, const double* lam, int64_t ldl, int m, i
   const bool w16 = m > 8;
 #define RPF_GR(D, MD, JW)                                                                                     \
   hipLaunchKernelGGL((k_gather_rows<D, MD, JW>), grid, dim3(256), 0, s, nbn, occ, pb->d_slot_off.p,             \
-                     pb->d_l2m_ptr.p, pb->d_l2m_code.p, rot, lam, ldl, m, X64, Xf, Xh, Xl, ldx)
+                     pb->d_l2m_ptr.p, pb->d_l2m_code.p, rot, lam, ldl, m, X64, Xf, Xh, Xl, ldx, pad)
 #define RPF_GRM(D)                                          \
   if (mode == 0) { if (w16) RPF_GR(D, 0, 16); else RPF_GR(D, 0, 8); } \
   else if (mode == 1) { if (w16) RPF_GR(D, 1, 16); else RPF_GR(D, 1, 8); } \
@@ -829,8 +842,10 @@ void apply_F_lowprec(rpf_problem pb, const rpf_pattern* pats, int m, const doubl
   hipLaunchKernelGGL((k_gather_lp<D, MODE>), grid, dim3(128), 0, s, nbn, occ, pb->d_slot_off.p, pb->d_l2m_ptr.p, \
                      pb->d_l2m_code.p, rot, X, ldx, m, pb->xloc32.p + off[p], pb->xhi.p + off[p],                 \
                      pb->xlo.p + off[p], ld[p])
-    // the padded rows between n_b and ld must hold zeros for the 16-byte loads
-    if (split && ld[p] != nb) {
+    // the padded rows between n_b and ld must hold zeros for the 16-byte loads (the gather by rows writes
+    // them itself)
+    const bool by_rows = !gsub && !pb->weighted && m >= 8;
+    if (split && ld[p] != nb && !by_rows) {
       const int64_t npad = (ld[p] - nb) * (int64_t)cols;
       hipLaunchKernelGGL(k_zero_pad, dim3((unsigned)cdiv(npad, 256)), dim3(256), 0, s, pb->xhi.p + off[p],
                          pb->xlo.p + off[p], ld[p], nb, cols);
@@ -848,7 +863,8 @@ void apply_F_lowprec(rpf_problem pb, const rpf_pattern* pats, int m, const doubl
       if (pb->weighted) {
         wgather(pb, p, X, ldx, m, 1, nullptr, nullptr, pb->xhi.p + off[p], pb->xlo.p + off[p], ld[p], s);
       } else if (m >= 8) {
-        gather_rows(pb, p, X, ldx, m, 1, nullptr, nullptr, pb->xhi.p + off[p], pb->xlo.p + off[p], ld[p], s);
+        gather_rows(pb, p, X, ldx, m, 1, nullptr, nullptr, pb->xhi.p + off[p], pb->xlo.p + off[p], ld[p], s,
+                    (int)(ld[p] - nb));
       } else {
         switch (pb->dpn) {
           case 1: RPF_GLP(1, 1); break;

@@ -185,7 +185,7 @@ void spmm_csr(hipStream_t s, int rows, int64_t cols, const int* ptr, const int* 
               const double* X, int64_t ldx, double alpha, double* Y, int64_t ldy, double beta);
 // A^(s)T gather of an interface block into the W format of pattern p
 void gather_pattern(rpf_problem pb, int p, int nbn, const double* lam, int64_t ldl, int m, double* X,
-                    int64_t ldx, hipStream_t s);
+                    int64_t ldx, hipStream_t s, int pad = 0);
 // Y = beta Y + sum_s A^(s) Y_loc
 void scatter_all(rpf_problem pb, const YLoc& yl, int m, double* Y, int64_t ldy, double beta, hipStream_t s);
 void ensure_coarse(rpf_problem pb, const rpf_pattern* pats, hipStream_t s);
@@ -211,7 +211,7 @@ void lambda0_M(rpf_problem pb, const rpf_pattern* pats, int kind, const double* 
 // Gather A^(s)T lam for every occurrence of pattern p into the W format (lanes over interface
 // columns; needs m >= 8 for full lanes).  mode 0: FP32 Xf, 1: bf16 hi/lo Xh/Xl, 2: FP64 X64.
 void gather_rows(rpf_problem pb, int p, const double* lam, int64_t ldl, int m, int mode, double* X64, float* Xf,
-                 uint16_t* Xh, uint16_t* Xl, int64_t ldx, hipStream_t s);
+                 uint16_t* Xh, uint16_t* Xl, int64_t ldx, hipStream_t s, int pad = 0);
 void apply_F_lowprec(rpf_problem pb, const rpf_pattern* pats, int m, const double* X, int64_t ldx, double* Y,
                      int64_t ldy, int prec, hipStream_t s, int op = OP_FLEX, const double* const* gsub = nullptr);
 // non-Boolean assembly: gather (mode 2 FP64, 0 FP32, 1 bf16 split), scatter from column-major
