@@ -841,10 +841,147 @@ YLoc run_F64(rpf_problem pb, const rpf_pattern* pats, const F64Plan& pl, int m, 
   return yl;
 }
 
+// ---------------------------------------------------------------------------- small structures
+constexpr int SMALL_ROWS = 1024, SMALL_NB = 96, SMALL_OCC = 64;
+struct SmallPats {
+  const double* M[MAXP];
+  int nb[MAXP];
+};
+
+// Y = sum_s A^(s) M A^(s)T X for a small structure in one launch, a workgroup per column: the gathered
+// boundary values of every occurrence, their products and the scattered sums all stand in LDS.  As three
+// launches it is three memory latencies and two launch gaps (2-D heat row of four: 14.8 us, in one launch 8.3).
+template <int DPN>
+__global__ __launch_bounds__(512) void k_apply_small(int n_occ, int n_slots, int n_mult, const int* slot_off,
+                                                     const int* occ_pat, const int* l2m_ptr, const int* l2m_code,
+                                                     const int* ep_q, const int* ep_occ, const int* ep_bn,
+                                                     const int8_t* ep_sign, const double* rot, SmallPats P,
+                                                     const double* X, int64_t ldx, double* Y, int64_t ldy) {
+  __shared__ double w[SMALL_ROWS], y[SMALL_ROWS];
+  __shared__ int so[SMALL_OCC], op[SMALL_OCC];
+  const int tid = threadIdx.x, j = blockIdx.x;
+  if (tid < n_occ) {
+    so[tid] = slot_off[tid];
+    op[tid] = occ_pat[tid];
+  }
+  __syncthreads();
+  auto occ_of = [&](int slot) {  // last occurrence that starts at or before the slot
+    int a = 0, b = n_occ - 1;
+    while (a < b) {
+      const int c = (a + b + 1) / 2;
+      if (so[c] <= slot) a = c;
+      else b = c - 1;
+    }
+    return a;
+  };
+  for (int i = tid; i < n_slots; i += 512) {
+    double acc[DPN];
+#pragma unroll
+    for (int c = 0; c < DPN; ++c) acc[c] = 0.0;
+    const int e1 = l2m_ptr[i + 1];
+    for (int e = l2m_ptr[i]; e < e1; ++e) {
+      const int code = l2m_code[e];
+      const double sg = (code & 1) ? -1.0 : 1.0;
+#pragma unroll
+      for (int c = 0; c < DPN; ++c) acc[c] += sg * X[((int64_t)(code >> 1) * DPN + c) * ldx + j];
+    }
+    if (DPN == 3 && rot) {
+      const double* O = rot + 9 * (int64_t)occ_of(i);
+#pragma unroll
+      for (int c = 0; c < DPN; ++c)
+        w[i * DPN + c] = O[c] * acc[0] + O[3 + c] * acc[1 % DPN] + O[6 + c] * acc[2 % DPN];
+    } else {
+#pragma unroll
+      for (int c = 0; c < DPN; ++c) w[i * DPN + c] = acc[c];
+    }
+  }
+  __syncthreads();
+  for (int r = tid; r < n_slots * DPN; r += 512) {
+    const int s = occ_of(r / DPN), base = so[s] * DPN, nb = P.nb[op[s]];
+    const double* M = P.M[op[s]] + (r - base);
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int k0 = 0; k0 < nb; k0 += 16) {  // 16 loads in flight: a batch is one memory latency
+      double v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = M[(int64_t)min(k0 + u, nb - 1) * nb];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) a[u & 3] += k0 + u < nb ? v[u] * w[base + min(k0 + u, nb - 1)] : 0.0;
+    }
+    y[r] = (a[0] + a[1]) + (a[2] + a[3]);
+  }
+  __syncthreads();
+  for (int t = tid; t < n_mult; t += 512) {
+    double acc[DPN];
+#pragma unroll
+    for (int c = 0; c < DPN; ++c) acc[c] = 0.0;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      if (ep_q[2 * t + e] < 0) continue;
+      const int s = ep_occ[2 * t + e];
+      const double sg = (double)ep_sign[2 * t + e];
+      const double* v = y + (so[s] + ep_bn[2 * t + e]) * DPN;
+      if (DPN == 3 && rot) {
+        const double* O = rot + 9 * (int64_t)s;
+#pragma unroll
+        for (int c = 0; c < DPN; ++c)
+          acc[c] += sg * (O[3 * c] * v[0] + O[3 * c + 1] * v[1 % DPN] + O[3 * c + 2] * v[2 % DPN]);
+      } else {
+#pragma unroll
+        for (int c = 0; c < DPN; ++c) acc[c] += sg * v[c];
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < DPN; ++c) Y[((int64_t)t * DPN + c) * ldy + j] = acc[c];
+  }
+}
+
+bool apply_small(rpf_problem pb, const rpf_pattern* pats, int m, const double* X, int64_t ldx, double* Y, int64_t ldy,
+                 hipStream_t s, int op) {
+  // An occurrence's product is a thread per row with n_b terms one after the other.  2-D heat row, n_b = 34:
+  // 8.3 us for 1 to 256 columns, the general path 14 at 1 column, 16 at 32, 43 at 256.  n_b = 80: 16.2 us
+  // against 13.2 at 1 column, 17.0 / 16.5 at 16, 17.1 / 18.7 at 32, 43 / 158 at 1024; so long rows want
+  // 32 columns.  Schedules and the tracer name the general path's products, and a column is read whole before it is
+  // written, so X and Y may be the same block but not share it in another way.
+  const int64_t xs = (pb->n_lambda - 1) * ldx + m, ys = (pb->n_lambda - 1) * ldy + m;
+  if (X < Y + ys && Y < X + xs && (X != Y || ldx != ldy)) return false;
+  if (pb->weighted || pb->n_occ > SMALL_OCC || pb->n_mult > SMALL_ROWS || trace_on() ||
+      pb->sched.count({m, RPF_FP64}))
+    return false;
+  SmallPats P{};
+  int64_t slots = 0;
+  for (int p = 0; p < pb->n_pat; ++p) {
+    if (pats[p]->n_b > (m < 32 ? SMALL_NB / 2 : SMALL_NB)) return false;
+    P.M[p] = op == OP_FLEX ? pats[p]->Splus.p : pats[p]->S.p;
+    P.nb[p] = pats[p]->n_b;
+    slots += (int64_t)pb->occ_of_pat[p].size() * pb->pat_nbn[p];
+  }
+  if (slots * pb->dpn > SMALL_ROWS) return false;
+#define RPF_AS(D)                                                                                                    \
+  hipLaunchKernelGGL(k_apply_small<D>, dim3((unsigned)m), dim3(512), 0, s, pb->n_occ, (int)slots, pb->n_mult,         \
+                     pb->d_slot_off.p, pb->d_occ_pat.p, pb->d_l2m_ptr.p, pb->d_l2m_code.p, pb->d_ep_q.p,              \
+                     pb->d_ep_occ.p, pb->d_ep_bn.p, pb->d_ep_sign.p, pb->has_rot ? pb->d_rot.p : (const double*)nullptr, \
+                     P, X, ldx, Y, ldy)
+  switch (pb->dpn) {
+    case 1: RPF_AS(1); break;
+    case 2: RPF_AS(2); break;
+    default: RPF_AS(3);
+  }
+#undef RPF_AS
+  RPF_LAUNCH_CHECK();
+  return true;
+}
+
 void apply_F(rpf_problem pb, const rpf_pattern* pats, int m, const double* X, int64_t ldx, double* Y, int64_t ldy,
              int prec, bool project, hipStream_t s, int op, const double* const* gsub) {
   if (prec != RPF_FP64) {
     apply_F_lowprec(pb, pats, m, X, ldx, Y, ldy, prec, s, op, gsub);
+    if (project) {
+      ensure_coarse(pb, pats, s);
+      project_block(pb, Y, ldy, m, s);
+    }
+    return;
+  }
+  if (!gsub && apply_small(pb, pats, m, X, ldx, Y, ldy, s, op)) {
     if (project) {
       ensure_coarse(pb, pats, s);
       project_block(pb, Y, ldy, m, s);

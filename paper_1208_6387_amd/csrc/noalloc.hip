@@ -45,6 +45,7 @@ extern "C" rpf_status feti_apply_noalloc(rpf_problem pb, const rpf_pattern* patt
               "feti_apply_noalloc: no flags are accepted (the coarse projector allocates its space)");
     check_patterns(pb, patterns, RPF_FP64);
     if (pb->n_lambda == 0) return;
+    if (apply_small(pb, patterns, m, X, ldx, Y, ldy, (hipStream_t)stream, OP_FLEX)) return;
     F64Plan pl = plan_F64(pb, patterns, m, schedule_for(pb, m, RPF_FP64));
     // the result slabs stay 256-byte aligned
     if (cdiv(pl.xneed, 32) * 32 + pl.yneed > SCRATCH_DOUBLES)
