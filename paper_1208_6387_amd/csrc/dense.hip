@@ -2965,9 +2965,15 @@ __global__ __launch_bounds__(1024) void k_mgs2(double* Y, int64_t n, int64_t ld,
   }
 }
 
-// Sums over the workgroup of v[0..7] (16 waves), to every thread.  Halving exchanges leave each lane with
+__device__ inline double read_lane(double v, int l) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), l), hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
+  return __hiloint2double(hi, lo);
+}
+
+// Sums over the workgroup of v[0..7] (NW waves), to every thread.  Halving exchanges leave each lane with
 // one of the eight sums over its wave, so 13 cross-lane moves and one barrier serve all of them; the
 // caller alternates between the two buffers.
+template <int NW>
 __device__ inline void block_sum8(const double (&v)[8], double (*red)[8], double (&out)[8]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   double a[4], b[2], c;
@@ -2989,79 +2995,92 @@ __device__ inline void block_sum8(const double (&v)[8], double (*red)[8], double
   for (int off = 4; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
   if ((lane & 7) == 0) red[wave][lane >> 3] = c;
   __syncthreads();
-  double t = red[lane & 7][lane >> 3] + red[8 + (lane & 7)][lane >> 3];
+  constexpr int G = NW < 8 ? NW : 8;
+  double t = red[lane & (G - 1)][lane >> 3];
+  if (NW > 8) t += red[8 + (lane & 7)][lane >> 3];
 #pragma unroll
-  for (int off = 4; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+  for (int off = G / 2; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
 #pragma unroll
-  for (int i = 0; i < 8; ++i) out[i] = __shfl(t, 8 * i, 64);
+  for (int i = 0; i < 8; ++i) out[i] = read_lane(t, 8 * i);
 }
 
-// Up to 8 columns of at most 1024 R rows in registers: classical Gram-Schmidt with every projection taken
-// twice (as orthogonal as the modified form taken twice), three reductions a column.  It is bound by
-// the reductions (24 of about 0.6 us); the general kernel below re-reads the columns for each of its
-// 64 (160 us at 2,598 rows, 74 us at 64).
-template <int R>
-__global__ __launch_bounds__(1024) void k_gs2(double* Y, int64_t n, int64_t ld, int k) {
-  __shared__ double red[2][16][8];
+// Up to 8 columns of at most T R rows in registers: classical Gram-Schmidt with every projection taken
+// twice (as orthogonal as the modified form taken twice).  A column's norm is summed with the next one's first
+// projection, so k columns are 2k - 1 reductions.  It is bound by them, and a reduction by the waves that share
+// the LDS unit for its moves: 34 rows take 12 us in 4 waves (30 in 16 waves with a reduction for each norm),
+// 888 rows 18 in 4 waves of 4 rows a lane, 2,598 rows 31 in 8 waves of 8 (32 in 16 waves of 4).
+// The general kernel above re-reads the columns for each of its 64 reductions (160 us at 2,598 rows, 74 us at 64).
+template <int T, int R>
+__global__ __launch_bounds__(T) void k_gs2(double* Y, int64_t n, int64_t ld, int k) {
+  __shared__ double red[2][T / 64][8];
   const int tid = threadIdx.x;
   double v[8][R];
 #pragma unroll
   for (int j = 0; j < 8; ++j)
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int64_t row = tid + 1024 * r;
+      const int64_t row = tid + T * r;
       const double x = Y[(int64_t)min(j, k - 1) * ld + min(row, n - 1)];
       v[j][r] = (j < k && row < n) ? x : 0.0;
     }
   int buf = 0;
+  double d[8], p[8];
+  // column j to unit length, given its squared norm
+  auto scale = [&](int j, double nn) {
+    const double inv = nn > 0.0 ? 1.0 / sqrt(nn) : 0.0;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
+    for (int r = 0; r < R; ++r) {
+      v[j][r] *= inv;
+      const int64_t row = tid + T * r;
+      if (row < n) Y[(int64_t)j * ld + row] = v[j][r];
+    }
+    return inv;
+  };
+#pragma unroll
+  for (int j = 1; j < 8; ++j) {
     if (j < k) {
-      double d[8], p[8];
 #pragma unroll
-      for (int pass = 0; pass < (j > 0 ? 2 : 0); ++pass) {
+      for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           p[i] = 0.0;
-          if (i < j) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) p[i] += v[i][r] * v[j][r];
+          for (int r = 0; r < R; ++r) {
+            if (i < j) p[i] += v[i][r] * v[j][r];
+            else if (i == 7 && pass == 0) p[i] += v[j - 1][r] * v[j - 1][r];
           }
         }
-        block_sum8(p, red[buf], d);
+        block_sum8<T / 64>(p, red[buf], d);
         buf ^= 1;
+        if (pass == 0) d[j - 1] *= scale(j - 1, d[7]);
 #pragma unroll
         for (int i = 0; i < j; ++i)
 #pragma unroll
           for (int r = 0; r < R; ++r) v[j][r] -= d[i] * v[i][r];
       }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    if (j == k - 1) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) p[i] = 0.0;
 #pragma unroll
       for (int r = 0; r < R; ++r) p[0] += v[j][r] * v[j][r];
-      block_sum8(p, red[buf], d);
-      buf ^= 1;
-      const double inv = d[0] > 0.0 ? 1.0 / sqrt(d[0]) : 0.0;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        v[j][r] *= inv;
-        const int64_t row = tid + 1024 * r;
-        if (row < n) Y[(int64_t)j * ld + row] = v[j][r];
-      }
+      block_sum8<T / 64>(p, red[buf], d);
+      scale(j, d[0]);
     }
-  }
 }
 
 void orthonormalize(hipStream_t s, double* Y, int64_t n, int64_t ld, int k) {
   if (k <= 0 || n <= 0) return;
-  if (k <= 8 && n <= 1024)
-    hipLaunchKernelGGL(k_gs2<1>, dim3(1), dim3(1024), 0, s, Y, n, ld, k);
-  else if (k <= 8 && n <= 2048)
-    hipLaunchKernelGGL(k_gs2<2>, dim3(1), dim3(1024), 0, s, Y, n, ld, k);
-  else if (k <= 8 && n <= 4096)
-    hipLaunchKernelGGL(k_gs2<4>, dim3(1), dim3(1024), 0, s, Y, n, ld, k);
-  else
-    hipLaunchKernelGGL(k_mgs2, dim3(1), dim3(1024), 0, s, Y, n, ld, k);
+#define RPF_GS(T, R) hipLaunchKernelGGL((k_gs2<T, R>), dim3(1), dim3(T), 0, s, Y, n, ld, k)
+  if (k <= 8 && n <= 512) RPF_GS(256, 2);
+  else if (k <= 8 && n <= 1024) RPF_GS(256, 4);
+  else if (k <= 8 && n <= 2048) RPF_GS(512, 4);
+  else if (k <= 8 && n <= 4096) RPF_GS(512, 8);
+  else hipLaunchKernelGGL(k_mgs2, dim3(1), dim3(1024), 0, s, Y, n, ld, k);
+#undef RPF_GS
   RPF_LAUNCH_CHECK();
 }
 
