@@ -275,9 +275,14 @@ def main():
                     if form == "fp64" else
                     f"k_gemm_bf16_group<{t}, {t}, X3> (bf16 MFMA 16x16x32, one grouped launch over all patterns, "
                     f"three products)")
+        # the size rule's bf16 kernel: 256 x 256 tiles where those alone fill the chip
+        cols = np.bincount(p.occ_pattern, minlength=len(p.patterns)) * p.n_rhs * p.n_perm
+        big = (any(t == 256 for (m, f), (t, w) in sched.items() if f == form)
+               or any(-(-len(q.bdofs) // 256) * -(-int(c) // 256) >= 240 for q, c in zip(p.patterns, cols)))
         return {"fp64": "k_dgemm_big (FP64 MFMA 16x16x4, 128x128 tiles, eight waves)",
                 "fp32": "k_sgemm_sym (FP32 MFMA 16x16x4)",
-                "bf16x3": "k_gemm_bf16_big X3 (bf16 MFMA 16x16x32, 256x256 tiles, three products)",
+                "bf16x3": "k_gemm_bf16_big X3 (bf16 MFMA 16x16x32, 256x256 tiles, three products)" if big else
+                          "k_gemm_bf16 X3 (bf16 MFMA 16x16x32, 128x128 or 64x64 tiles, three products)",
                 "bf16": "k_gemm_bf16 (bf16 MFMA 16x16x32)"}[form]
 
     def roofline(form):

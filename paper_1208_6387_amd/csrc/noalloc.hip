@@ -45,16 +45,18 @@ extern "C" rpf_status feti_apply_noalloc(rpf_problem pb, const rpf_pattern* patt
               "feti_apply_noalloc: no flags are accepted (the coarse projector allocates its space)");
     check_patterns(pb, patterns, RPF_FP64);
     if (pb->n_lambda == 0) return;
-    if (apply_small(pb, patterns, m, X, ldx, Y, ldy, (hipStream_t)stream, OP_FLEX)) return;
-    F64Plan pl = plan_F64(pb, patterns, m, schedule_for(pb, m, RPF_FP64));
+    // the limit is that of the general plan; the size rule's faster ones are taken where they fit too
+    F64Plan pl = plan_F64(pb, patterns, m, schedule_for(pb, m, RPF_FP64), true);
     // the result slabs stay 256-byte aligned
-    if (cdiv(pl.xneed, 32) * 32 + pl.yneed > SCRATCH_DOUBLES)
-      pl = plan_F64(pb, patterns, m, schedule_for(pb, m, RPF_FP64), true);
-    const int64_t xn = cdiv(pl.xneed, 32) * 32;
-    const int64_t need = xn + pl.yneed;
+    auto doubles = [](const F64Plan& q) { return cdiv(q.xneed, 32) * 32 + q.yneed; };
+    const int64_t need = doubles(pl);
     RPF_CHECK(need <= SCRATCH_DOUBLES, RPF_EINVAL,
               "feti_apply_noalloc: the block needs " + std::to_string(need * 8) + " bytes of workspace, above the " +
                   std::to_string((int64_t)RPF_NOALLOC_SCRATCH_BYTES) + "-byte limit; use fewer columns per call");
+    if (apply_small(pb, patterns, m, X, ldx, Y, ldy, (hipStream_t)stream, OP_FLEX)) return;
+    const F64Plan wide = plan_F64(pb, patterns, m, schedule_for(pb, m, RPF_FP64));
+    if (doubles(wide) <= SCRATCH_DOUBLES) pl = wide;
+    const int64_t xn = cdiv(pl.xneed, 32) * 32;
     double* base = scratch_on_current_device();
     hipStream_t s = (hipStream_t)stream;
     const YLoc yl = run_F64(pb, patterns, pl, m, X, ldx, base, base + xn, s, OP_FLEX, false);
