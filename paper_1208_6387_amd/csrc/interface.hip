@@ -848,15 +848,102 @@ struct SmallPats {
   int nb[MAXP];
 };
 
+// The stored rows of G, (G^T G)^{-1} and what names a row's occurrence, for a column in LDS
+constexpr int SMALL_G = 64;
+struct SmallCoarse {
+  const double *grow, *inv;
+  const int *ep_goff, *ep_occ, *occ_pat, *kp, *goff, *slot_off, *l2m_ptr, *l2m_code;
+  int n_occ, n_mult, nG, km;
+};
+// A wave walks every eighth occurrence, one after the other.  With a 5 us copy, 4 occurrences: 11.6 us against
+// 14.7 in two launches at 8 columns, 11.3 / 28.8 at 256; 64 occurrences: 17.5 / 15.8 at 1 column, 18.3 / 17.7 at 64,
+// 19.8 / 28.8 at 256.
+bool small_coarse(rpf_problem pb, int m, SmallCoarse& g) {
+  if (pb->weighted || pb->n_G == 0 || pb->n_G > SMALL_G || pb->n_lambda > SMALL_ROWS ||
+      pb->n_occ > (m < 128 ? SMALL_OCC / 2 : SMALL_OCC) || !pb->d_grow.p || pb->g_km == 0)
+    return false;
+  g = SmallCoarse{pb->d_grow.p,     pb->Ginv.p,   pb->d_ep_goff.p,  pb->d_ep_occ.p, pb->d_occ_pat.p,
+                  pb->d_kp.p,       pb->d_goff.p, pb->d_slot_off.p, pb->d_l2m_ptr.p, pb->d_l2m_code.p,
+                  pb->n_occ,        pb->n_mult,   pb->n_G,          pb->g_km};
+  return true;
+}
+// x -= G (G^T G)^{-1} G^T x for a column x in LDS, by a workgroup of 512: a wave per occurrence sums G^T x over its
+// multipliers, a thread per coarse unknown solves.  All threads call it after a barrier, and it ends with one.
+template <int DPN>
+__device__ void project_column(const SmallCoarse& G, double* x) {
+  __shared__ double c[SMALL_G], y[SMALL_G];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int s = wave; s < G.n_occ; s += 8) {
+    const int e1 = G.l2m_ptr[G.slot_off[s + 1]];
+    double acc[KMAX];
+#pragma unroll
+    for (int r = 0; r < KMAX; ++r) acc[r] = 0.0;
+    for (int e = G.l2m_ptr[G.slot_off[s]] + lane; e < e1; e += 64) {
+      const int mult = G.l2m_code[e] >> 1;
+      const double* g = G.grow + ((int64_t)mult * 2 + (G.ep_occ[2 * mult] == s ? 0 : 1)) * DPN * G.km;
+#pragma unroll
+      for (int q = 0; q < DPN; ++q)
+#pragma unroll
+        for (int r = 0; r < KMAX; ++r) acc[r] += r < G.km ? g[q * G.km + r] * x[mult * DPN + q] : 0.0;
+    }
+    const int k = G.kp[G.occ_pat[s]];
+#pragma unroll
+    for (int r = 0; r < KMAX; ++r) {
+      if (r >= k) break;
+      const double v = wave_sum(acc[r]);
+      if (lane == 0) c[G.goff[s] + r] = v;
+    }
+  }
+  __syncthreads();
+  if (tid < G.nG) {
+    double v = 0.0;
+    for (int h0 = 0; h0 < G.nG; h0 += 16) {
+      double a[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) a[u] = G.inv[(int64_t)min(h0 + u, G.nG - 1) * G.nG + tid];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v += h0 + u < G.nG ? a[u] * c[min(h0 + u, G.nG - 1)] : 0.0;
+    }
+    y[tid] = v;
+  }
+  __syncthreads();
+  for (int i = tid; i < G.n_mult * DPN; i += 512) {
+    const int mult = i / DPN, q = i % DPN;
+    double v = 0.0;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int go = G.ep_goff[2 * mult + e];
+      const double* g = G.grow + (((int64_t)mult * 2 + e) * DPN + q) * G.km;
+#pragma unroll
+      for (int r = 0; r < KMAX; ++r)  // rows past the occurrence's kernel hold zeros
+        v += (r < G.km && go >= 0 && go + r < G.nG) ? g[r] * y[min(max(go + r, 0), G.nG - 1)] : 0.0;
+    }
+    x[i] -= v;
+  }
+  __syncthreads();
+}
+// The projection of a small structure's block in one launch, a workgroup per column
+template <int DPN>
+__global__ __launch_bounds__(512) void k_project_small(SmallCoarse G, double* X, int64_t ldx) {
+  __shared__ double x[SMALL_ROWS];
+  double* col = X + blockIdx.x;
+  for (int i = threadIdx.x; i < G.n_mult * DPN; i += 512) x[i] = col[i * ldx];
+  __syncthreads();
+  project_column<DPN>(G, x);
+  for (int i = threadIdx.x; i < G.n_mult * DPN; i += 512) col[i * ldx] = x[i];
+}
+
 // Y = sum_s A^(s) M A^(s)T X for a small structure in one launch, a workgroup per column: the gathered
 // boundary values of every occurrence, their products and the scattered sums all stand in LDS.  As three
 // launches it is three memory latencies and two launch gaps (2-D heat row of four: 14.8 us, in one launch 8.3).
-template <int DPN>
+// PROJ: the result is projected before it is stored (product and projection of the 2-D heat row at 8 columns: 15.1 us
+// in three launches, 9.4 in one).
+template <int DPN, bool PROJ>
 __global__ __launch_bounds__(512) void k_apply_small(int n_occ, int n_slots, int n_mult, const int* slot_off,
                                                      const int* occ_pat, const int* l2m_ptr, const int* l2m_code,
                                                      const int* ep_q, const int* ep_occ, const int* ep_bn,
                                                      const int8_t* ep_sign, const double* rot, SmallPats P,
-                                                     const double* X, int64_t ldx, double* Y, int64_t ldy) {
+                                                     SmallCoarse G, const double* X, int64_t ldx, double* Y, int64_t ldy) {
   __shared__ double w[SMALL_ROWS], y[SMALL_ROWS];
   __shared__ int so[SMALL_OCC], op[SMALL_OCC];
   const int tid = threadIdx.x, j = blockIdx.x;
@@ -931,12 +1018,20 @@ __global__ __launch_bounds__(512) void k_apply_small(int n_occ, int n_slots, int
       }
     }
 #pragma unroll
-    for (int c = 0; c < DPN; ++c) Y[((int64_t)t * DPN + c) * ldy + j] = acc[c];
+    for (int c = 0; c < DPN; ++c) {
+      if (PROJ) w[t * DPN + c] = acc[c];
+      else Y[((int64_t)t * DPN + c) * ldy + j] = acc[c];
+    }
+  }
+  if (PROJ) {
+    __syncthreads();
+    project_column<DPN>(G, w);
+    for (int i = tid; i < n_mult * DPN; i += 512) Y[i * ldy + j] = w[i];
   }
 }
 
 bool apply_small(rpf_problem pb, const rpf_pattern* pats, int m, const double* X, int64_t ldx, double* Y, int64_t ldy,
-                 hipStream_t s, int op) {
+                 hipStream_t s, int op, bool project) {
   // An occurrence's product is a thread per row with n_b terms one after the other.  2-D heat row, n_b = 34:
   // 8.3 us for 1 to 256 columns, the general path 14 at 1 column, 16 at 32, 43 at 256.  n_b = 80: 16.2 us
   // against 13.2 at 1 column, 17.0 / 16.5 at 16, 17.1 / 18.7 at 32, 43 / 158 at 1024; so long rows want
@@ -956,18 +1051,28 @@ bool apply_small(rpf_problem pb, const rpf_pattern* pats, int m, const double* X
     slots += (int64_t)pb->occ_of_pat[p].size() * pb->pat_nbn[p];
   }
   if (slots * pb->dpn > SMALL_ROWS) return false;
-#define RPF_AS(D)                                                                                                    \
-  hipLaunchKernelGGL(k_apply_small<D>, dim3((unsigned)m), dim3(512), 0, s, pb->n_occ, (int)slots, pb->n_mult,         \
+  SmallCoarse G{};
+  if (project) ensure_coarse(pb, pats, s);
+  const bool fused = project && small_coarse(pb, m, G);
+#define RPF_AS(D, PR)                                                                                                \
+  hipLaunchKernelGGL((k_apply_small<D, PR>), dim3((unsigned)m), dim3(512), 0, s, pb->n_occ, (int)slots, pb->n_mult,   \
                      pb->d_slot_off.p, pb->d_occ_pat.p, pb->d_l2m_ptr.p, pb->d_l2m_code.p, pb->d_ep_q.p,              \
-                     pb->d_ep_occ.p, pb->d_ep_bn.p, pb->d_ep_sign.p, pb->has_rot ? pb->d_rot.p : (const double*)nullptr, \
-                     P, X, ldx, Y, ldy)
+                     pb->d_ep_occ.p, pb->d_ep_bn.p, pb->d_ep_sign.p,                                                  \
+                     pb->has_rot ? pb->d_rot.p : (const double*)nullptr, P, G, X, ldx, Y, ldy)
+#define RPF_AD(D)               \
+  do {                          \
+    if (fused) RPF_AS(D, true); \
+    else RPF_AS(D, false);      \
+  } while (0)
   switch (pb->dpn) {
-    case 1: RPF_AS(1); break;
-    case 2: RPF_AS(2); break;
-    default: RPF_AS(3);
+    case 1: RPF_AD(1); break;
+    case 2: RPF_AD(2); break;
+    default: RPF_AD(3);
   }
+#undef RPF_AD
 #undef RPF_AS
   RPF_LAUNCH_CHECK();
+  if (project && !fused) project_block(pb, Y, ldy, m, s);
   return true;
 }
 
@@ -981,13 +1086,7 @@ void apply_F(rpf_problem pb, const rpf_pattern* pats, int m, const double* X, in
     }
     return;
   }
-  if (!gsub && apply_small(pb, pats, m, X, ldx, Y, ldy, s, op)) {
-    if (project) {
-      ensure_coarse(pb, pats, s);
-      project_block(pb, Y, ldy, m, s);
-    }
-    return;
-  }
+  if (!gsub && apply_small(pb, pats, m, X, ldx, Y, ldy, s, op, project)) return;
   const F64Plan pl = plan_F64(pb, pats, m, schedule_for(pb, m, RPF_FP64));
   pb->xloc.ensure(pl.xneed);
   pb->yloc.ensure(pl.yneed);
@@ -1271,6 +1370,16 @@ void coarse_g(rpf_problem pb, const double* y, int m, double alpha, double* x, i
 void project_block(rpf_problem pb, double* x, int64_t ldx, int m, hipStream_t s) {
   const int nG = pb->n_G;
   if (nG == 0) return;
+  SmallCoarse G{};
+  if (small_coarse(pb, m, G)) {
+    switch (pb->dpn) {
+      case 1: hipLaunchKernelGGL(k_project_small<1>, dim3((unsigned)m), dim3(512), 0, s, G, x, ldx); break;
+      case 2: hipLaunchKernelGGL(k_project_small<2>, dim3((unsigned)m), dim3(512), 0, s, G, x, ldx); break;
+      default: hipLaunchKernelGGL(k_project_small<3>, dim3((unsigned)m), dim3(512), 0, s, G, x, ldx);
+    }
+    RPF_LAUNCH_CHECK();
+    return;
+  }
   pb->cbuf.ensure((size_t)nG * m);
   pb->ybuf.ensure((size_t)nG * m);
   coarse_gt(pb, x, ldx, m, pb->cbuf.p, s);

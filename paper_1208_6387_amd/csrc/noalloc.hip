@@ -53,7 +53,7 @@ extern "C" rpf_status feti_apply_noalloc(rpf_problem pb, const rpf_pattern* patt
     RPF_CHECK(need <= SCRATCH_DOUBLES, RPF_EINVAL,
               "feti_apply_noalloc: the block needs " + std::to_string(need * 8) + " bytes of workspace, above the " +
                   std::to_string((int64_t)RPF_NOALLOC_SCRATCH_BYTES) + "-byte limit; use fewer columns per call");
-    if (apply_small(pb, patterns, m, X, ldx, Y, ldy, (hipStream_t)stream, OP_FLEX)) return;
+    if (apply_small(pb, patterns, m, X, ldx, Y, ldy, (hipStream_t)stream, OP_FLEX, false)) return;
     const F64Plan wide = plan_F64(pb, patterns, m, schedule_for(pb, m, RPF_FP64));
     if (doubles(wide) <= SCRATCH_DOUBLES) pl = wide;
     const int64_t xn = cdiv(pl.xneed, 32) * 32;

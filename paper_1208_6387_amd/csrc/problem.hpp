@@ -156,7 +156,7 @@ Schedule schedule_for(rpf_problem pb, int m, int prec);
 F64Plan plan_F64(rpf_problem pb, const rpf_pattern* pats, int m, const Schedule& sc, bool narrow = false);
 // Y = F X (or the Schur sum) of a small structure in one launch; false (nothing launched) for others
 bool apply_small(rpf_problem pb, const rpf_pattern* pats, int m, const double* X, int64_t ldx, double* Y, int64_t ldy,
-                 hipStream_t s, int op);
+                 hipStream_t s, int op, bool project);
 // several patterns, none of which fills the chip with `tile`-sized tiles (at least `full` of them) by itself
 bool many_small_products(rpf_problem pb, const rpf_pattern* pats, int m, int tile, int full);
 // grouped persistent launches of the flexibility products (tile 64 or 128)

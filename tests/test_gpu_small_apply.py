@@ -73,3 +73,24 @@ def test_small_apply(built, R, m, project):
     assert float((N - F).norm(dim=0).max()) <= tol
     assert float((Z - G).norm(dim=0).max()) <= tol
     assert float((B - G).norm(dim=0).max()) <= tol
+
+
+@pytest.mark.parametrize("m", [1, 8, 33, 130])
+def test_small_projection(built, R, m):
+    """Q X by itself and behind the product, against the oracle's G on both sides of the single launch's limits."""
+    import oracle as O
+    p, pats, pb = built
+    o = O.FetiOracle(p)
+    gen = torch.Generator(device="cuda").manual_seed(1000 + m)
+    X = torch.randn((pb.n_lambda, m + 1), dtype=torch.float64, device="cuda", generator=gen)[:, :m]
+    P = R.feti_precond(pb, pats, X, R.PRECOND_NONE, project=True)
+    F = R.feti_apply(pb, pats, X)
+    Y = R.feti_apply(pb, pats, X, project=True)
+    torch.cuda.synchronize()
+    # the explicit inverse of G^T G, and kernels of two factorisations
+    cond = np.linalg.cond(o.GtG) if o.GtG.size else 1.0
+    tol = 1024 * np.finfo(float).eps * max(cond, 100.0)
+    for got, of in ((P, X), (Y, F)):
+        ref = of.cpu().numpy()
+        want = o.Q(ref)
+        assert np.linalg.norm(got.cpu().numpy() - want) <= tol * np.linalg.norm(ref)
