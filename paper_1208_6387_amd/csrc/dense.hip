@@ -2368,19 +2368,20 @@ static void launch_skinny(hipStream_t s, bool ta, int64_t M, int64_t c, int64_t 
                           int64_t lda, const double* X, int64_t xk, int64_t xj, double beta, double* C, int64_t cm,
                           int64_t cj) {
   const bool two = cdiv(M, 32) * cdiv(c, 16) >= 256;
-  const int w = two || K < 256 ? 4 : K < 1024 ? 8 : 16;
+  // waves that share a row block's K: more of them while the chip has room and each still gets 16 k (an application
+  // with 888 rows and 81 columns, 336 workgroups: 25.2 us with 4 waves, 28.7 with 16; the coarse solve of 384 unknowns,
+  // 24 workgroups: the projection 22.8 us with 4, 21.5 with 16)
+  const int w = (int64_t)cdiv(M, two ? 32 : 16) * cdiv(c, 16) > 256 || K < 256 ? 4 : 16;
   const dim3 g((unsigned)cdiv(M, two ? 32 : 16), (unsigned)cdiv(c, 16));
 #define RPF_SK(TA, R, W) \
   RPF_TIMED_LAUNCH((k_skinny<TA, R, W>), g, dim3(64 * W), 0, s, M, c, K, alpha, A, lda, X, xk, xj, beta, C, cm, cj)
   if (ta) {
     if (two) RPF_SK(true, 2, 4);
     else if (w == 4) RPF_SK(true, 1, 4);
-    else if (w == 8) RPF_SK(true, 1, 8);
     else RPF_SK(true, 1, 16);
   } else {
     if (two) RPF_SK(false, 2, 4);
     else if (w == 4) RPF_SK(false, 1, 4);
-    else if (w == 8) RPF_SK(false, 1, 8);
     else RPF_SK(false, 1, 16);
   }
 #undef RPF_SK
