@@ -1392,7 +1392,7 @@ void project_block(rpf_problem pb, double* x, int64_t ldx, int m, hipStream_t s)
 }
 
 // y = (G^T G)^{-1} c for n_G x m row-major blocks, with the explicit (symmetric) inverse: bound by reading
-// it once per 16 columns (75 MB at n_G = 3,072; before, 31 + 5 us on a split-K product with 16 output
+// it once per 16 columns (75 MB at n_G = 3,072: 27 us; before, 31 + 5 us on a split-K product with 16 output
 // rows there, and 11.5 us with one wave per row at n_G = 384)
 static void coarse_solve_with(rpf_problem pb, const double* inv, const double* c, double* y, int m, hipStream_t s) {
   const int nG = pb->n_G;
