@@ -785,7 +785,7 @@ extern "C" rpf_status block_krylov_solve(rpf_problem pb, const rpf_pattern* pats
       RPF_LAUNCH_CHECK();
       if (P->n_i > 0) {
         // Y2 = K_ii^{-1} f_i ; g = f_b - K_bi Y2
-        potrs(s, P->Lii(), P->ld, P->n_i, P->dinv_ii.p, P->inv_ii, P->env_ii, Y2[p].p, P->n_i, cols, P->L_upper);
+        potrs(s, P->L.p, P->ld, P->n_i, P->dinv_ii.p, P->inv_ii, P->env_ii, Y2[p].p, P->n_i, cols, P->L_upper);
         hipLaunchKernelGGL(k_spmm, dim3(spmm_blocks(P->n_b, cols)), dim3(256), 0, s, P->n_b, cols,
                            P->kbi_ptr.p, P->kbi_col.p, P->kbi_val.p, Y2[p].p, (int64_t)P->n_i, -1.0, G[p].p,
                            (int64_t)P->n_b, 1.0);
@@ -989,7 +989,7 @@ extern "C" rpf_status block_krylov_solve(rpf_problem pb, const rpf_pattern* pats
         hipLaunchKernelGGL(k_spmm, dim3(spmm_blocks(P->n_i, cols)), dim3(256), 0, s, P->n_i, cols, P->kib_ptr.p,
                            P->kib_col.p, P->kib_val.p, Ub.p, (int64_t)P->n_b, 1.0, Ti.p, (int64_t)P->n_i, 0.0);
         RPF_LAUNCH_CHECK();
-        potrs(s, P->Lii(), P->ld, P->n_i, P->dinv_ii.p, P->inv_ii, P->env_ii, Ti.p, P->n_i, cols, P->L_upper);
+        potrs(s, P->L.p, P->ld, P->n_i, P->dinv_ii.p, P->inv_ii, P->env_ii, Ti.p, P->n_i, cols, P->L_upper);
         hipLaunchKernelGGL(k_axpby, dim3(nblocks((int64_t)P->n_i * cols)), dim3(256), 0, s, (int64_t)P->n_i * cols, 1.0,
                            Y2[p].p, -1.0, Ti.p);
         RPF_LAUNCH_CHECK();

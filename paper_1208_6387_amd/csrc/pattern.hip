@@ -1,6 +1,7 @@
 // Pattern level: factorisation with rigid-mode detection (section 2: floating
 // subdomains, kernel N, Schur complement S) and condensation to the boundary
 // flexibility S+ = t K+ t^T (section 2), shared by every occurrence.
+#include "band.hpp"
 #include "pattern.hpp"
 
 #include <algorithm>
@@ -237,12 +238,10 @@ extern "C" rpf_status pattern_factor(int32_t n, const int32_t* rowptr, const int
     }
     for (int b = 0; b < n_b; ++b) pos[bdofs[b]] = n_i + ord[b];
     // interior factor: in a band where that is smaller (TRI_BW: the widest block read as a rectangle)
-    int64_t hw = TRI_BW;
-    for (int64_t t = 0; t < nblk; ++t) hw = std::max(hw, P->env_ii.rend[t] - t * NB + TRI_BW);
-    const bool band = 2 * hw - 1 < n_i;
-    P->ld = band ? 2 * hw - 1 : n_i;
-    P->l_off = band ? hw : 0;
-    const int64_t llen = P->ld * n_i + (band ? 2 * hw : 0);
+    const FactorLayout lay = factor_layout(n_i, P->env_ii.rend, NB, TRI_BW);
+    P->ld = lay.ld;
+    const int64_t llen = lay.len;
+    RPF_CHECK(n_i == 0 || (n_i - 1) * (P->ld + 1) < llen, RPF_EINVAL, "pattern_factor: factor storage");
     d_pos.upload(pos.data(), n, s);
     P->L.alloc((size_t)llen);
     fill(s, P->L.p, llen, 0.0);
@@ -254,7 +253,7 @@ extern "C" rpf_status pattern_factor(int32_t n, const int32_t* rowptr, const int
     double* Sw = sorted ? P->S.p : Sp.p;
     fill(s, Sw, (int64_t)n_b * n_b, 0.0);
     hipLaunchKernelGGL(k_scatter_csr, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, n, n_i, d_rowptr.p, d_colind.p, val,
-                       d_pos.p, P->Lii(), P->ld, Lbi.p, bnd.ld, Sw, (int64_t)n_b);
+                       d_pos.p, P->L.p, P->ld, Lbi.p, bnd.ld, Sw, (int64_t)n_b);
     RPF_LAUNCH_CHECK();
     auto upload_csr = [&](DevBuf<int>& dptr, DevBuf<int>& dcol, DevBuf<double>& dval, const std::vector<int>& hp,
                           const std::vector<int>& hc, const std::vector<int>& hs) {
@@ -277,11 +276,11 @@ extern "C" rpf_status pattern_factor(int32_t n, const int32_t* rowptr, const int
 
     if (n_i > 0) {
       P->dinv_ii.alloc((size_t)nblk * NB * NB);
-      potrf(s, P->Lii(), P->ld, n_i, P->env_ii, P->dinv_ii.p, P->status.p, bnd);
-      build_tri_inv(s, P->Lii(), P->ld, n_i, P->dinv_ii.p, P->inv_ii);
+      potrf(s, P->L.p, P->ld, n_i, P->env_ii, P->dinv_ii.p, P->status.p, bnd);
+      build_tri_inv(s, P->L.p, P->ld, n_i, P->dinv_ii.p, P->inv_ii);
       schur_update(s, Sw, n_b, n_i, bnd);
       // L_ii^T in the (otherwise unused) upper triangle: the backward solves read it row-contiguous
-      mirror_envelope(s, P->Lii(), P->ld, n_i, P->env_ii);
+      mirror_envelope(s, P->L.p, P->ld, n_i, P->env_ii);
       P->L_upper = true;
     }
     if (sorted) {

@@ -8,12 +8,11 @@ struct rpf_pattern_s {
   int n = 0, n_b = 0, n_i = 0, dpn = 1, k = 0;
   std::vector<int> bdofs, idofs;  // original dof ids of the boundary / interior rows
 
-  // Factor L_ii of the interior stiffness.  Entry (r, c) is Lii()[c ld + r]: dense (ld = n_i), or, where
-  // that is smaller, in a band that holds the envelope on both sides of the diagonal (ld = 2 hw - 1,
-  // |r - c| < hw, so that column c + 1 starts one row lower).
+  // Factor L_ii of the interior stiffness: entry (r, c) is L.p[c ld + r], dense (ld = n_i) or in a band on
+  // both sides of the diagonal (ld = 2 hw - 1; the diagonal advances ld + 1 = 2 hw a column and the block has
+  // (ld + 1) n_i entries, see factor_layout).
   rpf::DevBuf<double> L;
-  int64_t ld = 0, l_off = 0;
-  double* Lii() const { return L.p + l_off; }
+  int64_t ld = 0;
   rpf::DevBuf<double> dinv_ii;  // inverses of the NB x NB diagonal blocks of L_ii
   rpf::TriInv inv_ii;           // and of its TRI_BW-row ones
   rpf::Envelope env_ii;
