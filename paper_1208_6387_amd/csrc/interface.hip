@@ -761,7 +761,10 @@ F64Plan plan_F64(rpf_problem pb, const rpf_pattern* pats, int m, const Schedule&
       }
       pl.ldw[p] = pl.big[p] ? cdiv(nb, 32) * 32 : nb;
     }
-    pl.off[p + 1] = pl.off[p] + pl.ldw[p] * cols;
+    // every W block at a multiple of 32 doubles: the large-problem kernel reads 16 bytes at a time, whatever
+    // patterns stand before it (the narrow plan has no such padding: its workspace decides what is refused)
+    const int64_t w = pl.ldw[p] * cols;
+    pl.off[p + 1] = pl.off[p] + (narrow ? w : cdiv(w, 32) * 32);
     pl.yoff[p + 1] = pl.yoff[p] + (int64_t)nb * cols * pl.alloc_sp[p];
   }
   pl.xneed = std::max<int64_t>(pl.off[pb->n_pat], 1);
