@@ -60,6 +60,11 @@ typedef struct rpf_problem_s* rpf_problem;
 const char* rpf_last_error(void);
 /* ABI version (major * 100 + minor). */
 int32_t rpf_version(void);
+/* Device blocks of 256 KB and more are kept when the library is done with them, for its later allocations: on
+ * each device at most 1/32 of its memory while any pattern or structure handle exists, 1/256 once the last
+ * one is freed.  They are given back when one of the library's own allocations would fail; this call gives
+ * all of them back on every device, for other users of its memory.  Waits for the work that is queued. */
+rpf_status rpf_release_memory(void);
 
 /* ------------------------------------------------------------------ patterns */
 

@@ -20,7 +20,7 @@ from ._lib import (APPLY_PROJECT, BF16, BF16X3, BLOCK_CG, CLASSICAL, FP32, FP64,
 
 __all__ = ["Pattern", "Problem", "pattern_factor", "pattern_condense", "pattern_export", "problem_create", "problem_set_schedule", "problem_tune",
            "feti_apply", "feti_apply_noalloc", "feti_precond", "feti_permute", "block_krylov_solve", "dgemm", "dposv", "dsyev_small",
-           "load", "RpfError", "FP64", "FP32", "BF16X3", "BF16", "CLASSICAL", "BLOCK_CG", "ORTHODIR",
+           "load", "release_memory", "RpfError", "FP64", "FP32", "BF16X3", "BF16", "CLASSICAL", "BLOCK_CG", "ORTHODIR",
            "PRECOND_NONE", "PRECOND_LUMPED", "PRECOND_DIRICHLET", "APPLY_PROJECT"]
 
 
@@ -36,6 +36,11 @@ def _ptr(t: torch.Tensor) -> C.c_void_p:
 
 def _host(a, dtype) -> np.ndarray:
     return np.ascontiguousarray(np.asarray(a, dtype=dtype))
+
+
+def release_memory() -> None:
+    """Give back the device blocks that the library keeps for its later allocations."""
+    check(load().rpf_release_memory())
 
 
 class Pattern:

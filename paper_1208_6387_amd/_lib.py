@@ -17,7 +17,7 @@ APPLY_PROJECT = 1
 NOALLOC_SCRATCH_BYTES = 128 << 20   # RPF_NOALLOC_SCRATCH_BYTES
 
 # every symbol the header declares
-EXPORTS = ["rpf_last_error", "rpf_version", "pattern_factor", "pattern_condense", "pattern_info", "pattern_export",
+EXPORTS = ["rpf_last_error", "rpf_version", "rpf_release_memory", "pattern_factor", "pattern_condense", "pattern_info", "pattern_export",
            "pattern_free", "problem_create", "problem_n_lambda", "problem_free", "problem_n_perm", "problem_set_schedule", "problem_tune", "feti_apply",
            "feti_apply_noalloc", "feti_precond", "feti_permute",
            "block_krylov_solve",
@@ -70,6 +70,7 @@ def load() -> C.CDLL:
     sig = {
         "rpf_last_error": (C.c_char_p, []),
         "rpf_version": (i32, []),
+        "rpf_release_memory": (i32, []),
         "pattern_factor": (i32, [i32, vp, vp, vp, i32, vp, i32, f64, i32, vp, C.POINTER(vp), C.POINTER(i32)]),
         "pattern_condense": (i32, [vp, i32, vp]),
         "pattern_info": (i32, [vp, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]),

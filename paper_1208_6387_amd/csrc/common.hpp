@@ -101,7 +101,19 @@ rpf_status guarded(F&& f) {
 // Device memory for DevBuf on the current device (nullptr on failure); large released blocks are kept, up
 // to a bound, for later allocations.
 void* dev_alloc(size_t bytes);
-void dev_free(void* p);
+void dev_free(void* p) noexcept;
+// bytes that this library can still allocate on the current device: the free ones and those kept
+size_t dev_available();
+// gives back what is kept, on every device
+void dev_release();
+// Counts the pattern and structure handles: with the last of them most of what is kept is given back.
+// The first member of a handle, so that it goes after the handle's buffers.
+struct HandleRef {
+  HandleRef();
+  ~HandleRef();
+  HandleRef(const HandleRef&) = delete;
+  HandleRef& operator=(const HandleRef&) = delete;
+};
 
 template <class T>
 struct DevBuf {

@@ -1571,9 +1571,7 @@ static bool coarse_M_responses(rpf_problem pb, const rpf_pattern* pats, int kind
     slab = std::max(slab, (cdiv(nb, 32) * 32 + nb) * nq * W + nb * nq * (int64_t)cpb * kmax);
   }
   const double need = 8.0 * ((double)N * W + (double)slab + (double)no * W * W + (double)nG * cpb * kmax);
-  size_t free_b = 0, total_b = 0;
-  RPF_HIP(hipMemGetInfo(&free_b, &total_b));
-  if (need > 0.5 * (double)free_b) return false;
+  if (need > 0.5 * (double)dev_available()) return false;
 
   std::vector<int> pcol(nG);
   for (int o = 0; o < no; ++o)

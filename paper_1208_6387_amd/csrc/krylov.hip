@@ -417,8 +417,7 @@ struct Solver {
   }
 
   void alloc_store(int want_blocks) {
-    size_t free_b = 0, total_b = 0;
-    RPF_HIP(hipMemGetInfo(&free_b, &total_b));
+    const size_t free_b = dev_available();
     const double per_block = 2.0 * (double)N * m * sizeof(double);
     int cap = (int)std::max(1.0, std::floor(0.5 * (double)free_b / per_block));
     max_blocks = std::max(1, std::min(want_blocks, cap));

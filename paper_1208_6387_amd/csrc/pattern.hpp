@@ -4,6 +4,7 @@
 #include "common.hpp"
 
 struct rpf_pattern_s {
+  rpf::HandleRef ref;
   uint64_t uid = 0;  // unique per handle for the life of the process (cache keys)
   int n = 0, n_b = 0, n_i = 0, dpn = 1, k = 0;
   std::vector<int> bdofs, idofs;  // original dof ids of the boundary / interior rows

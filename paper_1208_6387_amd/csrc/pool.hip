@@ -12,6 +12,9 @@ namespace {
 
 // Smaller blocks cost 3 us to allocate and 2 us to free, less than the wait that a kept block needs.
 constexpr size_t KEEP_MIN = 256 << 10;
+// Kept on a device: 1/LIVE_PART of its memory while a pattern or structure exists, 1/IDLE_PART once the last
+// one is freed.
+constexpr size_t LIVE_PART = 32, IDLE_PART = 256;
 // A kept block serves requests down to 7/8 of its size.
 inline bool fits(size_t have, size_t need) { return have >= need && have - need <= have / 8; }
 // A kept block that this many later allocations passed over is given back.
@@ -28,20 +31,29 @@ struct Pool {
   std::vector<Block> kept;                      // oldest first
   std::unordered_map<void*, Block> live;        // large blocks in use
   std::unordered_map<int, size_t> kept_bytes;   // by device
-  std::unordered_map<int, size_t> bound;        // by device: 1/32 of its memory
+  std::unordered_map<int, size_t> memory;       // by device
   uint64_t ops = 0;
+  int64_t handles = 0;
 
   size_t limit(int dev) {
-    auto it = bound.find(dev);
-    if (it != bound.end()) return it->second;
-    size_t f = 0, t = 0;
-    if (hipMemGetInfo(&f, &t) != hipSuccess) return 0;
-    return bound[dev] = t / 32;
+    auto it = memory.find(dev);
+    if (it == memory.end()) {
+      size_t total = 0;
+      if (hipDeviceTotalMem(&total, dev) != hipSuccess) return 0;
+      it = memory.emplace(dev, total).first;
+    }
+    return it->second / (handles > 0 ? LIVE_PART : IDLE_PART);
   }
   void give_back(size_t i) {
     (void)hipFree(kept[i].p);
     kept_bytes[kept[i].dev] -= kept[i].bytes;
     kept.erase(kept.begin() + (std::ptrdiff_t)i);
+  }
+  // the oldest blocks of a device until it holds at most `most` bytes
+  void trim(int dev, size_t most) {
+    for (size_t i = 0; i < kept.size() && kept_bytes[dev] > most;)
+      if (kept[i].dev == dev) give_back(i);
+      else ++i;
   }
 };
 
@@ -74,10 +86,10 @@ void* dev_alloc(size_t bytes) {
       best = i;
   if (best < P.kept.size()) {
     if (hipDeviceSynchronize() != hipSuccess) return nullptr;
-    Pool::Block b = P.kept[best];
+    const Pool::Block b = P.kept[best];
+    P.live[b.p] = b;  // may throw: the block is still kept then
     P.kept.erase(P.kept.begin() + (std::ptrdiff_t)best);
     P.kept_bytes[dev] -= b.bytes;
-    P.live[b.p] = b;
     return b.p;
   }
   hipError_t e = hipMalloc(&p, bytes);
@@ -87,11 +99,17 @@ void* dev_alloc(size_t bytes) {
     e = hipMalloc(&p, bytes);
   }
   if (e != hipSuccess) return nullptr;
-  P.live[p] = Pool::Block{p, bytes, dev, 0};
+  try {
+    P.live[p] = Pool::Block{p, bytes, dev, 0};
+  } catch (...) {
+    (void)hipFree(p);
+    throw;
+  }
   return p;
 }
 
-void dev_free(void* p) {
+// Called from destructors: nothing leaves it.
+void dev_free(void* p) noexcept {
   if (!p) return;
   Pool& P = pool();
   std::lock_guard<std::mutex> lock(P.mu);
@@ -102,17 +120,49 @@ void dev_free(void* p) {
   }
   Pool::Block b = it->second;
   P.live.erase(it);
-  const size_t most = P.limit(b.dev);
-  if (b.bytes > most) {
-    (void)hipFree(p);
-    return;
+  try {
+    const size_t most = P.limit(b.dev);
+    b.op = P.ops;
+    size_t& held = P.kept_bytes[b.dev];
+    if (b.bytes <= most) {
+      P.kept.push_back(b);
+      held += b.bytes;
+      P.trim(b.dev, most);
+      return;
+    }
+  } catch (...) {  // no room for the note of it
   }
-  b.op = P.ops;
-  P.kept.push_back(b);
-  P.kept_bytes[b.dev] += b.bytes;
-  for (size_t i = 0; i < P.kept.size() && P.kept_bytes[b.dev] > most;)
-    if (P.kept[i].dev == b.dev) P.give_back(i);
-    else ++i;
+  (void)hipFree(p);
+}
+
+size_t dev_available() {
+  size_t free_b = 0, total_b = 0;
+  int dev = 0;
+  RPF_HIP(hipGetDevice(&dev));
+  RPF_HIP(hipMemGetInfo(&free_b, &total_b));
+  Pool& P = pool();
+  std::lock_guard<std::mutex> lock(P.mu);
+  const auto it = P.kept_bytes.find(dev);
+  return free_b + (it == P.kept_bytes.end() ? 0 : it->second);
+}
+
+void dev_release() {
+  Pool& P = pool();
+  std::lock_guard<std::mutex> lock(P.mu);
+  while (!P.kept.empty()) P.give_back(0);
+}
+
+HandleRef::HandleRef() {
+  Pool& P = pool();
+  std::lock_guard<std::mutex> lock(P.mu);
+  ++P.handles;
+}
+
+HandleRef::~HandleRef() {
+  Pool& P = pool();
+  std::lock_guard<std::mutex> lock(P.mu);
+  if (--P.handles > 0) return;
+  for (const auto& d : P.memory) P.trim(d.first, d.second / IDLE_PART);
 }
 
 }  // namespace rpf

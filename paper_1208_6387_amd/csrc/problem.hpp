@@ -64,6 +64,7 @@ struct Schedule {
 }  // namespace rpf
 
 struct rpf_problem_s {
+  rpf::HandleRef ref;
   int dpn = 1, n_pat = 0, n_occ = 0, n_mult = 0, n_perm = 1;
   int64_t n_lambda = 0;
   bool has_rot = false;
