@@ -774,12 +774,8 @@ void apply_F_lowprec(rpf_problem pb, const rpf_pattern* pats, int m, const doubl
   // W format with ld rounded up to a multiple of 64: every 64-k chunk of a row is one 128-byte
   // cache line (unaligned rows would make each chunk touch two lines)
   std::vector<int64_t> off(pb->n_pat + 1, 0), ld(pb->n_pat);
-  // split K (chunks of multiples of 64) while the output tiles alone give fewer than ~4 workgroups per CU; the
-  // scatter sums the split slabs.  Two 128 x 128 workgroups stand on a CU at once: a split that fills those
-  // places once gives the scatter half the slabs, and is taken where the fullest CU gets less to do by it, or as
-  // much with 15 of 16 places filled.  An application at 64 patterns of 12^3 (4 x 21 tiles at 8 columns):
-  // 70.8 us in 8 parts, 64.7 in 6; at 16 columns 100 us in 6, 86 in 3.  At 27 of 16^3 and 16 columns 3 parts
-  // fill 444 places: 150 us, 143 in 6.
+  // split K (chunks of multiples of 64) while the 64 x 64 output tiles alone give fewer than
+  // ~4 workgroups per CU; the scatter sums the split slabs
   std::vector<int64_t> yoff(pb->n_pat + 1, 0), ldr(pb->n_pat, 0);
   std::vector<int> nsp(pb->n_pat, 1), kch(pb->n_pat, 0), tile_m(pb->n_pat, 64), tile_n(pb->n_pat, 64);
   // a grouped schedule (bf16 forms only) runs every pattern's product in one persistent launch of
@@ -806,14 +802,9 @@ void apply_F_lowprec(rpf_problem pb, const rpf_pattern* pats, int m, const doubl
     tile_m[p] = tm;
     tile_n[p] = tn;
     const int64_t tiles = std::max<int64_t>(1, cdiv(nb, tm) * cdiv(cols, tn));
-    const int64_t maxsp = std::max<int64_t>(1, std::min<int64_t>(8, ld[p] / 256));
-    int64_t sp = tm == 256 ? 1 : std::min(std::max<int64_t>(1, 1024 / tiles), maxsp);
-    if (split && tm == 128) {
-      const int64_t once = std::min(512 / tiles, maxsp);
-      const int64_t a = cdiv(tiles * once, 256) * sp, b = cdiv(tiles * sp, 256) * once;
-      if (once >= 1 && (a < b || (a == b && tiles * once >= 480))) sp = once;
-    }
-    kch[p] = (int)(cdiv(cdiv(ld[p], sp), (int64_t)64) * 64);
+    int sp = (int)std::min<int64_t>(std::max<int64_t>(1, 1024 / tiles), std::max<int64_t>(1, ld[p] / 256));
+    sp = tm == 256 ? 1 : std::min(sp, 8);
+    kch[p] = (int)(cdiv(cdiv(ld[p], sp), 64) * 64);
     if (gtile) kch[p] = (int)group_kchunk(nb, ld[p], cols, gtile, sc.work, 64);
     nsp[p] = (int)cdiv(ld[p], kch[p]);
     // the 256 x 256 kernel's row-major result: n_b rows of ldr[p] (a multiple of 16 floats)
