@@ -6,17 +6,18 @@
 namespace rpf {
 
 // Y[(mult DPN + c) ldy + j] = beta Y + sum over the multiplier's endpoints of sign (O y_loc)[c], y_loc summed
-// over the K splits of its product.  A workgroup takes 32 multipliers (consecutive lanes: consecutive
-// boundary nodes of an interface, so a column's reads are contiguous) times 8 columns, and the rows
+// over the K splits of its product.  A workgroup takes MB multipliers (consecutive lanes: consecutive
+// boundary nodes of an interface, so a column's reads are contiguous) times CB = 256 / MB columns, and the rows
 // of Y leave through LDS.  The loads of both endpoints and four splits at a time are in flight
 // together: bound by their latency, so one thread per multiplier and column (a thread that walked
 // the columns and splits of its multiplier took 45 us at 25,360 multipliers, 8 columns and 8 splits).
-template <int DPN, class Loc>
+// CB is the least power of two that holds the columns, up to 8, so that no thread repeats a column.
+template <int DPN, int CB, class Loc>
 __global__ __launch_bounds__(256) void k_scatter_cols(int n_mult, const int* ep_q, const int* ep_bn,
                                                       const int8_t* ep_pat, const int8_t* ep_sign, const int* ep_occ,
                                                       const double* rot, Loc yl, int m, double* Y, int64_t ldy,
                                                       double beta) {
-  constexpr int MB = 32, CB = 8, U = 4;
+  constexpr int MB = 256 / CB, U = 4;
   __shared__ double out[MB * DPN][CB + 1];
   const int tid = threadIdx.x, lm = tid & (MB - 1), lj = tid / MB;
   const int mult = blockIdx.x * MB + lm, j = blockIdx.y * CB + lj;
@@ -80,16 +81,24 @@ __global__ __launch_bounds__(256) void k_scatter_cols(int n_mult, const int* ep_
 
 template <class Loc>
 void launch_scatter_cols(rpf_problem pb, const Loc& yl, int m, double* Y, int64_t ldy, double beta, hipStream_t s) {
-  const dim3 grid((unsigned)cdiv(pb->n_mult, 32), (unsigned)cdiv(m, 8));
   const double* rot = pb->has_rot ? pb->d_rot.p : nullptr;
-#define RPF_SC(D)                                                                                                   \
-  hipLaunchKernelGGL((k_scatter_cols<D, Loc>), grid, dim3(256), 0, s, pb->n_mult, pb->d_ep_q.p, pb->d_ep_bn.p,       \
-                     pb->d_ep_pat.p, pb->d_ep_sign.p, pb->d_ep_occ.p, rot, yl, m, Y, ldy, beta)
+#define RPF_SC(D, CB)                                                                                             \
+  hipLaunchKernelGGL((k_scatter_cols<D, CB, Loc>), dim3((unsigned)cdiv(pb->n_mult, 256 / CB), (unsigned)cdiv(m, CB)), \
+                     dim3(256), 0, s, pb->n_mult, pb->d_ep_q.p, pb->d_ep_bn.p, pb->d_ep_pat.p, pb->d_ep_sign.p,    \
+                     pb->d_ep_occ.p, rot, yl, m, Y, ldy, beta)
+#define RPF_SD(D)               \
+  do {                          \
+    if (m > 4) RPF_SC(D, 8);    \
+    else if (m > 2) RPF_SC(D, 4); \
+    else if (m > 1) RPF_SC(D, 2); \
+    else RPF_SC(D, 1);          \
+  } while (0)
   switch (pb->dpn) {
-    case 1: RPF_SC(1); break;
-    case 2: RPF_SC(2); break;
-    default: RPF_SC(3);
+    case 1: RPF_SD(1); break;
+    case 2: RPF_SD(2); break;
+    default: RPF_SD(3);
   }
+#undef RPF_SD
 #undef RPF_SC
   RPF_LAUNCH_CHECK();
 }
