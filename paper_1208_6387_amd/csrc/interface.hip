@@ -1394,13 +1394,25 @@ void project_block(rpf_problem pb, double* x, int64_t ldx, int m, hipStream_t s)
   coarse_g(pb, pb->ybuf.p, m, -1.0, x, ldx, 1.0, s);
 }
 
-// y = (G^T G)^{-1} c for n_G x m row-major blocks, with the explicit (symmetric) inverse: bound by reading
-// it once per 16 columns (75 MB at n_G = 3,072: 27 us; before, 31 + 5 us on a split-K product with 16 output
-// rows there, and 11.5 us with one wave per row at n_G = 384)
+// y = inv c for n_G x m row-major blocks, inv the explicit (symmetric) inverse of a coarse matrix.  The product for
+// few columns reads inv once per 16 of them, the split-K product y^T = c^T inv once per 64.  A projection, us, few
+// columns / split K:
+//   n_G    16 columns      32            33            64            128
+//   1,536  25.7 / 41.8   30.8 / 41.3   42.3 / 44.6   47.0 / 49.4   71.1 / 71.9
+//   1,920  31.2 / 46.5   35.2 / 44.7   48.2 / 48.6   54.8 / 54.4   81.4 / 78.4
+//   3,072  37.7 / 46.8   60.5 / 66.5   84.4 / 71.3   89.9 / 77.2   130 / 123
+//   3,888  45.8 / 51.9   72.6 / 86.7   102 / 92.9    112 / 98.1    205 / 165
+//   4,320  68.9 / 61.4   102 / 95.7    112 / 103     154 / 110     260 / 198
 static void coarse_solve_with(rpf_problem pb, const double* inv, const double* c, double* y, int m, hipStream_t s) {
   const int nG = pb->n_G;
   if (nG == 0) return;
-  few_columns_rows(s, nG, m, nG, inv, nG, c, m, y, m);
+  if (nG > 4096 || (nG >= 1920 && m > 32)) {
+    const int sp = gemm_splitk_count(m, nG, nG);
+    pb->cws.ensure((size_t)sp * m * nG);
+    dgemm_splitk(s, false, false, m, nG, nG, 1.0, c, m, inv, nG, 0.0, y, m, pb->cws.p, sp);
+  } else {
+    few_columns_rows(s, nG, m, nG, inv, nG, c, m, y, m);
+  }
 }
 
 void coarse_solve(rpf_problem pb, const double* c, double* y, int m, hipStream_t s) {

@@ -117,7 +117,7 @@ struct rpf_problem_s {
   rpf::DevBuf<int> d_ep_goff;
   int g_km = 0;
   rpf::DevBuf<const double*> d_Zp;
-  rpf::DevBuf<double> Ginv, cbuf, ybuf, cpart;
+  rpf::DevBuf<double> Ginv, cbuf, ybuf, cpart, cws;
   // coarse space with a preconditioner F~^{-1} in the projector: (G^T F~^{-1} G)^{-1}, built for the
   // pattern handles and preconditioner kind in hkey, and an N_lambda x m workspace
   std::vector<uint64_t> hkey;
