@@ -202,9 +202,6 @@ void rows_gemm(hipStream_t s, int64_t N, int a, int b, double alpha, const doubl
 // column-major with ld a).
 void rows_gemm_from(hipStream_t s, int64_t N, int a, int b, double alpha, const double* X, int64_t ldx,
                     const double* M, double beta, const double* Z, int64_t ldz, double* Y, int64_t ldy);
-// The paired product below (a, b <= 16, M column-major) that also returns the column sums of
-// squares of Y2 after the update: sq[c * ldsq], c < b, and sq[b b] = *raised (part: cdiv(N, 256) * b doubles of
-// workspace).  Returns false, doing nothing, when the block is too wide.
 // C = alpha A B (+ beta C) on the large-problem FP64 kernel (the flexibility product): column-major,
 // M and lda even, A and B 16-byte aligned, ldb a multiple of 32 with B's rows K .. ldb zero in
 // every column.  lower: only the tiles that reach the lower triangle of C are computed.  Returns
@@ -220,14 +217,16 @@ bool dgemm_flex_partials(hipStream_t s, int64_t M, int64_t N, int64_t K, const d
 bool rows_orth_lam(hipStream_t s, int64_t N, int a, int b, int c, const double* X, int64_t ldx, const double* M1,
                    const double* R, int64_t ldr, double* Z, int64_t ldz, const double* M2, double* Lam, int64_t ldl);
 // Y = beta Y + alpha X M (N x a, a = b <= 16), and from the same pass what the next block step starts from:
-// sq[c * ldsq] = the squared column norms of the new Y and sq[a a] = *raised (skipped when sq is NULL),
-// C = X^T Y_new,
-// Bo = T^T C (its diagonal only with diag) and Mo = T Bo, a x a column-major.  part: a workspace of
+// sq[c * ldsq] = the squared column norms of the new Y and sq[a a] = *raised (skipped when sq is NULL), and
+// with C = X^T Y_new: Bo = T^T C (its diagonal only with diag) and Mo = T Bo, a x a column-major.  part: a workspace of
 // update_gram_workspace doubles.  Returns false (nothing launched) when the shape is not supported.
 size_t update_gram_workspace(int64_t N, int a, int b);
 bool rows_update_gram(hipStream_t s, int64_t N, int a, int b, const double* M, const double* X, int64_t ldx,
                       double alpha, double beta, double* Y, int64_t ldy, double* sq, int64_t ldsq, double* part,
                       const double* T, bool diag, const double* raised, double* Bo, double* Mo);
+// The paired product below (a, b <= 16, M column-major) that also returns the column sums of
+// squares of Y2 after the update: sq[c * ldsq], c < b, and sq[b b] = *raised (part: cdiv(N, 256) * b doubles of
+// workspace).  Returns false, doing nothing, when the block is too wide.
 bool rows_gemm2_sq(hipStream_t s, int64_t N, int a, int b, const double* M, double alpha1, const double* X1,
                    int64_t ldx1, double beta1, double* Y1, int64_t ldy1, double alpha2, const double* X2,
                    int64_t ldx2, double beta2, double* Y2, int64_t ldy2, double* part, const double* raised, double* sq,
@@ -291,7 +290,6 @@ void mirror_envelope(hipStream_t s, double* A, int64_t lda, int64_t n, const Env
 void potri_lower(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double* dinv, double* Y,
                  int64_t ldy);
 void fill(hipStream_t s, double* p, int64_t count, double v);
-void fill_matrix(hipStream_t s, double* p, int64_t rows, int64_t cols, int64_t ld, double v);
 void copy_matrix(hipStream_t s, const double* src, int64_t lds, double* dst, int64_t ldd, int64_t rows,
                  int64_t cols);
 void mirror_lower(hipStream_t s, double* A, int64_t lda, int64_t n);  // upper <- lower^T
@@ -308,7 +306,8 @@ void syev_small(hipStream_t s, const double* A, int m, double* V, double* w, int
 void block_coef(hipStream_t s, int m, int nr, const double* eta, const double* zr, bool diag_only, int ka,
                 const double* B, double tau, double* T, int* drops, double* raised, double* alpha, double* alpha2);
 
-// Orthonormalise the k columns of Y (n x k, ld) in place (modified Gram-Schmidt, twice).
+// Orthonormalise the k columns of Y (n x k, ld) in place: classical Gram-Schmidt taken twice up to 8 columns of
+// 4,096 rows, modified Gram-Schmidt taken twice above.
 void orthonormalize(hipStream_t s, double* Y, int64_t n, int64_t ld, int k);
 
 }  // namespace rpf

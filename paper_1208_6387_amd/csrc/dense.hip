@@ -2462,11 +2462,6 @@ __global__ void k_fill(double* p, int64_t count, double v) {
   if (i < count) p[i] = v;
 }
 
-__global__ void k_fill_matrix(double* p, int64_t rows, int64_t cols, int64_t ld, double v) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < rows * cols) p[(i / rows) * ld + (i % rows)] = v;
-}
-
 __global__ void k_copy_matrix(const double* src, int64_t lds, double* dst, int64_t ldd, int64_t rows, int64_t cols) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < rows * cols) {
@@ -2486,12 +2481,6 @@ __global__ void k_mirror_lower(double* A, int64_t lda, int64_t n) {
 void fill(hipStream_t s, double* p, int64_t count, double v) {
   if (count <= 0) return;
   hipLaunchKernelGGL(k_fill, dim3((unsigned)cdiv(count, 256)), dim3(256), 0, s, p, count, v);
-  RPF_LAUNCH_CHECK();
-}
-
-void fill_matrix(hipStream_t s, double* p, int64_t rows, int64_t cols, int64_t ld, double v) {
-  if (rows <= 0 || cols <= 0) return;
-  hipLaunchKernelGGL(k_fill_matrix, dim3((unsigned)cdiv(rows * cols, 256)), dim3(256), 0, s, p, rows, cols, ld, v);
   RPF_LAUNCH_CHECK();
 }
 
