@@ -25,7 +25,7 @@ namespace rpf {
 // One output tile (tx, ty) of K split z, called with the same tile by every thread of the
 // workgroup (consecutive tiles of the grouped kernel reuse the LDS: the barrier that opens each k
 // stage orders a tile's stores after the previous tile's reads).
-template <int BM, int BN, int WGM, int WGN, bool TA, bool TB, int BK = 16>
+template <int BM, int BN, int WGM, int WGN, bool TA, bool TB, int BK = 16, bool SHORT = false>
 __device__ __forceinline__ void dgemm_tile(int64_t M, int64_t N, int64_t K, double alpha, const double* A,
                                            int64_t lda, const double* B, int64_t ldb, double beta, double* C,
                                            int64_t ldc, int lower, int64_t kchunk, double* part, int tx, int ty,
@@ -48,6 +48,13 @@ __device__ __forceinline__ void dgemm_tile(int64_t M, int64_t N, int64_t K, doub
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
+  v4d sum[SHORT ? TM : 1][SHORT ? TN : 1];
+  if constexpr (SHORT) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) sum[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
+  }
 
   double ra[EA], rb[EB];
   auto gload = [&](int64_t k0) {
@@ -103,6 +110,15 @@ __device__ __forceinline__ void dgemm_tile(int64_t M, int64_t N, int64_t K, doub
 #pragma unroll
         for (int j = 0; j < TN; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(bf[j], af[i], acc[i][j], 0, 0, 0);
+    }
+    if constexpr (SHORT) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          sum[i][j] += acc[i][j];
+          acc[i][j] = k0 + BK < kend ? v4d{0.0, 0.0, 0.0, 0.0} : sum[i][j];
+        }
     }
   }
 
@@ -1539,16 +1555,12 @@ __device__ __forceinline__ double row_lane(double v) {
   return __builtin_amdgcn_update_dpp(v, v, 0x150 + J, 0xf, 0xf, true);
 }
 
-// 1 / d and 1 / sqrt(d) by one third-order step on the hardware estimates (within an ulp of the division),
-// d well inside the range of the format: they stand on the serial chain of the factorisation.
+// 1 / d, d well inside the range of the format, to the rounding of the division: a third-order step on the
+// hardware estimate and a last correction.  It stands on the serial chain of the factorisation.
 __device__ __forceinline__ double pivot_recip(double d) {
   const double r = __builtin_amdgcn_rcp(d), e = __builtin_fma(-d, r, 1.0);
-  return __builtin_fma(__builtin_fma(e, e, e), r, r);
-}
-__device__ __forceinline__ double pivot_rsqrt(double d) {
-  const double y = __builtin_amdgcn_rsq(d), h = d * y;
-  const double e = __builtin_fma(-h, y, 1.0) - __builtin_fma(d, y, -h) * y;  // 1 - d y y, d y unrounded
-  return __builtin_fma(e * y, __builtin_fma(0.375, e, 0.5), y);
+  const double q = __builtin_fma(__builtin_fma(e, e, e), r, r);
+  return __builtin_fma(__builtin_fma(-d, q, 1.0), q, q);
 }
 
 // Steps J .. 15 of the elimination of a symmetric 16 x 16 tile and of the identity beside it: lane c of
@@ -1655,9 +1667,8 @@ __global__ __launch_bounds__(1024) void k_potrf_diag(double* Ag, int64_t lda, in
     eliminate(a, x, pivot_recip(row_lane<0>(a[0])));
     d = own();
     if (__any(!(d > 0.0)) && lane == 0) bad = 1;
-    const double rs = pivot_rsqrt(d);
-    scale_rows(a, x, rs);
-    double dl = d * rs, dw = rs;
+    double dl = sqrt(d), dw = 1.0 / dl;
+    scale_rows(a, x, dw);
     if (far) {
       dl = ldexp(dl, e);
       dw = ldexp(dw, -e);
@@ -1851,27 +1862,35 @@ __global__ __launch_bounds__(256) void k_panel(double* C0, int64_t ld0, int64_t 
 // C -= X Y^T for two ranges of rows in one launch, Y the first N rows of X0: rows X0 (len0) only where they
 // reach the lower triangle, rows X1 (len1, the boundary rows) in full; K columns.  64 x 64
 // tiles with 64-k stages: a rank-NB update is two stages, so two load latencies.
+template <bool SHORT>
 __global__ __launch_bounds__(256) void k_rank_update(int64_t len0, const double* X0, double* C0, int64_t ld0,
                                                      int64_t len1, const double* X1, double* C1, int64_t ld1,
                                                      int64_t N, int64_t K) {
   const int t0 = (int)((len0 + 63) / 64);
   const bool second = (int)blockIdx.x >= t0;
   const int64_t ld = second ? ld1 : ld0;
-  dgemm_tile<64, 64, 2, 2, false, true, 64>(second ? len1 : len0, N, K, -1.0, second ? X1 : X0, ld, X0, ld0, 1.0,
-                                            second ? C1 : C0, ld, second ? 0 : 1, K, nullptr,
-                                            second ? (int)blockIdx.x - t0 : (int)blockIdx.x, blockIdx.y, 0);
+  dgemm_tile<64, 64, 2, 2, false, true, 64, SHORT>(second ? len1 : len0, N, K, -1.0, second ? X1 : X0, ld, X0, ld0, 1.0,
+                                                   second ? C1 : C0, ld, second ? 0 : 1, K, nullptr,
+                                                   second ? (int)blockIdx.x - t0 : (int)blockIdx.x, blockIdx.y, 0);
 }
 
 // columns [r0, cend) of the rows [r0, rend) of the factor and of the first len1 boundary rows, minus the
-// K columns from j0
+// K columns from j0.  A factor without boundary rows (dense: of S + Z Z^T, S + sigma I, a coarse matrix) adds up 64
+// products at a time, as 64-wide blocks would: in one run of 256, S+ of a 7^3 brick was 6.6 eps off and
+// that of a 7 x 11 x 5 one 12.9, now 4.9 and 9.1 (64-wide blocks: 5.3 and 11.7).  Beside the boundary rows, whose
+// S is as accurate either way, the second set of accumulators cost 4 % of a 20^3 brick's setup.
 static void rank_update(hipStream_t s, double* A, int64_t lda, const BoundaryRows& bnd, int64_t len1, int64_t j0,
                         int64_t K, int64_t r0, int64_t rend, int64_t cend) {
   const int64_t N = cend - r0;
   if (N <= 0 || K <= 0) return;
   RPF_CHECK(cdiv(N, 64) <= 65535, RPF_EINVAL, "potrf: grid too large");
-  hipLaunchKernelGGL(k_rank_update, dim3((unsigned)(cdiv(rend - r0, 64) + cdiv(len1, 64)), (unsigned)cdiv(N, 64)),
-                     dim3(256), 0, s, rend - r0, A + j0 * lda + r0, A + r0 * lda + r0, lda, len1, bnd.p + j0 * bnd.ld,
-                     bnd.p + r0 * bnd.ld, bnd.ld, N, K);
+  const dim3 grid((unsigned)(cdiv(rend - r0, 64) + cdiv(len1, 64)), (unsigned)cdiv(N, 64));
+  if (bnd.n == 0)
+    hipLaunchKernelGGL(k_rank_update<true>, grid, dim3(256), 0, s, rend - r0, A + j0 * lda + r0, A + r0 * lda + r0, lda,
+                       (int64_t)0, (const double*)nullptr, (double*)nullptr, (int64_t)0, N, K);
+  else
+    hipLaunchKernelGGL(k_rank_update<false>, grid, dim3(256), 0, s, rend - r0, A + j0 * lda + r0, A + r0 * lda + r0,
+                       lda, len1, bnd.p + j0 * bnd.ld, bnd.p + r0 * bnd.ld, bnd.ld, N, K);
   RPF_LAUNCH_CHECK();
 }
 
@@ -2153,10 +2172,10 @@ __global__ __launch_bounds__(256) void k_join_blocks(int64_t n, int64_t bw, int6
   double* X11 = X + (j / bw) * bw * bw + lj * bw + lj;
   double* Tp = T + (int64_t)blockIdx.z * h * h;
   if (!SECOND)
-    dgemm_tile<TILE, TILE, 2, 2, false, false, BK>(M, h, h - j0, 1.0, L + (j + j0) * ldl + j + h, ldl, X11 + j0, bw, 0.0,
+    dgemm_tile<TILE, TILE, 2, 2, false, false, BK, BK == 64>(M, h, h - j0, 1.0, L + (j + j0) * ldl + j + h, ldl, X11 + j0, bw, 0.0,
                                                    Tp, h, 0, h, nullptr, blockIdx.x, blockIdx.y, 0);
   else
-    dgemm_tile<TILE, TILE, 2, 2, false, false, BK>(M, h, min<int64_t>(i0 + TILE, M), -1.0, X11 + h * bw + h, bw, Tp, h,
+    dgemm_tile<TILE, TILE, 2, 2, false, false, BK, BK == 64>(M, h, min<int64_t>(i0 + TILE, M), -1.0, X11 + h * bw + h, bw, Tp, h,
                                                    0.0, X11 + h, bw, 0, h, nullptr, blockIdx.x, blockIdx.y, 0);
 }
 
@@ -2190,7 +2209,7 @@ static void invert_blocks(hipStream_t s, const double* L, int64_t ldl, int64_t n
 template <int TILE, int BK>
 __global__ __launch_bounds__(256) void k_xtx(int64_t n, const double* X, int64_t bw, double* Y, int64_t ldy) {
   const int64_t i0 = (int64_t)blockIdx.x * TILE;
-  dgemm_tile<TILE, TILE, 2, 2, true, false, BK>(n, n, n - i0, 1.0, X + i0, bw, X + i0, bw, 0.0, Y, ldy, 1, n, nullptr,
+  dgemm_tile<TILE, TILE, 2, 2, true, false, BK, BK == 64>(n, n, n - i0, 1.0, X + i0, bw, X + i0, bw, 0.0, Y, ldy, 1, n, nullptr,
                                                 blockIdx.x, blockIdx.y, 0);
 }
 
