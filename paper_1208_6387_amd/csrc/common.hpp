@@ -279,8 +279,9 @@ void few_columns_rows(hipStream_t s, int64_t M, int64_t c, int64_t K, const doub
 // TRI_BW blocks (inv).
 // upper: the strict upper triangle of L's envelope holds L^T (mirror_envelope has run on it), so the
 // transposed solve reads the rows of L^T as contiguous columns.
+// refine: the solution of each block is corrected once, for factors of any condition (dense ones).
 void potrs(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double* dinv, const TriInv& inv,
-           const Envelope& env, double* B, int64_t ldb, int64_t nrhs, bool upper = false);
+           const Envelope& env, double* B, int64_t ldb, int64_t nrhs, bool upper = false, bool refine = false);
 // A[c, r] = A[r, c] for every entry r > c of the envelope of the leading n x n factor (column block
 // t: rows up to env.rend[t]); the lower triangle is left as it is.
 void mirror_envelope(hipStream_t s, double* A, int64_t lda, int64_t n, const Envelope& env);

@@ -448,7 +448,7 @@ extern "C" rpf_status rpf_dposv(int64_t n, double* A, int64_t lda, int64_t nrhs,
     if (nrhs > 0) {
       TriInv inv;
       build_tri_inv(s, A, lda, n, dinv.p, inv);
-      potrs(s, A, lda, n, dinv.p, inv, env, B, ldb, nrhs);
+      potrs(s, A, lda, n, dinv.p, inv, env, B, ldb, nrhs, false, true);
     }
     check_status(s, st.p, "rpf_dposv");
   });
