@@ -887,7 +887,8 @@ __device__ void project_column(const SmallCoarse& G, double* x) {
 #pragma unroll
       for (int q = 0; q < DPN; ++q)
 #pragma unroll
-        for (int r = 0; r < KMAX; ++r) acc[r] += r < G.km ? g[q * G.km + r] * x[mult * DPN + q] : 0.0;
+        for (int r = 0; r < KMAX; ++r)
+          if (r < G.km) acc[r] = __builtin_fma(g[q * G.km + r], x[mult * DPN + q], acc[r]);
     }
     const int k = G.kp[G.occ_pat[s]];
 #pragma unroll
@@ -905,7 +906,7 @@ __device__ void project_column(const SmallCoarse& G, double* x) {
 #pragma unroll
       for (int u = 0; u < 16; ++u) a[u] = G.inv[(int64_t)min(h0 + u, G.nG - 1) * G.nG + tid];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) v += h0 + u < G.nG ? a[u] * c[min(h0 + u, G.nG - 1)] : 0.0;
+      for (int u = 0; u < 16; ++u) v = h0 + u < G.nG ? __builtin_fma(a[u], c[min(h0 + u, G.nG - 1)], v) : v;
     }
     y[tid] = v;
   }
@@ -919,7 +920,7 @@ __device__ void project_column(const SmallCoarse& G, double* x) {
       const double* g = G.grow + (((int64_t)mult * 2 + e) * DPN + q) * G.km;
 #pragma unroll
       for (int r = 0; r < KMAX; ++r)  // rows past the occurrence's kernel hold zeros
-        v += (r < G.km && go >= 0 && go + r < G.nG) ? g[r] * y[min(max(go + r, 0), G.nG - 1)] : 0.0;
+        if (r < G.km && go >= 0 && go + r < G.nG) v = __builtin_fma(g[r], y[go + r], v);
     }
     x[i] -= v;
   }
@@ -995,7 +996,10 @@ __global__ __launch_bounds__(512) void k_apply_small(int n_occ, int n_slots, int
 #pragma unroll
       for (int u = 0; u < 16; ++u) v[u] = M[(int64_t)min(k0 + u, nb - 1) * nb];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) a[u & 3] += k0 + u < nb ? v[u] * w[base + min(k0 + u, nb - 1)] : 0.0;
+      for (int u = 0; u < 16; ++u) {
+        const double t = __builtin_fma(v[u], w[base + min(k0 + u, nb - 1)], a[u & 3]);
+        a[u & 3] = k0 + u < nb ? t : a[u & 3];
+      }
     }
     y[r] = (a[0] + a[1]) + (a[2] + a[3]);
   }
