@@ -210,7 +210,9 @@ rpf_status feti_apply(rpf_problem pb, const rpf_pattern* patterns, int32_t m, co
 /* Y = F X in FP64 without allocating device memory, for callers that cannot
  * allocate (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc).  Same arguments, layouts and results as feti_apply with
- * prec = RPF_FP64 and flags = 0, on the same kernels.  The W-format workspace
+ * prec = RPF_FP64 and flags = 0: the same bits where feti_apply's products and
+ * their split-K slabs fit the workspace, else from products with fewer splits,
+ * equal to rounding (the sums are taken in another order).  The W-format workspace
  * (gathered blocks, product results and split-K slabs) lives in a fixed device
  * array of RPF_NOALLOC_SCRATCH_BYTES per GPU, reserved when the library is
  * loaded on that GPU and held until the process ends; its address is looked up
