@@ -276,7 +276,7 @@ void few_columns(hipStream_t s, bool ta, int64_t M, int64_t c, int64_t K, double
 void few_columns_rows(hipStream_t s, int64_t M, int64_t c, int64_t K, const double* A, int64_t lda, const double* X,
                       int64_t ldx, double* C, int64_t ldc);
 // B <- (L L^T)^{-1} B, L = leading n x n of a factor with its inverted NB blocks (dinv, see potrf) and
-// TRI_BW blocks (inv).
+// TRI_BW blocks (inv; not read for n <= NB).
 // upper: the strict upper triangle of L's envelope holds L^T (mirror_envelope has run on it), so the
 // transposed solve reads the rows of L^T as contiguous columns.
 // refine: the solution of each block is corrected once, for factors of any condition (dense ones).

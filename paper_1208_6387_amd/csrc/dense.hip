@@ -2470,10 +2470,12 @@ void potrs(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double*
     RPF_HIP(hipStreamSynchronize(s));  // the bounds buffer is freed on return
     return;
   }
-  // at most 512 MB of second buffer, at least 512 columns at a time
+  // at most 512 MB of second buffer, at least 512 columns at a time; one NB block needs its own inverse only (and
+  // no correction up to 64 rows, which were one block of the 64-row inverses)
   const int64_t most = std::max<int64_t>(512, ((int64_t)1 << 26) / n);
   const int64_t nT = cdiv(n, TRI_BW), per = TRI_BW / NB;
   DevBuf<double> F((size_t)n * std::min(nrhs, most)), Lt, Rt;
+  refine = refine && n > 64;
   if (refine) {
     Lt.alloc((size_t)TRI_BW * TRI_BW);
     Rt.alloc((size_t)TRI_BW * std::min(nrhs, most));
@@ -2482,8 +2484,11 @@ void potrs(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double*
     const int64_t nc = std::min(most, nrhs - c0);
     // X = op(L_TT)^{-1} Y for the jb rows of block t
     auto block = [&](bool back, int64_t t, int64_t jb, const double* Y, int64_t ldy, double* X, int64_t ldx) {
-      const double* inv_t = (back ? inv.up.p : inv.lo.p) + t * TRI_BW * TRI_BW;
-      few_columns(s, false, jb, nc, jb, 1.0, inv_t, TRI_BW, Y, ldy, 0.0, X, ldx);
+      // op(L_TT)^{-1} as it is stored: dinv holds it by rows
+      const bool one = n <= NB, ta = one && !back;
+      const double* inv_t = one ? dinv : (back ? inv.up.p : inv.lo.p) + t * TRI_BW * TRI_BW;
+      const int64_t ldi = one ? NB : TRI_BW;
+      few_columns(s, ta, jb, nc, jb, 1.0, inv_t, ldi, Y, ldy, 0.0, X, ldx);
       if (!refine) return;
       const int64_t j0 = t * TRI_BW;
       hipLaunchKernelGGL(k_copy_lower, dim3((unsigned)cdiv(jb * jb, 256)), dim3(256), 0, s, jb, L + j0 * ldl + j0, ldl, Lt.p,
@@ -2491,7 +2496,7 @@ void potrs(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double*
       RPF_LAUNCH_CHECK();
       copy_matrix(s, Y, ldy, Rt.p, TRI_BW, jb, nc);
       few_columns(s, back, jb, nc, jb, -1.0, Lt.p, TRI_BW, X, ldx, 1.0, Rt.p, TRI_BW);
-      few_columns(s, false, jb, nc, jb, 1.0, inv_t, TRI_BW, Rt.p, TRI_BW, 1.0, X, ldx);
+      few_columns(s, ta, jb, nc, jb, 1.0, inv_t, ldi, Rt.p, TRI_BW, 1.0, X, ldx);
     };
     for (int64_t t = 0; t < nT; ++t) {
       const int64_t j0 = t * TRI_BW, jb = std::min(TRI_BW, n - j0), r0 = j0 + jb;

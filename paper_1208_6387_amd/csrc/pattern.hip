@@ -446,8 +446,8 @@ extern "C" rpf_status rpf_dposv(int64_t n, double* A, int64_t lda, int64_t nrhs,
     const Envelope env = Envelope::dense(n);
     potrf(s, A, lda, n, env, dinv.p, st.p);
     if (nrhs > 0) {
-      TriInv inv;
-      build_tri_inv(s, A, lda, n, dinv.p, inv);
+      TriInv inv;  // (one NB block is solved through dinv)
+      if (n > NB) build_tri_inv(s, A, lda, n, dinv.p, inv);
       potrs(s, A, lda, n, dinv.p, inv, env, B, ldb, nrhs, false, true);
     }
     check_status(s, st.p, "rpf_dposv");
