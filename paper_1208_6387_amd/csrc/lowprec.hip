@@ -775,15 +775,18 @@ void apply_F_lowprec(rpf_problem pb, const rpf_pattern* pats, int m, const doubl
   // cache line (unaligned rows would make each chunk touch two lines)
   std::vector<int64_t> off(pb->n_pat + 1, 0), ld(pb->n_pat);
   // split K (chunks of multiples of 64) while the 64 x 64 output tiles alone give fewer than
-  // ~4 workgroups per CU; the scatter sums the split slabs
+  // ~4 workgroups per CU; the scatter sums the split slabs in FP64.  (Fewer pieces, which fill the chip
+  // once, are faster, but the FP32 sums grow longer: 64 patterns of 12^3 at 8 columns 64.9 us in 6 pieces, 70.6 in 8,
+  // error 4.5361e-6 and 4.5356e-6; at 24 columns 122 and 134 us, 4.560e-6 and 4.554e-6.)
   std::vector<int64_t> yoff(pb->n_pat + 1, 0), ldr(pb->n_pat, 0);
   std::vector<int> nsp(pb->n_pat, 1), kch(pb->n_pat, 0), tile_m(pb->n_pat, 64), tile_n(pb->n_pat, 64);
   // a grouped schedule (bf16 forms only) runs every pattern's product in one persistent launch of
   // its tile, each pattern's K split set by the schedule's work target
   Schedule sc = schedule_for(pb, m, prec);
   // without a schedule, several small patterns share one launch too (the uneven three-pattern batch at 8
-  // columns: 36 us an application against 64 us in a launch per pattern)
-  if (split && sc.tile == 0 && many_small_products(pb, pats, m, 256, 240)) sc = Schedule{64, 1024};
+  // columns: 36 us an application against 64 us in a launch per pattern), with K in no fewer pieces than there
+  const bool ruled = split && sc.tile == 0 && many_small_products(pb, pats, m, 256, 240);
+  if (ruled) sc = Schedule{64, 1024};
   const int gtile = (split && (sc.tile == 64 || sc.tile == 128)) ? sc.tile : 0;
   for (int p = 0; p < pb->n_pat; ++p) {
     const int nb = pats[p]->n_b;
@@ -795,17 +798,19 @@ void apply_F_lowprec(rpf_problem pb, const rpf_pattern* pats, int m, const doubl
     int tm = (split && cdiv(nb, 256) * cdiv(cols, (int64_t)256) >= 240) ? 256
              : (split && nb >= 128 && cols >= 128)                       ? 128
                                                                          : 64;
-    if (gtile) tm = gtile;
+    if (gtile && !ruled) tm = gtile;
     else if (split && sc.tile == 256) tm = 256;
     if (tm == 256 && pb->weighted) tm = 128;  // the non-Boolean scatter reads column-major results
-    const int tn = tm;
-    tile_m[p] = tm;
-    tile_n[p] = tn;
-    const int64_t tiles = std::max<int64_t>(1, cdiv(nb, tm) * cdiv(cols, tn));
+    const int64_t tiles = std::max<int64_t>(1, cdiv(nb, tm) * cdiv(cols, (int64_t)tm));
     int sp = (int)std::min<int64_t>(std::max<int64_t>(1, 1024 / tiles), std::max<int64_t>(1, ld[p] / 256));
     sp = tm == 256 ? 1 : std::min(sp, 8);
     kch[p] = (int)(cdiv(cdiv(ld[p], sp), 64) * 64);
-    if (gtile) kch[p] = (int)group_kchunk(nb, ld[p], cols, gtile, sc.work, 64);
+    if (gtile) {
+      const int own = ruled ? kch[p] : INT32_MAX;
+      kch[p] = std::min(own, (int)group_kchunk(nb, ld[p], cols, gtile, sc.work, 64));
+      tm = gtile;
+    }
+    tile_m[p] = tile_n[p] = tm;
     nsp[p] = (int)cdiv(ld[p], kch[p]);
     // the 256 x 256 kernel's row-major result: n_b rows of ldr[p] (a multiple of 16 floats)
     ldr[p] = cdiv(cols, (int64_t)16) * 16;

@@ -67,3 +67,21 @@ def test_odd_pattern_before_the_large_kernel(R, sizes, occs, m):
     tol = 4 * max(sizes) * np.finfo(float).eps
     for a, b in ((Y, G), (N, G), (D, E)):
         assert float((a - b).norm(dim=0).max()) <= tol * float(b.norm(dim=0).max())
+
+
+def test_grouped_low_precision_keeps_its_pieces(R):
+    """Without a schedule several small patterns share a launch, with K in as many pieces as each would have alone (8
+    here: 21 x 2 tiles of 128 x 128), since FP32 sums run within a piece: the same bits as a schedule that asks
+    for 8, its pieces' sums no longer."""
+    pats, pb = _structure(R, (2598, 2402), (33, 33), 5)
+    m = 7
+    assert 1024 // (-(-2598 // 128) * -(-33 * m // 128)) >= 8
+    for q in pats:
+        R.pattern_condense(q, R.BF16X3)
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    X = torch.randn((pb.n_lambda, m), dtype=torch.float64, device="cuda", generator=gen)
+    Y = R.feti_apply(pb, pats, X, prec=R.BF16X3)
+    R.problem_set_schedule(pb, m, R.BF16X3, 64, 4096)
+    G = R.feti_apply(pb, pats, X, prec=R.BF16X3)
+    torch.cuda.synchronize()
+    assert torch.equal(Y, G)
