@@ -24,7 +24,8 @@ namespace rpf {
 // into registers while the current one is consumed.
 // One output tile (tx, ty) of K split z, called with the same tile by every thread of the
 // workgroup (consecutive tiles of the grouped kernel reuse the LDS: the barrier that opens each k
-// stage orders a tile's stores after the previous tile's reads).
+// stage orders a tile's stores after the previous tile's reads).  SHORT: each k stage is added up by itself and
+// then to the tile, so that the rounding grows with the stage's length and not with K's.
 template <int BM, int BN, int WGM, int WGN, bool TA, bool TB, int BK = 16, bool SHORT = false>
 __device__ __forceinline__ void dgemm_tile(int64_t M, int64_t N, int64_t K, double alpha, const double* A,
                                            int64_t lda, const double* B, int64_t ldb, double beta, double* C,
@@ -1603,8 +1604,9 @@ __device__ __forceinline__ void scale_rows(double (&a)[16], double (&x)[16], dou
 //   (2) L_ik = A_ik W_kk^T for the tiles below, and W_k,j = W_kk Acc_k,j for the tiles left of it;
 //   (3) A_ij -= L_ik L_jk^T and Acc_ij -= L_ik W_kj, tile by tile on FP64 MFMA.  Wave 0 takes the next
 //       diagonal tile and goes straight on with its step (1) while the other waves do the rest.
-// It is bound by the serial step (1), about 1.5 us of 2 us a step.  Rows and columns from jb on are
-// those of the identity.  dinv: W by rows, dinv[r NB + c], zeros above the diagonal.
+// A block takes 34.5 us by the device's clock: 3.2 us for the entry loads, 0.5 for the last store, and 3.9 a step:
+// 2.4 the serial tile (1), 0.35 its update before it, 0.6 the products (2), 0.5 waiting for the other waves
+// (1.1 in the second step, none in the last).  Rows and columns from jb on are those of the identity.  dinv: W by rows, dinv[r NB + c], zeros above the diagonal.
 __global__ __launch_bounds__(1024) void k_potrf_diag(double* Ag, int64_t lda, int jb, double* dinv, int* status,
                                                     int blk) {
   static_assert(NB == 128, "k_potrf_diag assumes 128 x 128 blocks");
@@ -2213,6 +2215,10 @@ __global__ __launch_bounds__(256) void k_xtx(int64_t n, const double* X, int64_t
                                                 blockIdx.x, blockIdx.y, 0);
 }
 
+// The 64 x 64 tiles here and in k_join_blocks add up 64 products at a time: with one run of sums S+ of a 9 x 8 x 8
+// brick was 7.5 eps off, where solves by 64-row blocks had given 6.9; now 5.8 (7^3: 6.1, 5.3, 4.9).  The 128 x 128
+// ones do without (S+ at 17^3: 20 eps, 22 by blocks).
+//
 // Y = (L L^T)^{-1} from a dense lower Cholesky factor L (n x n, ld ldl) and its inverted diagonal
 // blocks: X = L^{-1} by joining blocks, then Y = X^T X, its lower triangle only (the upper one is left
 // to the caller, see mirror_lower and add_outer).  Two thirds n^3 flops in about 2 log2(n / NB) + 2
@@ -2381,8 +2387,7 @@ __global__ __launch_bounds__(64 * W) void k_skinny(int64_t M, int64_t c, int64_t
   }
 }
 
-// Two row tiles a workgroup where that still gives every CU one; else the waves that leave each about 64 k
-// (n_G = 3,072, 16 columns: 33 us with four waves)
+// Two row tiles a workgroup where that still gives every CU one, else one.
 static void launch_skinny(hipStream_t s, bool ta, int64_t M, int64_t c, int64_t K, double alpha, const double* A,
                           int64_t lda, const double* X, int64_t xk, int64_t xj, double beta, double* C, int64_t cm,
                           int64_t cj) {
@@ -2407,7 +2412,8 @@ static void launch_skinny(hipStream_t s, bool ta, int64_t M, int64_t c, int64_t 
   RPF_LAUNCH_CHECK();
 }
 
-// up to this many columns k_skinny is the faster one (64 x 64 tiles re-read less of A above)
+// up to this many columns k_skinny is the faster one (64 x 64 tiles re-read less of A above): an application with 888
+// rows takes 26.7 us at 96 columns, and 34.3 on the tiles at 104; with 486 rows 23.6 and 54.3
 constexpr int64_t SKINNY = 96;
 void few_columns(hipStream_t s, bool ta, int64_t M, int64_t c, int64_t K, double alpha, const double* A, int64_t lda,
                  const double* X, int64_t ldx, double beta, double* C, int64_t ldc) {

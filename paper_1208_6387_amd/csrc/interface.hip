@@ -705,7 +705,7 @@ F64Plan plan_F64(rpf_problem pb, const rpf_pattern* pats, int m, const Schedule&
   //   columns: 45 us an application against 82 us in a launch per pattern);
   // - a small pattern with few columns: the product for few columns, which waits for memory a few times
   //   instead of once per 16 k (51 rows and 12 columns: 2.4 us against 7.6; 888
-  //   rows and 81 columns: 10 us against 23);
+  //   rows and 81 columns: 10 us against 23; an application with 888 rows and 96 columns: 27 us against 52);
   // - where the 128 x 128 tiles of the large-problem kernel, times K pieces of at least 256, fill
   //   three quarters of the 256 CUs or more: that kernel, with the number of pieces that leaves
   //   the last round fullest (2,598 rows and 512 columns: 127 us against 201); its W blocks
