@@ -2476,9 +2476,9 @@ void potrs(hipStream_t s, const double* L, int64_t ldl, int64_t n, const double*
     RPF_HIP(hipStreamSynchronize(s));  // the bounds buffer is freed on return
     return;
   }
-  // at most 512 MB of second buffer, at least 512 columns at a time; one NB block needs its own inverse only (and
+  // at most 512 MB of second buffer, at least 512 columns at a time, at most a grid's; one NB block needs its own inverse only (and
   // no correction up to 64 rows, which were one block of the 64-row inverses)
-  const int64_t most = std::max<int64_t>(512, ((int64_t)1 << 26) / n);
+  const int64_t most = std::min<int64_t>((int64_t)1 << 22, std::max<int64_t>(512, ((int64_t)1 << 26) / n));
   const int64_t nT = cdiv(n, TRI_BW), per = TRI_BW / NB;
   DevBuf<double> F((size_t)n * std::min(nrhs, most)), Lt, Rt;
   refine = refine && n > 64;

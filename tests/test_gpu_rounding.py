@@ -120,3 +120,14 @@ def test_dense_solve_residual(R, n, cond):
         R.dposv(Ad, Bd)
         torch.cuda.synchronize()
         assert residual(Bd.cpu().numpy()) <= 2 * residual(ref[:, :cols])
+
+
+def test_more_columns_than_the_second_buffer(R):
+    """Columns are taken in turn past the second buffer's bound (2^22 of them for three rows)."""
+    n, cols = 3, (1 << 22) + 5
+    A = np.array([[4.0, 1.0, 0.5], [1.0, 3.0, 0.25], [0.5, 0.25, 2.0]])
+    B = torch.randn((cols, n), dtype=torch.float64, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    X = B.clone()
+    R.dposv(torch.from_numpy(A.copy()).cuda().T, X.T)
+    r = X @ torch.from_numpy(A).cuda() - B
+    assert float(r.abs().max()) <= 32 * np.finfo(float).eps * float(X.abs().max()) * 5.5
